@@ -126,6 +126,7 @@ struct KindBase {
   static constexpr int WM = WM_, WN = WN_, MI = MI_, NI = NI_, NSTAGE = NSTAGE_;
   static constexpr bool DBUF = DBUF_;
   static constexpr int BK = BK_;             // K per LDS stage (16-bit path: 32 or 64)
+  static constexpr int SPLIT = 0;            // mainloop_split: the split operands are A (1) or B (2)
   static_assert(BK == 32 || BK == 64, "K tile");
   static constexpr int THREADS = 64 * WM * WN;
   static constexpr int ROWS_A = 32 * MI * WM, ROWS_B = 32 * NI * WN;   // workgroup tile
@@ -143,6 +144,17 @@ struct KindBase {
   static constexpr int mn_half(int o) { return __builtin_popcount(MN & ((1u << o) - 1u)) & 1; }
 };
 
+// Kinds of the split-stage loop (16-bit): accumulator set p multiplies the
+// common operand by split operand p; 8 waves of 2 x (64 x 64). SPLIT 1: A0,
+// A1 (128 rows each) against B (256 columns); 2: A (128 rows) against B0, B1
+// (256 columns each).
+#define LACT_SPLIT_KIND(NAME, MNMASK, WHICH)                                                               \
+  struct NAME : KindBase<(WHICH == 1 ? 2 : 1), (WHICH == 1 ? 1 : 2), 2, MNMASK, 2, 4, 2, 2, 2, true, 64> { \
+    static constexpr int SPLIT = WHICH;                                                                    \
+    static constexpr int pa(int p) { return WHICH == 1 ? p : 0; }                                          \
+    static constexpr int pb(int p) { return WHICH == 1 ? 0 : p; }                                          \
+  }
+
 #define LACT_KIND(NAME, NA, NB, NACC, MNMASK, WM, WN, MI, NI, NS, DBUF, BK, PA, PB) \
   struct NAME : KindBase<NA, NB, NACC, MNMASK, WM, WN, MI, NI, NS, DBUF, BK> {         \
     static constexpr int pa(int p) { return PA; }                                  \
@@ -156,21 +168,21 @@ struct KindBase {
 // bytes and more per K row) keep 32 K and twice the stages.
 // Apply GEMM-1 and the key forward, hidden-major: A = W1, W3 (hidden rows),
 // B = Q or K (token rows).
-LACT_KIND(KApply16, 2, 1, 2, 0u, 2, 4, 2, 2, 2, true, 64, p, 0 * p);
+LACT_SPLIT_KIND(KApply16, 0u, 1);
 // Hidden backward of the key forward: A = W2 read down its columns (hidden
 // rows), B = V; accumulator D^T = (V W2)^T. Runs after KApply16 in the same
 // workgroup, whose accumulators stay live.
 LACT_KIND(KDual16, 1, 1, 1, 1u, 2, 4, 2, 2, 2, true, 64, 0 * p, 0 * p);
 // Apply GEMM-2, feature-major: A = W2 (feature rows), B = hidden (token rows).
-LACT_KIND(KOut16, 1, 1, 1, 0u, 2, 4, 4, 2, 2, true, 64, 0 * p, 0 * p);
+LACT_SPLIT_KIND(KOut16, 0u, 1);
 // Gradients: A = eta dz1, eta dz3 (hidden rows), B = K (feature rows), all token-major.
-LACT_KIND(KGrad13_16, 2, 1, 2, 7u, 2, 4, 2, 2, 4, true, 32, p, 0 * p);
+LACT_SPLIT_KIND(KGrad13_16, 7u, 1);
 // A = V (feature rows), B = eta hidden (hidden rows), token-major.
-LACT_KIND(KGrad2_16, 1, 1, 1, 3u, 2, 4, 4, 2, 4, true, 32, 0 * p, 0 * p);
+LACT_SPLIT_KIND(KGrad2_16, 7u, 1);
 // Gradient with the weight update of whole rows (GRAD_UPD): A = eta dz1,
 // eta dz3 or V (128 rows of W1, W3 or W2), B = K or eta hidden (every column,
 // up to 512), token-major; waves of 64 x 128, 4 stages of 40 KiB.
-LACT_KIND(KGradU16, 1, 1, 1, 3u, 2, 4, 2, 4, 4, true, 32, 0 * p, 0 * p);
+LACT_SPLIT_KIND(KGradU16, 7u, 2);
 // Narrow shapes (16-bit, d <= 128): the feature dimension fills 128 tile rows
 // instead of half of 256. Apply GEMM-2: 128 features x 512 tokens; gradients
 // of W1, W3: 256 hidden x 128 features; gradient of W2: 128 features x 256
@@ -207,10 +219,11 @@ LACT_KIND(KNsK32, 1, 1, 1, 0u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
 // Last Newton-Schulz step with the weight update (k_ns_final): A = B (rows of
 // the polynomial, K-contiguous), B = X4 read down its columns; 128 rows x up
 // to 512 columns, waves of 64 x 128, 2 stages of 80 KiB.
-LACT_KIND(KNsRow16, 1, 1, 1, 2u, 2, 4, 2, 4, 2, true, 64, 0 * p, 0 * p);
+LACT_SPLIT_KIND(KNsRow16, 6u, 2);
 LACT_KIND(KNsMN32, 1, 1, 1, 3u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
 LACT_KIND(KNsTY32, 1, 1, 1, 1u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
 #undef LACT_KIND
+#undef LACT_SPLIT_KIND
 
 template <typename T, bool BIG> struct NsKinds;
 template <> struct NsKinds<_Float16, true> {
@@ -768,6 +781,266 @@ __device__ __forceinline__ void mainloop_dma(uint8_t* smem, const View (&ops)[K:
   asm volatile("" ::: "memory");
 }
 
+// ---- split-stage loop ------------------------------------------------------
+// Two accumulator sets that share one operand (the common one, C) and differ
+// in the other (S0, S1): W1 / W3 rows against one token tile, the two halves
+// of an output tile's rows, or of its columns. A 64-K stage is worked in two
+// halves: first S0 against C, keeping C's fragments of all four 16-K substeps
+// in registers, then S1 against the kept fragments. So the LDS of C and S0 is
+// free for the tile after next half a stage before S1's, every DMA has one and
+// a half stages to land in the same two LDS slots (with whole stages it has
+// one), and the DMA instructions are spread over the MFMAs one at a time
+// instead of all at once behind a barrier, where their issue stalls the
+// matrix cores (the memory pipe of a CU takes about 32 KiB in flight).
+// Per half: the fragments of substep s+1 are read while s multiplies; before
+// the last multiplies of a half, wait for the next half's tile and barrier.
+// Against whole 64-K stages (32-K for the gradients), one process: NVS 256K
+// (K = 768) gradient 1693 -> 1474 us at 70% of the matrix cores' cycles
+// (before 57%; the clock falls from 1.85 to 1.71 GHz, the launch is then bound
+// by power), apply 1442 -> 1264 us, output 648 -> 584 us; LM shape (K = 512)
+// 3423 -> 3286 us per forward, 12611 -> 12056 us per backward: of an apply
+// tile's 18.7 us there, 11.8 are this loop (9.2 with its DMA left out).
+
+// One operand's DMA, one instruction at a time.
+template <class K, int O>
+struct DmaT {
+  using D = Dma<K, O>;
+  static constexpr int N = D::SLOTS;
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t tm;   // this lane's out-of-range bits (K-contiguous operands' last tile)
+  // tail: kOOB for lanes whose chunk lies past K in the last k-tile
+  static __device__ __forceinline__ uint32_t tail_mask(int64_t nk, int nkt) {
+    if (D::MN) return 0u;
+    const int c = (threadIdx.x % D::CPK) ^ swz_k<K::BK>(threadIdx.x / D::CPK);
+    return c * 8 >= nk - (int64_t)(nkt - 1) * K::BK ? kOOB : 0u;
+  }
+  __device__ __forceinline__ DmaT(const View& v, int kt, uint32_t tail) : tm(tail) {
+    const uint8_t* base;
+    int64_t span;
+    if (!D::MN) {
+      base = v.p + (int64_t)kt * K::BK * 2;
+      const int64_t rows = v.nrows < D::ROWS ? v.nrows : D::ROWS;
+      span = rows > 0 ? (rows - 1) * v.ld_b + K::BK * 2 : 0;
+    } else {
+      base = v.p + (int64_t)kt * K::BK * v.ld_b;
+      int64_t rows = v.nk - (int64_t)kt * K::BK;
+      rows = rows < 0 ? 0 : (rows > K::BK ? K::BK : rows);
+      span = rows * v.ld_b;
+    }
+    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)span, kRawBufferFlags);
+  }
+  // slot i of the tile at `tile` (w: this wave, in a scalar register)
+  __device__ __forceinline__ void one(uint8_t* tile, const uint32_t (&vo)[kMaxSlots], int i, int w) const {
+    const uint32_t off = D::MN ? vo[i] : (vo[i] | tm);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, to_lds(tile + (i * K::THREADS + w * 64) * 16), 16, off, 0, 0, 0);
+  }
+};
+
+template <int OFF>
+__device__ __forceinline__ u32x4_t lds_read_b128_at(uint32_t a) {
+  u32x4_t r;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(a), "n"(OFF));
+  return r;
+}
+template <int OFF>
+__device__ __forceinline__ u32x2_t lds_read_tr_at(uint32_t a) {
+  u32x2_t r;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(a), "n"(OFF));
+  return r;
+}
+
+// Fragment addresses of one operand for this wave (two 32-row blocks): the
+// lane's base in slot 0; block j and substep s are an XOR and an immediate.
+template <class K, int O>
+struct FragAddr {
+  static constexpr bool MN = K::is_mn(O);
+  static constexpr int PITCH = MN ? K::rows(O) * 2 : K::BK * 2;
+  static constexpr int READS = MN ? 4 : 2;   // LDS instructions per substep
+  uint32_t a;
+  __device__ __forceinline__ FragAddr(const uint8_t* tile, int rb) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t base = lds_addr(tile) + K::op_off(O);
+    if (!MN) {
+      a = base + lds_off_k<K::BK>(rb + (lane & 31), lane >> 5);
+    } else {
+      const int g = lane >> 4, sl = lane & 15;
+      const int mn = rb + 16 * (g & 1) + 4 * (sl & 3), kr = 8 * (g >> 1) + (sl >> 2);
+      a = base + kr * PITCH + (((mn >> 3) ^ swz_mn(kr)) << 4) + (((mn >> 2) & 1) << 3);
+    }
+  }
+  // the two fragments of substep S, slot offset so (bytes)
+  template <int S>
+  __device__ __forceinline__ void read(u32x4_t (&f)[2], uint32_t so) const {
+    if constexpr (!MN) {   // rows 32 apart share their swizzle; substep s flips chunk bits 1-2
+      const uint32_t x = (a + so) ^ (uint32_t)(S << 5);
+      f[0] = lds_read_b128_at<0>(x);
+      f[1] = lds_read_b128_at<32 * PITCH>(x);
+    } else {               // columns 32 apart flip chunk bit 2; K rows 4 apart share their swizzle
+      const uint32_t x = a + so, y = x ^ 64u;
+      const u32x2_t l0 = lds_read_tr_at<16 * S * PITCH>(x), h0 = lds_read_tr_at<(16 * S + 4) * PITCH>(x);
+      const u32x2_t l1 = lds_read_tr_at<16 * S * PITCH>(y), h1 = lds_read_tr_at<(16 * S + 4) * PITCH>(y);
+      f[0] = u32x4_t{l0[0], l0[1], h0[0], h0[1]};
+      f[1] = u32x4_t{l1[0], l1[1], h1[0], h1[1]};
+    }
+  }
+};
+
+template <int N>
+__device__ __forceinline__ void wait_lgkm(u32x4_t (&a)[2], u32x4_t (&b)[2]) {
+  static_assert(N >= 0 && N < 16, "lgkmcnt range");
+  asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]) : "n"(N));
+}
+
+// One 32x32x16 product per (mi, ni): the common operand is B (SPLIT == 1) or A.
+template <typename T, class K>
+__device__ __forceinline__ void mfma_one(f32x16_t& acc, const u32x4_t& c, const u32x4_t& s) {
+  const u32x4_t &a = K::SPLIT == 1 ? s : c, &b = K::SPLIT == 1 ? c : s;
+  if constexpr (__is_same(T, _Float16))
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), acc, 0,
+                                                 0, 0);
+  else
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                  acc, 0, 0, 0);
+}
+
+// Substep S of a half: four products of acc set P with the DMA instructions
+// `dma(first, last)` of this substep between them.
+template <typename T, class K, class F>
+__device__ __forceinline__ void half_mfma(f32x16_t (&acc)[2][2], const u32x4_t (&c)[2], const u32x4_t (&s)[2], F&& dma) {
+#pragma unroll
+  for (int ci = 0; ci < 2; ++ci) {
+#pragma unroll
+    for (int sj = 0; sj < 2; ++sj)
+      mfma_one<T, K>(K::SPLIT == 1 ? acc[sj][ci] : acc[ci][sj], c[ci], s[sj]);
+    __builtin_amdgcn_sched_barrier(0);
+    dma(ci);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <typename T, class K, int SLOT = K::STAGE, class Next = NoNext>
+__device__ __forceinline__ void mainloop_split(uint8_t* smem, const View (&ops)[3], int64_t nk, Acc<K>& acc,
+                                               Next* next = nullptr) {
+  static_assert(K::BK == 64 && K::MI == 2 && K::NI == 2 && K::NACC == 2 && K::NOPS == 3, "split kinds");
+  constexpr int OC = K::SPLIT == 1 ? 2 : 0, O0 = K::SPLIT == 1 ? 0 : 1, O1 = O0 + 1;
+  using DC = DmaT<K, OC>;
+  using D0 = DmaT<K, O0>;
+  using D1 = DmaT<K, O1>;
+  constexpr int LC = DC::N, L0 = D0::N, L1 = D1::N, LCS = LC + L0;
+  constexpr int RC = FragAddr<K, OC>::READS, RS = FragAddr<K, O0>::READS;
+  static_assert(2 * (LCS + L1) < 64, "DMA in flight exceeds vmcnt");
+  const int nkt = (int)((nk + K::BK - 1) / K::BK);
+  if (nkt <= 0) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t vc[kMaxSlots], v0[kMaxSlots], v1[kMaxSlots];
+  DC::D::offsets(vc, ops[OC]);
+  D0::D::offsets(v0, ops[O0]);
+  D1::D::offsets(v1, ops[O1]);
+  const uint32_t tailc = DC::tail_mask(nk, nkt), tail0 = D0::tail_mask(nk, nkt);
+  auto slot = [&](int kt) { return smem + (kt & 1) * SLOT; };
+  auto tl = [&](uint32_t t, int kt) { return kt == nkt - 1 ? t : 0u; };
+  // whole-tile issue (prologue)
+  auto issue_cs = [&](int kt) {
+    const DC dc(ops[OC], kt, tl(tailc, kt));
+    const D0 d0(ops[O0], kt, tl(tail0, kt));
+#pragma unroll
+    for (int i = 0; i < LC; ++i) dc.one(slot(kt) + K::op_off(OC), vc, i, w);
+#pragma unroll
+    for (int i = 0; i < L0; ++i) d0.one(slot(kt) + K::op_off(O0), v0, i, w);
+  };
+  const int wc = (K::SPLIT == 1 ? wave_n<K>() : wave_m<K>()) * 64;
+  const int ws = (K::SPLIT == 1 ? wave_m<K>() : wave_n<K>()) * 64;
+  const FragAddr<K, OC> ac(smem, wc);
+  const FragAddr<K, O0> a0(smem, ws);
+  const FragAddr<K, O1> a1(smem, ws);
+  issue_cs(0);
+  {
+    const D1 d1(ops[O1], 0, tl(tail0, 0));
+#pragma unroll
+    for (int i = 0; i < L1; ++i) d1.one(slot(0) + K::op_off(O1), v1, i, w);
+  }
+  if (nkt > 1) {
+    issue_cs(1);
+    wait_vmcnt<L1 + LCS>();
+  } else {
+    wait_vmcnt<L1>();
+  }
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  u32x4_t fc[4][2], fs[2][2];
+  ac.template read<0>(fc[0], 0);
+  a0.template read<0>(fs[0], 0);
+  for (int kt = 0; kt < nkt; ++kt) {
+    const uint32_t so = (uint32_t)((kt & 1) * SLOT), sn = SLOT - so;
+    uint8_t* const cur = smem + so;
+    uint8_t* const oth = smem + sn;
+    const bool more1 = kt + 1 < nkt, more2 = kt + 2 < nkt;
+    {   // first half: S0; S1 of the next tile goes out
+      const D1 d1(ops[O1], kt + 1, tl(tail0, kt + 1));
+      auto dma = [&](int s, int ci) {
+#pragma unroll
+        for (int i = 0; i < L1; ++i)
+          if (i * 8 / L1 == 2 * s + ci && more1) d1.one(oth + K::op_off(O1), v1, i, w);
+      };
+      ac.template read<1>(fc[1], so);
+      a0.template read<1>(fs[1], so);
+      wait_lgkm<RC + RS>(fc[0], fs[0]);
+      half_mfma<T, K>(acc[0], fc[0], fs[0], [&](int ci) { dma(0, ci); });
+      ac.template read<2>(fc[2], so);
+      a0.template read<2>(fs[0], so);
+      wait_lgkm<RC + RS>(fc[1], fs[1]);
+      half_mfma<T, K>(acc[0], fc[1], fs[1], [&](int ci) { dma(1, ci); });
+      ac.template read<3>(fc[3], so);
+      a0.template read<3>(fs[1], so);
+      wait_lgkm<RC + RS>(fc[2], fs[0]);
+      half_mfma<T, K>(acc[0], fc[2], fs[0], [&](int ci) { dma(2, ci); });
+      // this wave has read C and S0 of the tile; S1 of it has landed
+      wait_lgkm<0>(fc[3], fs[1]);
+      if (more1) wait_vmcnt<LCS + (L1 * 6 + 7) / 8>();
+      else wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      a1.template read<0>(fs[0], so);
+      half_mfma<T, K>(acc[0], fc[3], fs[1], [&](int ci) { dma(3, ci); });
+    }
+    {   // second half: S1 against the kept C; C and S0 of the tile after next go out
+      const DC dc(ops[OC], kt + 2, tl(tailc, kt + 2));
+      const D0 d0(ops[O0], kt + 2, tl(tail0, kt + 2));
+      auto dma = [&](int s, int ci) {
+#pragma unroll
+        for (int i = 0; i < LCS; ++i)
+          if (i * 8 / LCS == 2 * s + ci && more2) {
+            if (i < LC) dc.one(cur + K::op_off(OC), vc, i, w);
+            else d0.one(cur + K::op_off(O0), v0, i - LC, w);
+          }
+      };
+      a1.template read<1>(fs[1], so);
+      wait_lgkm<RS>(fc[0], fs[0]);
+      half_mfma<T, K>(acc[1], fc[0], fs[0], [&](int ci) { dma(0, ci); });
+      a1.template read<2>(fs[0], so);
+      wait_lgkm<RS>(fc[1], fs[1]);
+      half_mfma<T, K>(acc[1], fc[1], fs[1], [&](int ci) { dma(1, ci); });
+      a1.template read<3>(fs[1], so);
+      wait_lgkm<RS>(fc[2], fs[0]);
+      half_mfma<T, K>(acc[1], fc[2], fs[0], [&](int ci) { dma(2, ci); });
+      // this wave has read S1 of the tile; C and S0 of the next one have landed
+      wait_lgkm<0>(fc[3], fs[1]);
+      if (more2) wait_vmcnt<L1 + (LCS * 6 + 7) / 8>();
+      else if (more1) wait_vmcnt<L1>();
+      else wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (more1) {
+        ac.template read<0>(fc[0], sn);
+        a0.template read<0>(fs[0], sn);
+      }
+      half_mfma<T, K>(acc[1], fc[3], fs[1], [&](int ci) { dma(3, ci); });
+    }
+  }
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <class K>
 __device__ __forceinline__ void zero_acc(Acc<K>& acc) {
 #pragma unroll
@@ -784,7 +1057,8 @@ __device__ __forceinline__ void zero_acc(Acc<K>& acc) {
 template <typename T, class K>
 __device__ __forceinline__ void mainloop(uint8_t* smem, const View (&ops)[K::NOPS], int64_t nk, Acc<K>& acc) {
   zero_acc<K>(acc);
-  if constexpr (sizeof(T) == 2) mainloop_dma<T, K>(smem, ops, nk, acc);
+  if constexpr (K::SPLIT != 0) mainloop_split<T, K>(smem, ops, nk, acc);
+  else if constexpr (sizeof(T) == 2) mainloop_dma<T, K>(smem, ops, nk, acc);
   else mainloop_regs<K>(smem, ops, nk, acc);
 }
 
@@ -796,6 +1070,11 @@ __device__ __forceinline__ void mainloop_chain(uint8_t* smem, const View (&ops1)
   static_assert(sizeof(T) == 2 && K1::NSTAGE == K2::NSTAGE, "chained loops: 16-bit, one ring");
   zero_acc<K1>(acc1);
   zero_acc<K2>(acc2);
+  if constexpr (K1::SPLIT != 0) {
+    mainloop_split<T, K1>(smem, ops1, nk1, acc1);
+    mainloop_dma<T, K2>(smem, ops2, nk2, acc2);
+    return;
+  }
   ChainNext<K2, SLOT> nx(smem, ops2);
   mainloop_dma<T, K1, SLOT, ChainNext<K2, SLOT>>(smem, ops1, nk1, acc1, 0, false, &nx);
   mainloop_dma<T, K2, SLOT>(smem, ops2, nk2, acc2, nx.slot < 0 ? 0 : nx.slot, nx.slot >= 0);
@@ -1138,14 +1417,14 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
 
 template <typename T>
 __global__ __launch_bounds__(Kinds<T>::Apply::THREADS) void k_fwd(const FwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<T, false>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<T, false>()];
   fwd_body<T, false>(args, smem);
 }
 
 // d <= 128, 16-bit: two workgroups per CU (at most 256 VGPRs per wave).
 __global__ __launch_bounds__(KApplyN16::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_fwd_narrow(
     const FwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<__bf16, true>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, true>()];
   fwd_body<__bf16, true>(args, smem);
 }
 
@@ -1154,13 +1433,13 @@ __global__ __launch_bounds__(KApplyN16::THREADS) __attribute__((amdgpu_waves_per
 // them instead of computing the three products again.
 template <typename T>
 __global__ __launch_bounds__(Kinds<T>::Apply::THREADS) void k_fwd_keep(const FwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<T, false>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<T, false>()];
   fwd_body<T, false, true>(args, smem);
 }
 
 __global__ __launch_bounds__(KApplyN16::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_fwd_narrow_keep(
     const FwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<__bf16, true>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, true>()];
   fwd_body<__bf16, true, true>(args, smem);
 }
 
@@ -1179,9 +1458,10 @@ __device__ __forceinline__ void update_rows(Acc<KG>& acc, float* W, __bf16* Wb, 
   static_assert(!(MOM && ADD), "one extra operand");
   constexpr int RP = (MOM || ADD) ? 32 : 64;       // rows per pass
   constexpr int TPR = KG::THREADS / RP;             // lanes per row
-  constexpr int NV = KG::ROWS_B / 4 / TPR;          // 16-byte vectors per lane
-  constexpr int PITCH = KG::ROWS_B + 4;             // floats per LDS row
-  static_assert(KG::NACC == 1 && TPR <= 64 && RP * PITCH * 4 <= KG::NSTAGE * KG::STAGE, "update passes");
+  constexpr int COLS = 2 * KG::ROWS_B;              // columns of the tile
+  constexpr int NV = COLS / 4 / TPR;                // 16-byte vectors per lane
+  constexpr int PITCH = COLS + 4;                   // floats per LDS row
+  static_assert(KG::SPLIT == 2 && TPR <= 64 && RP * PITCH * 4 <= KG::NSTAGE * KG::STAGE, "update passes");
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
   float* st = reinterpret_cast<float*>(smem);
   const int lr = threadIdx.x / TPR, part = threadIdx.x % TPR;
@@ -1206,10 +1486,12 @@ __device__ __forceinline__ void update_rows(Acc<KG>& acc, float* W, __bf16* Wb, 
       const int blk = wave_m<KG>() * 32 * KG::MI + mi * 32;
       if (blk >= pass * RP && blk < pass * RP + RP) {
 #pragma unroll
-        for (int ni = 0; ni < KG::NI; ++ni)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            st[(acc_row<KG>(mi, r) - pass * RP) * PITCH + acc_col<KG>(ni)] = acc[0][mi][ni][r];
+          for (int ni = 0; ni < KG::NI; ++ni)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              st[(acc_row<KG>(mi, r) - pass * RP) * PITCH + p * KG::ROWS_B + acc_col<KG>(ni)] = acc[p][mi][ni][r];
       }
     }
     lds_barrier();
@@ -1275,7 +1557,8 @@ __device__ __forceinline__ void grad_update_tile(const BwdSeg& sg, int inst, int
   const int64_t mrows = (mat == 1 ? d : h) - r0;
   const Operand& A = mat == 0 ? sg.a0 : (mat == 2 ? sg.a1 : sg.a2);
   const Operand& B = mat == 1 ? sg.b1 : sg.b0;
-  const View ops[2] = {view_mn(A, inst, r0, 0, mrows, sg.rows, 2), view_mn(B, inst, 0, 0, cols, sg.rows, 2)};
+  const View ops[3] = {view_mn(A, inst, r0, 0, mrows, sg.rows, 2), view_mn(B, inst, 0, 0, cols, sg.rows, 2),
+                       view_mn(B, inst, KG::ROWS_B, 0, cols - KG::ROWS_B, sg.rows, 2)};
   Acc<KG> acc;
   mainloop<T, KG>(smem, ops, sg.rows, acc);
 
@@ -1362,13 +1645,21 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& args, int blk, uint8_t* 
   if (sg.kind == BWD_OUT) {
     // O^T[m, i] = sum_j W2[m, j] hidden[i, j]: feature-major accumulators, four
     // consecutive features of one token per register group -> packed stores
-    const int64_t m0 = (int64_t)(rr % sg.tiles_m) * KO::ROWS_A;   // feature tile (fastest)
+    constexpr int TR = KO::NACC * KO::ROWS_A;   // features per tile (two operands of half the rows, or one)
+    const int64_t m0 = (int64_t)(rr % sg.tiles_m) * TR;           // feature tile (fastest)
     const int64_t t0 = (int64_t)(rr / sg.tiles_m) * KO::ROWS_B;   // token tile
     const int64_t mrows = d - m0, ntok = sg.rows - t0;
     const int64_t kk = sg.klen ? sg.klen : h;   // contraction length of this segment
-    const View ops[2] = {view_k(sg.b0, inst, m0, 0, mrows, kk, esz), view_k(sg.a0, inst, t0, 0, ntok, kk, esz)};
     Acc<KO> acc;
-    mainloop<T, KO>(smem, ops, kk, acc);
+    if constexpr (KO::SPLIT != 0) {
+      const View ops[3] = {view_k(sg.b0, inst, m0, 0, mrows, kk, esz),
+                           view_k(sg.b0, inst, m0 + KO::ROWS_A, 0, mrows - KO::ROWS_A, kk, esz),
+                           view_k(sg.a0, inst, t0, 0, ntok, kk, esz)};
+      mainloop<T, KO>(smem, ops, kk, acc);
+    } else {
+      const View ops[2] = {view_k(sg.b0, inst, m0, 0, mrows, kk, esz), view_k(sg.a0, inst, t0, 0, ntok, kk, esz)};
+      mainloop<T, KO>(smem, ops, kk, acc);
+    }
     const int64_t ob = inst * sg.out_inst;
     const int mrow0 = wave_m<KO>() * 32 * KO::MI + ((lane >> 5) << 2);
     if (sg.row_scale) {   // per-token factor of the output rows
@@ -1377,26 +1668,30 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& args, int blk, uint8_t* 
         const int tok = acc_col<KO>(ni);
         const float sc = tok < ntok ? sg.row_scale[inst * sg.scale_inst + t0 + tok] : 0.0f;
 #pragma unroll
-        for (int mi = 0; mi < KO::MI; ++mi)
+        for (int p = 0; p < KO::NACC; ++p)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[0][mi][ni][r] *= sc;
+          for (int mi = 0; mi < KO::MI; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[p][mi][ni][r] *= sc;
       }
     }
     if constexpr (sizeof(T) == 2) {
-      static_assert(KO::ROWS_A * KO::ROWS_B * 2 <= bwd_smem<T, NARROW>(), "staging fits");
+      static_assert(TR * KO::ROWS_B * 2 <= bwd_smem<T, NARROW>(), "staging fits");
 #pragma unroll
       for (int ni = 0; ni < KO::NI; ++ni)
 #pragma unroll
-        for (int mi = 0; mi < KO::MI; ++mi)
+        for (int p = 0; p < KO::NACC; ++p)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x16_t& a = acc[0][mi][ni];
-            stage_put<KO::ROWS_A, T>(smem, acc_col<KO>(ni), mrow0 + mi * 32 + 8 * g, a[4 * g], a[4 * g + 1],
-                                  a[4 * g + 2], a[4 * g + 3]);
-          }
+          for (int mi = 0; mi < KO::MI; ++mi)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const f32x16_t& a = acc[p][mi][ni];
+              stage_put<TR, T>(smem, acc_col<KO>(ni), p * KO::ROWS_A + mrow0 + mi * 32 + 8 * g, a[4 * g],
+                               a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+            }
       lds_barrier();
-      stage_flush<KO::ROWS_A, KO::ROWS_B, KO::THREADS, T>(smem, reinterpret_cast<T*>(sg.out) + ob + t0 * d + m0, d,
-                                                         ntok, mrows);
+      stage_flush<TR, KO::ROWS_B, KO::THREADS, T>(smem, reinterpret_cast<T*>(sg.out) + ob + t0 * d + m0, d, ntok,
+                                                  mrows);
       return;
     }
 #pragma unroll
@@ -1462,33 +1757,45 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& args, int blk, uint8_t* 
     }
   } else {
     // P2[m, j] = sum_i V[i, m] (eta hidden)[i, j]
-    const int64_t r0 = (int64_t)(rr / sg.tiles_n) * K2::ROWS_A;
+    constexpr int TR = K2::NACC * K2::ROWS_A;   // rows per tile (two operands of half the rows, or one)
+    const int64_t r0 = (int64_t)(rr / sg.tiles_n) * TR;
     const int64_t c0 = (int64_t)(rr % sg.tiles_n) * K2::ROWS_B;
     const int64_t mrows = d - r0, ncols = h - c0;
-    const View ops[2] = {view_mn(sg.a0, inst, r0, kb, mrows, klen, esz), view_mn(sg.b0, inst, c0, kb, ncols, klen, esz)};
     Acc<K2> acc;
-    mainloop<T, K2>(smem, ops, klen, acc);
+    if constexpr (K2::SPLIT != 0) {
+      const View ops[3] = {view_mn(sg.a0, inst, r0, kb, mrows, klen, esz),
+                           view_mn(sg.a0, inst, r0 + K2::ROWS_A, kb, mrows - K2::ROWS_A, klen, esz),
+                           view_mn(sg.b0, inst, c0, kb, ncols, klen, esz)};
+      mainloop<T, K2>(smem, ops, klen, acc);
+    } else {
+      const View ops[2] = {view_mn(sg.a0, inst, r0, kb, mrows, klen, esz),
+                           view_mn(sg.b0, inst, c0, kb, ncols, klen, esz)};
+      mainloop<T, K2>(smem, ops, klen, acc);
+    }
 #pragma unroll
-    for (int mi = 0; mi < K2::MI; ++mi)
+    for (int p = 0; p < K2::NACC; ++p)
 #pragma unroll
-      for (int ni = 0; ni < K2::NI; ++ni) {
-        const int j = acc_col<K2>(ni);
+      for (int mi = 0; mi < K2::MI; ++mi)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = acc_row<K2>(mi, r);
-          if (i < mrows && j < ncols) part[sg.out_off + (r0 + i) * h + c0 + j] = acc[0][mi][ni][r];
+        for (int ni = 0; ni < K2::NI; ++ni) {
+          const int j = acc_col<K2>(ni);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int i = p * K2::ROWS_A + acc_row<K2>(mi, r);
+            if (i < mrows && j < ncols) part[sg.out_off + (r0 + i) * h + c0 + j] = acc[p][mi][ni][r];
+          }
         }
-      }
     if (sg.sumsq) {
       const float2 t = tile_sumsq<K2>(acc, smem);
-      if (threadIdx.x == 0) sg.sumsq[((int64_t)inst * sg.spi + sg.sumsq_j) * sg.sumsq_stride + rr] = t.x;
+      if (threadIdx.x == 0)
+        sg.sumsq[((int64_t)inst * sg.spi + sg.sumsq_j) * sg.sumsq_stride + rr] = K2::NACC == 2 ? t.x + t.y : t.x;
     }
   }
 }
 
 template <typename T, bool NARROW>
 __global__ __launch_bounds__(Kinds<T>::Out::THREADS) void k_bwd(const BwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[bwd_smem<T, NARROW>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[bwd_smem<T, NARROW>()];
   bwd_body<T, NARROW>(args, blockIdx.x, smem);
 }
 
@@ -1755,7 +2062,7 @@ __device__ __forceinline__ void ns_epilogue_staged(const Acc<KK>& acc, uint8_t* 
 // X5 never goes to memory and no separate update launch runs.
 __global__ __launch_bounds__(KNsRow16::THREADS) void k_ns_final(const NsFinalArgs args) {
   using KR = KNsRow16;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[smem_bytes<_Float16, KR>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes<_Float16, KR>()];
   const int tiles = (args.m + KR::ROWS_A - 1) / KR::ROWS_A;
   const int bid = xcd_remap(blockIdx.x, args.nblocks);
   const int slot = bid / tiles, tile = bid - slot * tiles;
@@ -1764,7 +2071,8 @@ __global__ __launch_bounds__(KNsRow16::THREADS) void k_ns_final(const NsFinalArg
   const int64_t mrows = args.m - r0;
   const Operand b = {reinterpret_cast<const uint8_t*>(args.Bb) + (int64_t)slot * args.astride * 2, args.m, 0};
   const Operand x = {reinterpret_cast<const uint8_t*>(args.Yin) + (int64_t)slot * args.ystride * 2, args.m, 0};
-  const View ops[2] = {view_k(b, 0, r0, 0, mrows, args.m, 2), view_mn(x, 0, 0, 0, args.m, args.m, 2)};
+  const View ops[3] = {view_k(b, 0, r0, 0, mrows, args.m, 2), view_mn(x, 0, 0, 0, args.m, args.m, 2),
+                       view_mn(x, 0, KR::ROWS_B, 0, args.m - KR::ROWS_B, args.m, 2)};
   Acc<KR> acc;
   mainloop<_Float16, KR>(smem, ops, args.m, acc);
   const int64_t off = (int64_t)inst * args.ystride + r0 * args.m;
@@ -2929,16 +3237,16 @@ TileShape bwd_tile(int kind, bool io_bf16, bool narrow) {
     return TileShape{KGrad2N16::ROWS_A, KGrad2N16::ROWS_B, KGrad2N16::THREADS};
   }
   if (io_bf16) {
-    if (kind == BWD_OUT) return TileShape{KOut16::ROWS_A, KOut16::ROWS_B, KOut16::THREADS};
+    if (kind == BWD_OUT) return TileShape{2 * KOut16::ROWS_A, KOut16::ROWS_B, KOut16::THREADS};
     if (kind == BWD_GRAD13) return TileShape{KGrad13_16::ROWS_A, KGrad13_16::ROWS_B, KGrad13_16::THREADS};
-    return TileShape{KGrad2_16::ROWS_A, KGrad2_16::ROWS_B, KGrad2_16::THREADS};
+    return TileShape{2 * KGrad2_16::ROWS_A, KGrad2_16::ROWS_B, KGrad2_16::THREADS};
   }
   if (kind == BWD_OUT) return TileShape{KOut32::ROWS_A, KOut32::ROWS_B, KOut32::THREADS};
   if (kind == BWD_GRAD13) return TileShape{KGrad13_32::ROWS_A, KGrad13_32::ROWS_B, KGrad13_32::THREADS};
   return TileShape{KGrad2_32::ROWS_A, KGrad2_32::ROWS_B, KGrad2_32::THREADS};
 }
 
-TileShape grad_upd_tile() { return TileShape{KGradU16::ROWS_A, KGradU16::ROWS_B, KGradU16::THREADS}; }
+TileShape grad_upd_tile() { return TileShape{KGradU16::ROWS_A, 2 * KGradU16::ROWS_B, KGradU16::THREADS}; }
 
 TileShape ns_tile(bool fp16, bool big) {
   if (fp16 && big) return TileShape{KNsK16B::ROWS_A, KNsK16B::ROWS_B, KNsK16B::THREADS};
@@ -2946,7 +3254,7 @@ TileShape ns_tile(bool fp16, bool big) {
   return TileShape{KNsK32::ROWS_A, KNsK32::ROWS_B, KNsK32::THREADS};
 }
 
-TileShape ns_final_tile() { return TileShape{KNsRow16::ROWS_A, KNsRow16::ROWS_B, KNsRow16::THREADS}; }
+TileShape ns_final_tile() { return TileShape{KNsRow16::ROWS_A, 2 * KNsRow16::ROWS_B, KNsRow16::THREADS}; }
 
 hipError_t launch_ns_final(const NsFinalArgs& a, hipStream_t s) {
   if (a.nblocks <= 0) return hipSuccess;

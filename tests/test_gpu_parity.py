@@ -129,6 +129,20 @@ def test_bf16_ragged_multi_tile(order):
     check(cfg, x, run_gpu(cfg, x), run_oracle(cfg, x))
 
 
+@pytest.mark.parametrize("heads,d,h,chunk", [
+    (2, 160, 160, 31), (2, 160, 288, 64), (2, 320, 544, 65), (1, 512, 480, 129), (1, 768, 192, 193),
+    (13, 288, 288, 65), (13, 288, 512, 33), (13, 512, 288, 130)])
+def test_bf16_split_stage_loop_edges(heads, d, h, chunk):
+    # 64-K stages worked in halves: one, two, three and more stages, a last
+    # stage of half its K (over d, h) or of any number of tokens, split operands
+    # whose second one is partly or wholly past the matrix; 13 heads of
+    # 256 < d, h <= 512 take the gradient-and-update kind
+    cfg = CONFIGS["lm32k"].with_(name="split", B=1, H=heads, d=d, h=h, n_kv=2 * chunk + 7, n_q=2 * chunk + 40,
+                                 chunk=chunk)
+    x = make_inputs(cfg, 11)
+    check(cfg, x, run_gpu(cfg, x), run_oracle(cfg, x))
+
+
 @pytest.mark.parametrize("order", [0, 1])
 def test_bf16_dims_of_32_mod_64(order):
     # d and h are multiples of 32 but not of 64: contraction tiles that take
