@@ -2794,10 +2794,8 @@ int lact_rmsnorm_out_backward(const lact_desc* desc, const void* o, const float*
   a.dy = dy;
   a.d_o = d_o;
   a.dweight = dweight;
-  a.r = dweight ? reinterpret_cast<float*>(workspace) : nullptr;
-  a.part = dweight ? reinterpret_cast<float*>((uint8_t*)workspace +
-                                              align_up((size_t)desc->B * desc->n_q * desc->H * 4))
-                   : nullptr;
+  a.part = dweight ? reinterpret_cast<float*>(workspace) : nullptr;
+  a.part_room = (int64_t)(need / 4);
   a.eps = eps;
   a.B = desc->B;
   a.H = desc->H;

@@ -280,17 +280,16 @@ struct PrologueBwdArgs {
   int group;               // set by the launcher
 };
 hipError_t launch_prologue_bwd(PrologueBwdArgs a, bool io_bf16, hipStream_t s);
-// Reverse of the output RMSNorm: do from dy, and with dweight its cotangent
-// through a second pass (r: B*L*H floats of per-vector scales, part: the
-// pass's partial sums, rms_dw_splits(...) * H * hd floats).
+// Reverse of the output RMSNorm: do from dy, and with dweight its cotangent,
+// summed over token splits (part: at least rms_dw_splits(...) * H * hd floats).
 struct RmsBwdArgs {
   const void* o;           // [B*H, L, hd]
   const float* weight;     // [H, hd] or nullptr
   const void* dy;          // [B, L, H, hd]
   void* d_o;               // [B*H, L, hd]
   float* dweight;          // [H, hd] or nullptr
-  float* r;                // scratch [B*L*H] (with dweight)
-  float* part;             // scratch (with dweight)
+  float* part;             // scratch (with dweight): partial sums, part_room floats
+  int64_t part_room;
   float eps;
   int B, H, hd;
   int64_t L;

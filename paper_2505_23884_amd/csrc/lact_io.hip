@@ -6,6 +6,8 @@
 // A "group" of G lanes (G a power of two, G <= 64) owns (token, head) vectors
 // of hd elements; each lane moves 16 bytes per access, NV accesses per vector,
 // and the group's sum of squares is a shuffle reduction within it.
+#include <algorithm>
+
 #include "lact_internal.h"
 
 namespace lact {
@@ -283,8 +285,7 @@ __global__ __launch_bounds__(256) void k_prologue_bwd(const PrologueBwdArgs a) {
 }
 
 // Reverse of k_rmsnorm_out, one group per output vector (b, l, h): with r =
-// 1 / sqrt(mean(o^2) + eps) and g = w dy, do = r g - (r^3 / hd) o (g . o);
-// with dweight the vector's r goes to a.r for the weight's pass.
+// 1 / sqrt(mean(o^2) + eps) and g = w dy, do = r g - (r^3 / hd) o (g . o).
 template <typename T, int NV, typename IX>
 __global__ __launch_bounds__(256) void k_rmsnorm_out_bwd(const RmsBwdArgs a) {
   constexpr int EPV = Io<T>::EPV;
@@ -329,65 +330,101 @@ __global__ __launch_bounds__(256) void k_rmsnorm_out_bwd(const RmsBwdArgs a) {
       for (int e = 0; e < EPV; ++e) o[e] = r * gv[j][e] - c * x[j][e];
       Io<T>::store(reinterpret_cast<T*>(a.d_o) + oo + (lane_g + j * G) * EPV, o);
     }
-    if (a.dweight && lane_g == 0) a.r[g] = r;
   }
 }
 
-// The weight's cotangent, pass 1: workgroup (head h, 512 columns, split s)
-// sums dy o r over its split's tokens into part[s][h][col]. Each lane owns 8
-// columns (16-byte loads of bf16), each of the 4 waves every 4th token; the
-// waves' sums are then added in order.
-template <typename T>
-__device__ __forceinline__ void load8c(const T* p, float (&x)[8]);
-template <>
-__device__ __forceinline__ void load8c<__bf16>(const __bf16* p, float (&x)[8]) { Io<__bf16>::load(p, x); }
-template <>
-__device__ __forceinline__ void load8c<float>(const float* p, float (&x)[8]) { Io<float>::load8(p, x, 8); }
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_rms_dw_part(const RmsBwdArgs a, int nsplit, int64_t per) {
-  __shared__ float red[4][512];
-  const int cchunks = (a.hd + 511) / 512;
-  const int sidx = blockIdx.x % nsplit;
-  const int rest = blockIdx.x / nsplit;
-  const int hh = rest / cchunks, c0 = (rest - hh * cchunks) * 512;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int col = c0 + 8 * lane;
-  const bool on = col < a.hd;   // hd is a multiple of 8: a lane's columns are all in or all out
+// The same with the weight's cotangent, which sums dy o r over every (batch,
+// token) of a head: workgroup (head, token split) keeps its columns' sums in
+// registers while it writes d_o, so o and dy are read once (a pass of its own
+// over o and dy took 104 us of 450 at [2, 4, 32768, 512] bf16); the groups'
+// sums are added in order through LDS into part[split][head][hd].
+template <typename T, int NV>
+__global__ __launch_bounds__(256) void k_rmsnorm_out_bwd_dw(const RmsBwdArgs a, int64_t per) {
+  constexpr int EPV = Io<T>::EPV;
+  extern __shared__ float red[];   // [256 / G][hd]
+  const int G = a.group, NG = 256 / G;
+  const int lane_g = threadIdx.x & (G - 1), grp = threadIdx.x / G;
+  const int hh = blockIdx.x % a.H, sp = blockIdx.x / a.H;
+  const int nvec = a.hd / EPV;
   const int64_t ntok = (int64_t)a.B * a.L;
-  const int64_t t0 = sidx * per, t1 = t0 + per < ntok ? t0 + per : ntok;
-  const T* dy = reinterpret_cast<const T*>(a.dy);
-  const T* o = reinterpret_cast<const T*>(a.o);
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (on) {
-    for (int64_t t = t0 + w; t < t1; t += 4) {
-      const int64_t b = t / a.L, l = t - b * a.L;
-      float x[8], y[8];
-      load8c<T>(dy + (t * a.H + hh) * a.hd + col, y);
-      load8c<T>(o + ((b * a.H + hh) * a.L + l) * a.hd + col, x);
-      const float rr = a.r[t * a.H + hh];
+  const int64_t t0 = sp * per, t1 = t0 + per < ntok ? t0 + per : ntok;
+  float w[NV][8], dw[NV][8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += y[e] * x[e] * rr;
+  for (int j = 0; j < NV; ++j) {
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) dw[j][e] = 0.0f;
+    if (lane_g + j * G < nvec) Io<float>::load8(a.weight + (int64_t)hh * a.hd + (lane_g + j * G) * EPV, w[j], EPV);
+  }
+  int64_t t = t0 + grp;
+  int64_t b = t / a.L, l = t - b * a.L;
+  for (; t < t1; t += NG) {
+    const int64_t oo = ((b * a.H + hh) * a.L + l) * a.hd, yo = (t * a.H + hh) * a.hd;
+    float x[NV][8], y[NV][8];
+    float ss = 0.0f, dot = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      if (lane_g + j * G >= nvec) continue;
+      Io<T>::load(reinterpret_cast<const T*>(a.o) + oo + (lane_g + j * G) * EPV, x[j]);
+      Io<T>::load(reinterpret_cast<const T*>(a.dy) + yo + (lane_g + j * G) * EPV, y[j]);
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) {
+        ss += x[j][e] * x[j][e];
+        dot += y[j][e] * w[j][e] * x[j][e];
+      }
+    }
+    ss = group_sum(ss, G);
+    dot = group_sum(dot, G);
+    const float r = 1.0f / sqrtf(ss / (float)a.hd + a.eps);
+    const float c = r * r * r * dot / (float)a.hd;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      if (lane_g + j * G >= nvec) continue;
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) {
+        o[e] = r * (y[j][e] * w[j][e]) - c * x[j][e];
+        dw[j][e] += y[j][e] * x[j][e] * r;
+      }
+      Io<T>::store(reinterpret_cast<T*>(a.d_o) + oo + (lane_g + j * G) * EPV, o);
+    }
+    l += NG;
+    while (l >= a.L) {
+      l -= a.L;
+      ++b;
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[w][8 * lane + e] = acc[e];
-  __syncthreads();
-  if (w == 0 && on) {
+  for (int j = 0; j < NV; ++j)
+    if (lane_g + j * G < nvec)
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      a.part[((int64_t)sidx * a.H + hh) * a.hd + col + e] =
-          (red[0][8 * lane + e] + red[1][8 * lane + e]) + (red[2][8 * lane + e] + red[3][8 * lane + e]);
+      for (int e = 0; e < EPV; ++e) red[grp * a.hd + (lane_g + j * G) * EPV + e] = dw[j][e];
+  __syncthreads();
+  for (int c = threadIdx.x; c < a.hd; c += 256) {
+    float s = red[c];
+    for (int q = 1; q < NG; ++q) s += red[q * a.hd + c];
+    a.part[((int64_t)sp * a.H + hh) * a.hd + c] = s;
   }
 }
 
-// Pass 2: dweight = the splits' partials summed in order.
+// dweight = the splits' partials: workgroup of 32 columns, 8 threads a column
+// each over an eighth of the splits, their sums then added in order (one
+// thread per column over all the splits was a chain of 256 loads: 71 us at
+// 2048 columns).
 __global__ __launch_bounds__(256) void k_rms_dw_sum(const float* part, float* dweight, int nsplit, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
+  __shared__ float red[8][32];
+  const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+  const int64_t i = (int64_t)blockIdx.x * 32 + c;
+  const int per = (nsplit + 7) / 8, s1 = (q + 1) * per < nsplit ? (q + 1) * per : nsplit;
   float acc = 0.0f;
-  for (int sp = 0; sp < nsplit; ++sp) acc += part[(int64_t)sp * n + i];
-  dweight[i] = acc;
+  if (i < n)
+    for (int sp = q * per; sp < s1; ++sp) acc += part[(int64_t)sp * n + i];
+  red[q][c] = acc;
+  __syncthreads();
+  if (q == 0 && i < n) {
+#pragma unroll
+    for (int k = 1; k < 8; ++k) acc += red[k][c];
+    dweight[i] = acc;
+  }
 }
 
 // Group size and accesses per lane for hd elements of esz bytes.
@@ -468,7 +505,7 @@ hipError_t launch_prologue_bwd(PrologueBwdArgs a, bool io_bf16, hipStream_t s) {
   return io_bf16 ? launch_nv<PrologueBwdK, __bf16>(a, nv, s) : launch_nv<PrologueBwdK, float>(a, nv, s);
 }
 
-// Token splits of the weight's pass: about 2048 workgroups in all.
+// Token splits whose partial sums the workspace has room for.
 int rms_dw_splits(int B, int64_t L, int H, int hd) {
   const int64_t ntok = (int64_t)B * L, tiles = (int64_t)H * ((hd + 511) / 512);
   int64_t sp = (2048 + tiles - 1) / tiles;
@@ -477,22 +514,28 @@ int rms_dw_splits(int B, int64_t L, int H, int hd) {
   return (int)(sp < 1 ? 1 : sp);
 }
 
+template <typename T, int NV> struct RmsBwdDwK {
+  static void launch(const RmsBwdArgs& a, hipStream_t s) {
+    // about 2048 workgroups of one head's tokens each, a round of its groups
+    // at least, as many as there is room for partial sums
+    const int64_t ntok = (int64_t)a.B * a.L, ng = 256 / a.group;
+    const int64_t want = std::min<int64_t>((2048 + a.H - 1) / a.H, (ntok + ng - 1) / ng);
+    int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>(want, a.part_room / ((int64_t)a.H * a.hd)));
+    const int64_t per = (ntok + nsplit - 1) / nsplit;
+    nsplit = (ntok + per - 1) / per;
+    const int64_t n = (int64_t)a.H * a.hd;
+    k_rmsnorm_out_bwd_dw<T, NV><<<(unsigned)(nsplit * a.H), 256, (size_t)ng * a.hd * 4, s>>>(a, per);
+    k_rms_dw_sum<<<(unsigned)((n + 31) / 32), 256, 0, s>>>(a.part, a.dweight, (int)nsplit, n);
+  }
+};
+
 hipError_t launch_rmsnorm_out_bwd(RmsBwdArgs a, bool io_bf16, hipStream_t s) {
   int nv;
   io_shape(a.hd, io_bf16 ? 2 : 4, a.group, nv);
   if ((int64_t)a.B * a.L * a.H <= 0) return hipSuccess;
   nv = round_nv(nv);
-  hipError_t e = io_bf16 ? launch_nv<RmsBwdK, __bf16>(a, nv, s) : launch_nv<RmsBwdK, float>(a, nv, s);
-  if (e != hipSuccess || !a.dweight) return e;
-  const int nsplit = rms_dw_splits(a.B, a.L, a.H, a.hd);
-  const int64_t ntok = (int64_t)a.B * a.L, per = (ntok + nsplit - 1) / nsplit;
-  const int64_t blocks = (int64_t)nsplit * a.H * ((a.hd + 511) / 512);
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  if (io_bf16) k_rms_dw_part<__bf16><<<(unsigned)blocks, 256, 0, s>>>(a, nsplit, per);
-  else k_rms_dw_part<float><<<(unsigned)blocks, 256, 0, s>>>(a, nsplit, per);
-  const int64_t n = (int64_t)a.H * a.hd;
-  k_rms_dw_sum<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a.part, a.dweight, nsplit, n);
-  return hipGetLastError();
+  if (a.dweight) return io_bf16 ? launch_nv<RmsBwdDwK, __bf16>(a, nv, s) : launch_nv<RmsBwdDwK, float>(a, nv, s);
+  return io_bf16 ? launch_nv<RmsBwdK, __bf16>(a, nv, s) : launch_nv<RmsBwdK, float>(a, nv, s);
 }
 
 hipError_t launch_prologue(PrologueArgs a, bool io_bf16, hipStream_t s) {

@@ -1271,6 +1271,29 @@ def test_output_rmsnorm_backward_matches_oracle(io, d, weighted):
         assert v <= TOL[io], (k, v)
 
 
+@pytest.mark.parametrize("B,H,L,d", [(5, 3, 7, 8), (2, 3, 701, 264), (1, 1, 1, 4096), (3, 40, 33, 128), (2, 2, 1500, 32)])
+@pytest.mark.parametrize("io", ["bf16", "fp32"])
+def test_output_rmsnorm_weight_cotangent_splits(B, H, L, d, io):
+    # one head per workgroup, its tokens split over workgroups and groups of
+    # lanes: fewer tokens than groups, batches shorter than a workgroup's step,
+    # lanes past the vector's end, one and many splits; fp32 sums of at most
+    # B L = 3000 products (error below 3000 x 2^-24 of their magnitude sum)
+    rng = np.random.default_rng(96 + d)
+    from lact_synth import round_to_bf16
+    rnd = round_to_bf16 if io == "bf16" else (lambda a: a)
+    o = rnd(rng.standard_normal((B, H, L, d), dtype=np.float32))
+    dy = rnd(rng.standard_normal((B, L, H, d), dtype=np.float32))
+    w = rng.standard_normal((H, d), dtype=np.float32)
+    dt = torch.bfloat16 if io == "bf16" else torch.float32
+    print(f"[gpu] rmsnorm backward splits io={io} B={B} H={H} L={L} d={d}", flush=True)
+    d_o, dw = P.rmsnorm_out_backward(torch.from_numpy(o).to("cuda", dt), torch.from_numpy(dy).to("cuda", dt),
+                                     torch.from_numpy(w).cuda())
+    torch.cuda.synchronize()
+    rdo, rdw = O.rmsnorm_out_vjp(o.reshape(B * H, L, d), B, H, dy, w)
+    assert rel(d_o.float().cpu().numpy().reshape(B * H, L, d), rdo) <= TOL[io]
+    assert rel(dw.cpu().numpy(), rdw) <= 1e-5
+
+
 def test_output_rmsnorm_backward_lm_tokens():
     # the LM head layout (B = H = 4, d = 512) over 4096 tokens: the weight's
     # cotangent sums 16384 vectors per head in token splits
