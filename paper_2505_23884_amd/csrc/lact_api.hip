@@ -49,7 +49,7 @@ struct Plan {
   int nsplit;         // split-K ways of the gradient contraction
   int64_t split_len;  // tokens per split
   bool fused;         // gradient and weight update in one kind (BWD_GRAD_UPD)
-  bool narrow;        // narrow tile shapes of both launches (16-bit, d <= 128)
+  bool narrow;        // narrow tile shapes of both launches (16-bit: d <= 128; fp32: small_tiles)
   bool ns_out;        // a chunk's output tiles run with its fused Newton-Schulz
   bool muon;
   bool tile_sums;     // Muon without split: the gradient tiles leave the sums of squares
@@ -96,6 +96,17 @@ int check_desc(const lact_desc* d) {
   return LACT_OK;
 }
 
+// fp32 I/O, T tokens per launch: 64 x 64 tiles instead of 128 x 128 where the
+// larger ones would leave three quarters of the 256 CUs idle, so that a
+// quarter of the fp32 MFMA time per tile (a 128 x 128 tile multiplies 16 K in
+// 2048 clocks per accumulator, mostly padding where d or h is 64) decides the
+// launch. [1, 2, 1024, 64], h = 64, chunks of 256: first launch 24 -> 7 us,
+// second 48 -> 9 us (with the gradient split every 64 tokens).
+bool small_tiles(int BH, int h, int64_t T) {
+  const TileShape t = fwd_tile(FWD_APPLY, false, false);
+  return BH * cdiv(h, t.rows) * cdiv(std::max<int64_t>(T, 1), t.cols) <= 64;
+}
+
 Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   Plan p{};
   p.BH = dsc->B * dsc->H;
@@ -107,7 +118,9 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   p.linear = dsc->fast_weight == LACT_FW_LINEAR;
   p.nmat = p.linear ? 1 : 3;
   p.C = std::min<int64_t>(dsc->chunk, dsc->n_kv);
-  p.narrow = p.bf16 && p.d <= 128;
+  const int64_t tail = dsc->n_q - dsc->n_kv;
+  const int64_t tail_rows = std::min<int64_t>(tail, std::max<int64_t>(p.C, 65536));
+  p.narrow = p.bf16 ? p.d <= 128 : small_tiles(p.BH, p.h, std::max(p.C, tail_rows));
   // Small matrices with Muon (one fused Newton-Schulz workgroup each) and the
   // narrow tile shapes: the output tiles of a chunk's apply run in the
   // Newton-Schulz launch, on the CUs its one workgroup per matrix leaves idle,
@@ -115,12 +128,11 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   // operand copies. (Video: 4.39 -> 4.29 ms per step. The gradient tiles then
   // have the second launch to themselves; three or four splits instead of two
   // did not pay: the Newton-Schulz workgroups sum the partials.)
-  p.ns_out = p.narrow && dsc->use_muon && !p.linear && std::min(p.d, p.h) <= kNsFusedM &&
+  p.ns_out = p.bf16 && p.narrow && dsc->use_muon && !p.linear && std::min(p.d, p.h) <= kNsFusedM &&
              std::max(p.d, p.h) <= kNsFusedN;
-  const int64_t tail = dsc->n_q - dsc->n_kv;
   // The applied-hidden buffer holds one chunk plus (bounded) tail rows so that
   // update-then-apply can apply its last chunk together with the tail.
-  p.cap = std::min<int64_t>(dsc->n_q, p.C + std::min<int64_t>(tail, std::max<int64_t>(p.C, 65536)));
+  p.cap = std::min<int64_t>(dsc->n_q, p.C + tail_rows);
   if (p.cap < 1) p.cap = 1;
   // Split-K of the gradient contraction (fp32 partials, summed by the weight
   // update). Each split adds a full write and read of 3*d*h fp32 per instance,
@@ -160,8 +172,10 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
       }
     }
   } else {
+    // (64 x 64 tiles: matrices so small that a partial costs nothing beside
+    // the idle CUs, so down to 64 tokens)
     ns = std::max<int64_t>(1, cdiv(128, tiles));
-    ns = std::min<int64_t>(ns, std::max<int64_t>(1, p.C / 256));
+    ns = std::min<int64_t>(ns, std::max<int64_t>(1, p.C / (!p.bf16 && p.narrow ? 64 : 256)));
   }
   ns = std::min<int64_t>(ns, kMaxSplit);
   p.split_len = std::max<int64_t>(32, cdiv(cdiv(std::max<int64_t>(p.C, 1), ns), 32) * 32);

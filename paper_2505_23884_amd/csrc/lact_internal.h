@@ -50,7 +50,7 @@ struct FwdArgs {
   int d, h;
   Operand w1, w3;       // h x d, kmajor (operand copies of the fast weight)
   Operand w2;           // d x h; the key forward reads it as an mn operand
-  bool narrow;          // 128 x 128 tiles, two workgroups per CU (16-bit, d <= 128)
+  bool narrow;          // 16-bit: 128 x 128 tiles, two workgroups per CU; fp32: 64 x 64 tiles
 };
 
 // ---- second launch: apply GEMM-2 and/or the gradient contractions ---------
@@ -97,7 +97,7 @@ struct BwdArgs {
   int nseg;
   int total_blocks;
   int d, h;
-  int narrow;           // 16-bit I/O with d <= 128: the narrow tile shapes (bwd_tile)
+  int narrow;           // the narrow tile shapes (bwd_tile; 16-bit I/O with d <= 128, small fp32 calls)
 };
 
 // ---- weight update ----------------------------------------------------------

@@ -53,7 +53,6 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 constexpr int kRowBytes = 64;
-constexpr int kTileBytes = 128 * kRowBytes;   // a 128-row operand tile (fp32 path)
 
 template <typename T> struct Tr;
 template <> struct Tr<__bf16> {   // 32 K per tile, 8 elements per 16 bytes
@@ -140,8 +139,12 @@ struct KindBase {
     return s;
   }
   static constexpr int STAGE = op_off(NOPS);
-  // which half of the block (threads 0-127 / 128-255) loads mn operand o (fp32 path)
-  static constexpr int mn_half(int o) { return __builtin_popcount(MN & ((1u << o) - 1u)) & 1; }
+  // fp32 path: bytes of an operand tile (ROWS_A == ROWS_B rows); the threads
+  // that load mn operand o (one per 4 rows and 4 K) start at mn_first(o)
+  static constexpr int TILE32 = ROWS_A * kRowBytes;
+  static constexpr int mn_first(int o) {
+    return __builtin_popcount(MN & ((1u << o) - 1u)) * ROWS_A % THREADS;
+  }
 };
 
 // Kinds of the split-stage loop (16-bit): accumulator set p multiplies the
@@ -204,6 +207,13 @@ LACT_KIND(KUpdate32, 3, 2, 3, 1u << 2, 2, 2, 2, 2, 2, false, 32, p, (p == 2 ? 1 
 LACT_KIND(KOut32, 1, 1, 1, 0u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
 LACT_KIND(KGrad13_32, 2, 1, 2, 7u, 2, 2, 2, 2, 2, false, 32, p, 0 * p);
 LACT_KIND(KGrad2_32, 1, 1, 1, 3u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
+// The same with 64 x 64 tiles (waves of 32 x 32), for small calls
+// (small_tiles in lact_api.hip).
+LACT_KIND(KApplyS32, 2, 1, 2, 0u, 2, 2, 1, 1, 2, false, 32, p, 0 * p);
+LACT_KIND(KUpdateS32, 3, 2, 3, 1u << 2, 2, 2, 1, 1, 2, false, 32, p, (p == 2 ? 1 : 0));
+LACT_KIND(KOutS32, 1, 1, 1, 0u, 2, 2, 1, 1, 2, false, 32, 0 * p, 0 * p);
+LACT_KIND(KGrad13_S32, 2, 1, 2, 7u, 2, 2, 1, 1, 2, false, 32, p, 0 * p);
+LACT_KIND(KGrad2_S32, 1, 1, 1, 3u, 2, 2, 1, 1, 2, false, 32, 0 * p, 0 * p);
 // Newton-Schulz products, each computed in the orientation whose transpose is
 // stored (see k_ns): both operands K-contiguous (K), both row-contiguous (MN),
 // or the first row-contiguous (TY: Y read down its columns). fp16 operands:
@@ -273,6 +283,12 @@ struct FwdKinds {
   using Dual = KDual16;
 };
 template <>
+struct FwdKinds<float, true> {
+  using Apply = KApplyS32;
+  using Update = KUpdateS32;
+  using Dual = KDual16;   // unused
+};
+template <>
 struct FwdKinds<__bf16, true> {
   using Apply = KApplyN16;
   using Update = KApplyN16;
@@ -285,6 +301,12 @@ struct BwdKinds {
   using Out = typename Kinds<T>::Out;
   using Grad13 = typename Kinds<T>::Grad13;
   using Grad2 = typename Kinds<T>::Grad2;
+};
+template <>
+struct BwdKinds<float, true> {
+  using Out = KOutS32;
+  using Grad13 = KGrad13_S32;
+  using Grad2 = KGrad2_S32;
 };
 template <>
 struct BwdKinds<__bf16, true> {
@@ -319,13 +341,14 @@ __device__ __forceinline__ int acc_col(int ni) {
 }
 
 // ===========================================================================
-// fp32 register path (4 waves, 128 x 128, MI = NI = 2)
+// fp32 register path (4 waves of 64 x 64 or 32 x 32: tiles of R = 128 or 64
+// rows of both operands)
 
-template <typename T>
+template <typename T, int R>
 __device__ __forceinline__ void gload_k(u32x4_t (&r)[4], const View& v, int64_t k0) {
   constexpr int E = Tr<T>::E;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < R / 64; ++i) {
     const int q = threadIdx.x + i * 256;
     const int row = q >> 2, c = q & 3;
     const int64_t k = k0 + c * E;
@@ -336,9 +359,10 @@ __device__ __forceinline__ void gload_k(u32x4_t (&r)[4], const View& v, int64_t 
   }
 }
 
+template <int R>
 __device__ __forceinline__ void sstore_k(uint8_t* tile, const u32x4_t (&r)[4]) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < R / 64; ++i) {
     const int q = threadIdx.x + i * 256;
     *reinterpret_cast<u32x4_t*>(tile + lds_off(q >> 2, q & 3)) = r[i];
   }
@@ -376,22 +400,23 @@ __device__ __forceinline__ u32x4_t frag32(const uint8_t* tile, int row, int chun
 
 template <class K>
 __device__ __forceinline__ void compute_ktile32(const uint8_t* buf, Acc<K>& acc) {
-  static_assert(K::MI == 2 && K::NI == 2 && K::THREADS == 256, "fp32 path shape");
+  static_assert(K::MI == K::NI && K::ROWS_A == K::ROWS_B && K::THREADS == 256, "fp32 path shape");
+  constexpr int M = K::MI, TB = K::TILE32;
   const int lane = threadIdx.x & 63;
-  const int arow = wave_m<K>() * 64 + (lane & 31), brow = wave_n<K>() * 64 + (lane & 31);
+  const int arow = wave_m<K>() * 32 * M + (lane & 31), brow = wave_n<K>() * 32 * M + (lane & 31);
   const int half = lane >> 5;
   // lanes 0-31 hold K 0..7 of the tile, lanes 32-63 K 8..15; MFMA s contracts
   // K s (first half-wave) and K 8+s (second half-wave)
-  float af[K::NA][2][8], bf[K::NB][2][8];
+  float af[K::NA][M][8], bf[K::NB][M][8];
 #pragma unroll
   for (int o = 0; o < K::NA; ++o)
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
+    for (int mi = 0; mi < M; ++mi) {
       // whole-vector bit casts: a bit cast of one vector element is not
       // reliable with this compiler (it reads element 0)
-      const f32x4_t lo = __builtin_bit_cast(f32x4_t, frag32(buf + o * kTileBytes, arow + mi * 32, 2 * half, K::is_mn(o)));
+      const f32x4_t lo = __builtin_bit_cast(f32x4_t, frag32(buf + o * TB, arow + mi * 32, 2 * half, K::is_mn(o)));
       const f32x4_t hi =
-          __builtin_bit_cast(f32x4_t, frag32(buf + o * kTileBytes, arow + mi * 32, 2 * half + 1, K::is_mn(o)));
+          __builtin_bit_cast(f32x4_t, frag32(buf + o * TB, arow + mi * 32, 2 * half + 1, K::is_mn(o)));
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         af[o][mi][e] = lo[e];
@@ -401,8 +426,8 @@ __device__ __forceinline__ void compute_ktile32(const uint8_t* buf, Acc<K>& acc)
 #pragma unroll
   for (int o = 0; o < K::NB; ++o)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const uint8_t* t = buf + (K::NA + o) * kTileBytes;
+    for (int ni = 0; ni < M; ++ni) {
+      const uint8_t* t = buf + (K::NA + o) * TB;
       const f32x4_t lo = __builtin_bit_cast(f32x4_t, frag32(t, brow + ni * 32, 2 * half, K::is_mn(K::NA + o)));
       const f32x4_t hi = __builtin_bit_cast(f32x4_t, frag32(t, brow + ni * 32, 2 * half + 1, K::is_mn(K::NA + o)));
 #pragma unroll
@@ -416,16 +441,16 @@ __device__ __forceinline__ void compute_ktile32(const uint8_t* buf, Acc<K>& acc)
 #pragma unroll
     for (int p = 0; p < K::NACC; ++p)
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
+      for (int mi = 0; mi < M; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
+        for (int ni = 0; ni < M; ++ni)
           acc[p][mi][ni] =
               __builtin_amdgcn_mfma_f32_32x32x2f32(af[K::pa(p)][mi][s], bf[K::pb(p)][ni][s], acc[p][mi][ni], 0, 0, 0);
 }
 
 template <class K>
 __device__ __forceinline__ void mainloop_regs(uint8_t* smem, const View (&ops)[K::NOPS], int64_t nk, Acc<K>& acc) {
-  constexpr int BK = 16;
+  constexpr int BK = 16, R = K::ROWS_A;
   const int nkt = (int)((nk + BK - 1) / BK);
   if (nkt <= 0) return;
   u32x4_t st[K::NOPS][4];
@@ -433,10 +458,10 @@ __device__ __forceinline__ void mainloop_regs(uint8_t* smem, const View (&ops)[K
 #pragma unroll
     for (int o = 0; o < K::NOPS; ++o) {
       if (K::is_mn(o)) {
-        const int tt = threadIdx.x - 128 * K::mn_half(o);
-        if (tt >= 0 && tt < 128) gload_mn<float>(st[o], ops[o], k0, tt);
+        const int tt = threadIdx.x - K::mn_first(o);
+        if (tt >= 0 && tt < R) gload_mn<float>(st[o], ops[o], k0, tt);
       } else {
-        gload_k<float>(st[o], ops[o], k0);
+        gload_k<float, R>(st[o], ops[o], k0);
       }
     }
   };
@@ -444,10 +469,10 @@ __device__ __forceinline__ void mainloop_regs(uint8_t* smem, const View (&ops)[K
 #pragma unroll
     for (int o = 0; o < K::NOPS; ++o) {
       if (K::is_mn(o)) {
-        const int tt = threadIdx.x - 128 * K::mn_half(o);
-        if (tt >= 0 && tt < 128) sstore_mn32(buf + o * kTileBytes, st[o], tt);
+        const int tt = threadIdx.x - K::mn_first(o);
+        if (tt >= 0 && tt < R) sstore_mn32(buf + o * K::TILE32, st[o], tt);
       } else {
-        sstore_k(buf + o * kTileBytes, st[o]);
+        sstore_k<R>(buf + o * K::TILE32, st[o]);
       }
     }
   };
@@ -455,11 +480,11 @@ __device__ __forceinline__ void mainloop_regs(uint8_t* smem, const View (&ops)[K
   sstore(smem);
   __syncthreads();
   for (int kt = 0; kt < nkt; ++kt) {
-    const uint8_t* cur = smem + (kt & 1) * K::NOPS * kTileBytes;
+    const uint8_t* cur = smem + (kt & 1) * K::NOPS * K::TILE32;
     const bool more = kt + 1 < nkt;
     if (more) gload((int64_t)(kt + 1) * BK);
     compute_ktile32<K>(cur, acc);
-    if (more) sstore(smem + ((kt + 1) & 1) * K::NOPS * kTileBytes);
+    if (more) sstore(smem + ((kt + 1) & 1) * K::NOPS * K::TILE32);
     __syncthreads();
   }
 }
@@ -1082,7 +1107,7 @@ __device__ __forceinline__ void mainloop_chain(uint8_t* smem, const View (&ops1)
 
 template <typename T, class K>
 constexpr int smem_bytes() {
-  return sizeof(T) == 2 ? K::NSTAGE * K::STAGE : 2 * K::NOPS * kTileBytes;
+  return sizeof(T) == 2 ? K::NSTAGE * K::STAGE : 2 * K::NOPS * K::TILE32;
 }
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
@@ -1434,6 +1459,16 @@ __global__ __launch_bounds__(KApplyN16::THREADS) __attribute__((amdgpu_waves_per
     const FwdArgs args) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, true>()];
   fwd_body<__bf16, true>(args, smem);
+}
+
+// fp32, small calls: 64 x 64 tiles.
+__global__ __launch_bounds__(KApplyS32::THREADS) void k_fwd_small(const FwdArgs args) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<float, true>()];
+  fwd_body<float, true>(args, smem);
+}
+__global__ __launch_bounds__(KApplyS32::THREADS) void k_fwd_small_keep(const FwdArgs args) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<float, true>()];
+  fwd_body<float, true, true>(args, smem);
 }
 
 // The same two kernels with the key forward's Z1, Z3 and D written out too
@@ -3234,6 +3269,7 @@ TileShape fwd_tile(int kind, bool io_bf16, bool narrow) {
   if (io_bf16 && narrow) return TileShape{KApplyN16::ROWS_A, KApplyN16::ROWS_B, KApplyN16::THREADS};
   if (io_bf16) return kind == FWD_APPLY ? TileShape{KApply16::ROWS_A, KApply16::ROWS_B, KApply16::THREADS}
                                         : TileShape{KApply16::ROWS_A, KApply16::ROWS_B, KApply16::THREADS};
+  if (narrow) return TileShape{KApplyS32::ROWS_A, KApplyS32::ROWS_B, KApplyS32::THREADS};
   return kind == FWD_APPLY ? TileShape{KApply32::ROWS_A, KApply32::ROWS_B, KApply32::THREADS}
                            : TileShape{KUpdate32::ROWS_A, KUpdate32::ROWS_B, KUpdate32::THREADS};
 }
@@ -3249,6 +3285,7 @@ TileShape bwd_tile(int kind, bool io_bf16, bool narrow) {
     if (kind == BWD_GRAD13) return TileShape{KGrad13_16::ROWS_A, KGrad13_16::ROWS_B, KGrad13_16::THREADS};
     return TileShape{2 * KGrad2_16::ROWS_A, KGrad2_16::ROWS_B, KGrad2_16::THREADS};
   }
+  if (narrow) return TileShape{KOutS32::ROWS_A, KOutS32::ROWS_B, KOutS32::THREADS};   // every kind
   if (kind == BWD_OUT) return TileShape{KOut32::ROWS_A, KOut32::ROWS_B, KOut32::THREADS};
   if (kind == BWD_GRAD13) return TileShape{KGrad13_32::ROWS_A, KGrad13_32::ROWS_B, KGrad13_32::THREADS};
   return TileShape{KGrad2_32::ROWS_A, KGrad2_32::ROWS_B, KGrad2_32::THREADS};
@@ -3354,11 +3391,13 @@ hipError_t launch_fwd(const FwdArgs& a, bool io_bf16, hipStream_t s) {
   if (keep) {
     if (io_bf16 && a.narrow) k_fwd_narrow_keep<<<a.total_blocks, KApplyN16::THREADS, 0, s>>>(a);
     else if (io_bf16) k_fwd_keep<__bf16><<<a.total_blocks, KApply16::THREADS, 0, s>>>(a);
+    else if (a.narrow) k_fwd_small_keep<<<a.total_blocks, KApplyS32::THREADS, 0, s>>>(a);
     else k_fwd_keep<float><<<a.total_blocks, KApply32::THREADS, 0, s>>>(a);
     return hipGetLastError();
   }
   if (io_bf16 && a.narrow) k_fwd_narrow<<<a.total_blocks, KApplyN16::THREADS, 0, s>>>(a);
   else if (io_bf16) k_fwd<__bf16><<<a.total_blocks, KApply16::THREADS, 0, s>>>(a);
+  else if (a.narrow) k_fwd_small<<<a.total_blocks, KApplyS32::THREADS, 0, s>>>(a);
   else k_fwd<float><<<a.total_blocks, KApply32::THREADS, 0, s>>>(a);
   return hipGetLastError();
 }
@@ -3367,6 +3406,7 @@ hipError_t launch_bwd(const BwdArgs& a, bool io_bf16, hipStream_t s) {
   if (a.total_blocks <= 0) return hipSuccess;
   if (io_bf16 && a.narrow) k_bwd<__bf16, true><<<a.total_blocks, KOutN16::THREADS, 0, s>>>(a);
   else if (io_bf16) k_bwd<__bf16, false><<<a.total_blocks, KOut16::THREADS, 0, s>>>(a);
+  else if (a.narrow) k_bwd<float, true><<<a.total_blocks, KOutS32::THREADS, 0, s>>>(a);
   else k_bwd<float, false><<<a.total_blocks, KOut32::THREADS, 0, s>>>(a);
   return hipGetLastError();
 }

@@ -131,15 +131,32 @@ def test_bf16_ragged_multi_tile(order):
 
 @pytest.mark.parametrize("heads,d,h,chunk", [
     (2, 160, 160, 31), (2, 160, 288, 64), (2, 320, 544, 65), (1, 512, 480, 129), (1, 768, 192, 193),
-    (13, 288, 288, 65), (13, 288, 512, 33), (13, 512, 288, 130)])
+    (34, 160, 160, 31), (14, 192, 544, 300), (13, 288, 288, 65), (17, 288, 512, 33), (13, 512, 288, 300)])
 def test_bf16_split_stage_loop_edges(heads, d, h, chunk):
     # 64-K stages worked in halves: one, two, three and more stages, a last
     # stage of half its K (over d, h) or of any number of tokens, split operands
-    # whose second one is partly or wholly past the matrix; 13 heads of
-    # 256 < d, h <= 512 take the gradient-and-update kind
+    # whose second one is partly or wholly past the matrix; 13 and 17 heads
+    # of 256 < d, h <= 512 take the gradient-and-update kind. The first launch
+    # takes wide tiles where both segments' are more than 128 (34 x 4, 14 x 20,
+    # 17 x 8 and 13 x 12 tiles), narrow ones of 32-K stages else
     cfg = CONFIGS["lm32k"].with_(name="split", B=1, H=heads, d=d, h=h, n_kv=2 * chunk + 7, n_q=2 * chunk + 40,
                                  chunk=chunk)
     x = make_inputs(cfg, 11)
+    check(cfg, x, run_gpu(cfg, x), run_oracle(cfg, x))
+
+
+@pytest.mark.parametrize("heads,d,h,chunk", [(1, 8, 8, 17), (2, 64, 64, 256), (1, 72, 136, 130), (3, 200, 64, 100),
+                                             (5, 128, 256, 700), (11, 128, 256, 400), (1, 64, 72, 4000)])
+def test_fp32_small_and_large_tiles(heads, d, h, chunk):
+    # fp32: 64 x 64 tiles (waves of 32 x 32, the gradient split down to 64
+    # tokens) up to 64 large first-launch tiles, 128 x 128 beyond (11 x 8
+    # tiles); partial tiles of either side, K past the last 16, ragged splits
+    cfg = CONFIGS["tiny_fp32"].with_(name="fp32_tiles", B=1, H=heads, d=d, h=h, n_kv=chunk + 9, n_q=chunk + 70,
+                                     chunk=chunk)
+    x = make_inputs(cfg, 12)
+    # rates 30 times the recipe's: a short chunk then moves W by 1e-2 and more,
+    # so that the fp32 rounding of W itself (6e-8) stays below 1e-5 of its change
+    x["eta"] = x["eta"] * np.float32(30)
     check(cfg, x, run_gpu(cfg, x), run_oracle(cfg, x))
 
 
