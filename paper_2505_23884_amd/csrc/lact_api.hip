@@ -1121,9 +1121,11 @@ int run_schedule(const lact_desc* desc, const lact_segment* segs, int64_t nseg, 
 // and then goes back one step at a time:
 //   dB = dX' X^T,  S = dB + dB^T,  M = b S + c (S A + (S A)^T)  (= dA + dA^T),
 //   dX = a dX' + B dX' + M X,
-// and through the scaling X_0 = G / (||G|| + eps). Products: the k_bwd kinds
-// (OUT for sums along rows, GRAD2 for sums down columns, fp32 partials) on
-// fp16 operand copies with bf16 I/O, fp32 ones with fp32 I/O; fp32 iterates.
+// and through the scaling X_0 = G / (||G|| + eps); fp32 iterates. With bf16
+// I/O the operand copies are fp16 and each product takes its combination in
+// its epilogue (S and M as P Q^T + Q P^T: A, S symmetric): three launches per
+// step and direction. With fp32 I/O they are fp32: the k_bwd kinds (OUT for
+// sums along rows, GRAD2 for sums down columns) and elementwise launches.
 struct NsBwdLayout {
   int S, m, n;
   int64_t iters;   // slices of the iterates and steps: 1 (replayed per chunk) or one per chunk (kept)
@@ -1259,7 +1261,7 @@ struct NsBwd {
   int out(const void* a, int64_t a_ld, int64_t a_inst, const void* b, int64_t b_ld, int64_t b_inst,
           void* o, int rows, int rows_out, int K) const {
     BwdArgs x{};
-    const TileShape t = bwd_tile(BWD_OUT, !f32(), false);
+    const TileShape t = bwd_tile(BWD_OUT, false, false);
     BwdSeg& g = x.seg[0];
     g.kind = BWD_OUT;
     g.tiles_m = (int)cdiv(rows_out, t.rows);
@@ -1277,16 +1279,12 @@ struct NsBwd {
     x.d = rows_out;
     x.h = K;
     x.narrow = 0;
-    return timed(LACT_KCLASS_NS, 2.0 * N.S * rows * rows_out * K, s,
-                 [&] { return f32() ? launch_bwd(x, false, s) : launch_bwd_f16(x, s); });
+    return timed(LACT_KCLASS_NS, 2.0 * N.S * rows * rows_out * K, s, [&] { return launch_bwd(x, false, s); });
   }
   // out = a^T b per slot: a [m x m] (rows i), b [m x n] (rows i), fp32 [m x n]; up to two at once
   int grad2(const void* const* a, const void* const* b, float* const* o, int nseg) const {
     BwdArgs x{};
-    // fp16: 128 x 256 tiles (the narrow kinds), twice the workgroups of the
-    // 256 x 256 ones, so that the slots' tiles fill the chip
-    const bool half = !f32();
-    const TileShape t = bwd_tile(BWD_GRAD2, !f32(), half);
+    const TileShape t = bwd_tile(BWD_GRAD2, false, false);
     for (int i = 0; i < nseg; ++i) {
       BwdSeg& g = x.seg[i];
       g.kind = BWD_GRAD2;
@@ -1308,9 +1306,8 @@ struct NsBwd {
     for (int i = 0; i < nseg; ++i) x.total_blocks += x.seg[i].nblocks;
     x.d = N.m;
     x.h = N.n;
-    x.narrow = half ? 1 : 0;
-    return timed(LACT_KCLASS_NS, 2.0 * nseg * N.S * mm() * N.n, s,
-                 [&] { return f32() ? launch_bwd(x, false, s) : launch_bwd_f16(x, s); });
+    x.narrow = 0;
+    return timed(LACT_KCLASS_NS, 2.0 * nseg * N.S * mm() * N.n, s, [&] { return launch_bwd(x, false, s); });
   }
   int lin(int mode, const float* x, const float* y, const float* p1, const float* p2, const float* sc,
           const float* sc2, float a, float* o32, void* oc) const {
@@ -1337,14 +1334,48 @@ struct NsBwd {
   uint8_t* Ao(int k) const { return at<uint8_t>(N.ao) + sk(k) * N.S * mm() * N.es; }
   uint8_t* Bo(int k) const { return at<uint8_t>(N.bo) + sk(k) * N.S * mm() * N.es; }
   uint8_t* buf(size_t off) const { return at<uint8_t>(off); }
-  // out = alpha X + beta (Y + Y^T) per [m x m] slot in the operand type (X may be nullptr)
+  // out = alpha X + beta (Y + Y^T) per [m x m] fp32 slot (X may be nullptr)
   int sym(const void* X, float alpha, const void* Y, float beta, void* o) const {
     return timed(LACT_KCLASS_NS, 0.0, s, [&] {
-      return f32() ? launch_sym32(reinterpret_cast<const float*>(X), alpha, reinterpret_cast<const float*>(Y), beta,
-                                  reinterpret_cast<float*>(o), N.S, N.m, s)
-                   : launch_sym(reinterpret_cast<const _Float16*>(X), alpha, reinterpret_cast<const _Float16*>(Y),
-                                beta, reinterpret_cast<_Float16*>(o), N.S, N.m, s);
+      return launch_sym32(reinterpret_cast<const float*>(X), alpha, reinterpret_cast<const float*>(Y), beta,
+                          reinterpret_cast<float*>(o), N.S, N.m, s);
     });
+  }
+  // The fp16 products with their combinations in one launch each (NsSymArgs,
+  // NsDxArgs): out = alpha E + beta (P Q^T [+ Q P^T]) and the step
+  // out32 = ca x32 + B0 Y0 [+ B1 Y1] with its fp16 copy.
+  int symp(const void* P, const void* Q, int K, int64_t in_inst, bool two, float beta, const void* E, float alpha,
+           void* o) const {
+    NsSymArgs a{};
+    a.P = reinterpret_cast<const _Float16*>(P);
+    a.Q = reinterpret_cast<const _Float16*>(Q);
+    a.E = reinterpret_cast<const _Float16*>(E);
+    a.out = reinterpret_cast<_Float16*>(o);
+    a.alpha = alpha;
+    a.beta = beta;
+    a.two = two;
+    a.S = N.S;
+    a.m = N.m;
+    a.K = K;
+    a.in_inst = in_inst;
+    return timed(LACT_KCLASS_NS, (two ? 2.0 : 1.0) * N.S * mm() * (double)K, s, [&] { return launch_ns_sym(a, s); });
+  }
+  int dx(const void* Y0, const void* B0, const void* Y1, const void* B1, const float* x32, float* out32,
+         void* out16) const {
+    NsDxArgs a{};
+    a.Y[0] = reinterpret_cast<const _Float16*>(Y0);
+    a.B[0] = reinterpret_cast<const _Float16*>(B0);
+    a.Y[1] = reinterpret_cast<const _Float16*>(Y1);
+    a.B[1] = reinterpret_cast<const _Float16*>(B1);
+    a.two = Y1 != nullptr;
+    a.x32 = x32;
+    a.out32 = out32;
+    a.out16 = reinterpret_cast<_Float16*>(out16);
+    a.ca = (float)kNsA;
+    a.S = N.S;
+    a.m = N.m;
+    a.n = N.n;
+    return timed(LACT_KCLASS_NS, (a.two ? 4.0 : 2.0) * N.S * mm() * N.n, s, [&] { return launch_ns_dx(a, s); });
   }
   float* pst() const { return at<float>(N.pstep) + (size_t)(ci % N.iters) * N.S * mn(); }   // the step, negated
   bool kept() const { return N.iters > 1; }
@@ -1369,6 +1400,12 @@ struct NsBwd {
     if (!rc) rc = timed(LACT_KCLASS_NS, 0.0, s, [&] { return launch_slot_dot(G, G, N.S, mn(), at<float>(N.nrm), at<float>(N.dotp), s); });
     if (!rc) rc = lin(0, G, nullptr, nullptr, nullptr, at<float>(N.nrm), nullptr, 0.f, X, steps > 0 ? Xo(0) : nullptr);
     for (int k = 0; k < steps && !rc; ++k) {
+      if (!f32()) {
+        rc = symp(Xo(k), Xo(k), N.n, mn(), false, 1.0f, nullptr, 0.0f, Ao(k));                  // A = X X^T
+        if (!rc) rc = symp(Ao(k), Ao(k), N.m, mm(), false, (float)kNsC, Ao(k), (float)kNsB, Bo(k));   // B = b A + c A A
+        if (!rc) rc = dx(Xo(k), Bo(k), nullptr, nullptr, X, X, k + 1 < steps ? Xo(k + 1) : nullptr);   // a X + B X
+        continue;
+      }
       rc = out(Xo(k), N.n, mn(), Xo(k), N.n, mn(), Ao(k), N.m, N.m, N.n);   // A = X X^T
       if (!rc) rc = out(Ao(k), N.m, mm(), Ao(k), N.m, mm(), buf(N.qo), N.m, N.m, N.m);   // A A
       if (!rc) rc = sym(Ao(k), (float)kNsB, buf(N.qo), 0.5f * (float)kNsC, Bo(k));   // B = b A + c A A (symmetrised)
@@ -1390,7 +1427,15 @@ struct NsBwd {
     uint8_t* T = buf(N.to);
     int rc = gather(at<float>(N.ustep), 1, 0, -1.0f, X);   // d step = -dU
     if (!rc) rc = lin(1, X, nullptr, nullptr, nullptr, nullptr, nullptr, 1.0f, nullptr, T);
+    uint8_t* T2 = buf(N.p1);   // the other copy of dX' (fp16: p1 holds no partials)
     for (int k = steps - 1; k >= 0 && !rc; --k) {
+      if (!f32()) {
+        rc = symp(T, Xo(k), N.n, mn(), true, 1.0f, nullptr, 0.0f, buf(N.so));   // S = dX' X^T + X dX'^T
+        if (!rc) rc = symp(buf(N.so), Ao(k), N.m, mm(), true, (float)kNsC, buf(N.so), (float)kNsB, buf(N.mo));   // M
+        if (!rc) rc = dx(T, Bo(k), Xo(k), buf(N.mo), X, X, k > 0 ? T2 : nullptr);   // a dX' + B dX' + M X
+        std::swap(T, T2);
+        continue;
+      }
       rc = out(T, N.n, mn(), Xo(k), N.n, mn(), buf(N.dbo), N.m, N.m, N.n);   // dB = dX' X^T
       if (!rc) rc = sym(nullptr, 0.f, buf(N.dbo), 1.0f, buf(N.so));
       if (!rc) rc = out(buf(N.so), N.m, mm(), Ao(k), N.m, mm(), buf(N.qo), N.m, N.m, N.m);

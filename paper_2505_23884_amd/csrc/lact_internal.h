@@ -379,9 +379,6 @@ hipError_t launch_copies(const CopySeg* c, int n, int BH, bool io_bf16, hipStrea
 hipError_t launch_copies_f32(const CopySeg* c, int n, int BH, hipStream_t s);
 
 // ---- reverse of Newton-Schulz (slots of wide [m x n] fp32 matrices) --------
-// The k_bwd kinds with fp16 operands (fp16 OUT results, fp32 GRAD partials).
-// a.narrow: the narrow kinds (128-row GRAD2 tiles)
-hipError_t launch_bwd_f16(const BwdArgs& a, hipStream_t s);
 // out[s] = sum over len elements of x[s] * y[s] (slot s), in a fixed order
 // (32 workgroups per slot, then their partials in order).
 hipError_t launch_slot_dot(const float* x, const float* y, int S, int64_t len, float* out, float* part,
@@ -401,10 +398,37 @@ struct NsLinArgs {
   int S; int64_t len;
 };
 hipError_t launch_ns_lin(const NsLinArgs& a, hipStream_t s);
-// out = alpha X + beta (Y + Y^T) per slot of fp16 [m x m] matrices (X may be nullptr).
-hipError_t launch_sym(const _Float16* X, float alpha, const _Float16* Y, float beta, _Float16* out, int S, int m,
-                      hipStream_t s);
-// The same for fp32 slots (fp32 I/O).
+// Symmetric product per slot of fp16 matrices:
+//   out = alpha E + beta (P Q^T [+ Q P^T])   (two: both terms)
+// P, Q [m x K] (in_inst apart), E (or nullptr) and out [m x m] (mm apart), in
+// fp32 up to the rounding of out. The sum must be symmetric: only tiles of the
+// upper triangle are computed, the others written as their mirrors.
+struct NsSymArgs {
+  const _Float16* P; const _Float16* Q; const _Float16* E;
+  _Float16* out;
+  float alpha, beta;
+  int two;
+  int S, m, K;
+  int64_t in_inst;
+  int nblocks;   // set by the launcher
+};
+hipError_t launch_ns_sym(NsSymArgs a, hipStream_t s);
+// Update product per slot of wide [m x n] iterates:
+//   out32 = ca x32 + B0 Y0 [+ B1 Y1],  out16 its fp16 copy (or nullptr)
+// with symmetric fp16 B [m x m] and fp16 Y [m x n]; out32 may be x32, out16
+// must be neither Y.
+struct NsDxArgs {
+  const _Float16* Y[2]; const _Float16* B[2];
+  int two;
+  const float* x32;
+  float* out32; _Float16* out16;
+  float ca;
+  int S, m, n;
+  int nblocks;   // set by the launcher
+};
+hipError_t launch_ns_dx(NsDxArgs a, hipStream_t s);
+// out = alpha X + beta (Y + Y^T) per slot of fp32 [m x m] matrices (X may be
+// nullptr; fp32 I/O).
 hipError_t launch_sym32(const float* X, float alpha, const float* Y, float beta, float* out, int S, int m,
                         hipStream_t s);
 // G = base + sum of the sets over BH instances of RL floats each (RL a

@@ -260,13 +260,6 @@ template <> struct Kinds<__bf16> {
   using Grad13 = KGrad13_16;
   using Grad2 = KGrad2_16;
 };
-template <> struct Kinds<_Float16> {   // the backward of Newton-Schulz: fp16 operands
-  using Apply = KApply16;
-  using Update = KApply16;
-  using Out = KOut16;
-  using Grad13 = KGrad13_16;
-  using Grad2 = KGrad2_16;
-};
 template <> struct Kinds<float> {
   using Apply = KApply32;
   using Update = KUpdate32;
@@ -314,13 +307,6 @@ struct BwdKinds<__bf16, true> {
   using Grad13 = KGrad13N16;
   using Grad2 = KGrad2N16;
 };
-template <>
-struct BwdKinds<_Float16, true> {   // the Newton-Schulz reverse's GRAD2 products on 128 x 256 tiles
-  using Out = KOutN16;
-  using Grad13 = KGrad13N16;
-  using Grad2 = KGrad2N16;
-};
-
 template <class K>
 using Acc = f32x16_t[K::NACC][K::MI][K::NI];
 
@@ -1754,7 +1740,7 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& args, int blk, uint8_t* 
     return;
   }
 
-  if constexpr (sizeof(T) == 2 && !NARROW && !__is_same(T, _Float16)) {
+  if constexpr (sizeof(T) == 2 && !NARROW) {
     if (sg.kind == BWD_GRAD_UPD) {
       grad_update_tile<T>(sg, inst, rr, d, h, smem);
       return;
@@ -2224,6 +2210,162 @@ __global__ __launch_bounds__((NsKinds<T, BIG>::K::THREADS)) void k_ns(const NsAr
         }
       }
     }
+}
+
+// ---- Newton-Schulz of the backward: products with their combinations ------
+// (NsSymArgs, NsDxArgs in lact_internal.h.) The replayed iteration and its
+// reverse alternate small products with elementwise combinations of their
+// results; both run in one launch here, the combination in the product's
+// epilogue on the fp32 accumulators: per 48 slots of 512 x 512 a symmetric
+// combination in a launch of its own took 14 us (its product 24), the step's
+// fp32 combination 27 us (its products 35 and 57 with their fp32 results
+// written and read back).
+
+// Accumulators of a tile through LDS, as ns_epilogue_staged: `row(idx, v)` for
+// four consecutive elements (tile rows) of stored row j0 + c at idx =
+// (j0 + c) * ld + i0 + r; with `mirror` also `row` on the transposed place.
+// `pre(i, idx)` runs before the hand-over (loads of the row's other operand).
+template <class KK, bool MIRROR, class PRE, class ROW, class MIR>
+__device__ __forceinline__ void ns_rows_staged(const Acc<KK>& acc, uint8_t* smem, int64_t ld, int64_t i0, int64_t j0,
+                                               int64_t mrows, int64_t ncols, bool mirror, PRE&& pre, ROW&& row,
+                                               MIR&& mir) {
+  constexpr int R = KK::ROWS_A, SR = KK::WN * 32, CPR = R / 4, PER = SR * CPR / KK::THREADS;
+  static_assert(KK::NI == 2 && SR * R * 4 <= KK::NSTAGE * KK::STAGE && (SR * CPR) % KK::THREADS == 0 &&
+                    (CPR & (CPR - 1)) == 0, "staging shape");
+  float* st = reinterpret_cast<float*>(smem);
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int sr = wave_n<KK>() * 32 + (lane & 31);
+#pragma unroll
+    for (int mi = 0; mi < KK::MI; ++mi)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int r = acc_row<KK>(mi, 4 * g);
+        const f32x16_t& a = acc[0][mi][half];
+        *reinterpret_cast<float4*>(st + sr * R + (((r >> 2) ^ (sr & (CPR - 1))) << 2)) =
+            make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+      }
+    lds_barrier();
+    int64_t idx[PER];
+    bool ok[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int q = i * KK::THREADS + threadIdx.x;
+      const int srow = q / CPR, ch = q % CPR;
+      const int c = (srow / 32) * (KK::NI * 32) + half * 32 + (srow & 31);
+      ok[i] = c < ncols && ch * 4 < mrows;
+      idx[i] = (j0 + c) * ld + i0 + ch * 4;
+      if (ok[i]) pre(i, idx[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int q = i * KK::THREADS + threadIdx.x;
+      const int srow = q / CPR, ch = q % CPR;
+      const float4 v = *reinterpret_cast<const float4*>(st + srow * R + ((ch ^ (srow & (CPR - 1))) << 2));
+      if (ok[i]) row(i, idx[i], v);
+    }
+    if (MIRROR && mirror) {
+      constexpr int S4 = SR / 4, PERM = R * S4 / KK::THREADS;
+      static_assert((R * S4) % KK::THREADS == 0, "mirror shape");
+#pragma unroll
+      for (int i = 0; i < PERM; ++i) {
+        const int q = i * KK::THREADS + threadIdx.x;
+        const int r = q / S4, s0 = 4 * (q % S4);
+        const int c0 = (s0 / 32) * (KK::NI * 32) + half * 32 + (s0 & 31);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int sr2 = s0 + e;
+          v[e] = st[sr2 * R + ((((r >> 2) ^ (sr2 & (CPR - 1)))) << 2) + (r & 3)];
+        }
+        if (r < mrows && c0 < ncols) mir((i0 + r) * ld + j0 + c0, make_float4(v[0], v[1], v[2], v[3]));
+      }
+    }
+    if (half == 0) lds_barrier();   // every wave has read the first half
+  }
+}
+
+// acc = A0 B0^T [+ A1 B1^T]: the second product's first tile is handed over.
+template <class KK>
+__device__ __forceinline__ void mainloop_two(uint8_t* smem, const View (&o0)[2], const View (&o1)[2], bool two,
+                                             int64_t nk, Acc<KK>& acc) {
+  zero_acc<KK>(acc);
+  if (!two) {
+    mainloop_dma<_Float16, KK>(smem, o0, nk, acc);
+    return;
+  }
+  ChainNext<KK, KK::STAGE> nx(smem, o1);
+  mainloop_dma<_Float16, KK, KK::STAGE, ChainNext<KK, KK::STAGE>>(smem, o0, nk, acc, 0, false, &nx);
+  mainloop_dma<_Float16, KK>(smem, o1, nk, acc, nx.slot < 0 ? 0 : nx.slot, nx.slot >= 0);
+}
+
+__global__ __launch_bounds__(KNsK16S::THREADS) void k_ns_sym(const NsSymArgs a) {
+  using KK = KNsK16S;
+  typedef __attribute__((ext_vector_type(4))) _Float16 h4;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[smem_bytes<_Float16, KK>()];
+  const int bid = xcd_remap(blockIdx.x, a.nblocks);
+  const int t = (a.m + KK::ROWS_A - 1) / KK::ROWS_A, per = t * (t + 1) / 2;
+  const int slot = bid / per;
+  int ti = 0, left = bid - slot * per;
+  while (left >= t - ti) {   // row ti of the upper triangle holds t - ti tiles
+    left -= t - ti;
+    ++ti;
+  }
+  const int tj = ti + left;
+  const int64_t i0 = (int64_t)ti * KK::ROWS_A, j0 = (int64_t)tj * KK::ROWS_B, mrows = a.m - i0, ncols = a.m - j0;
+  const _Float16 *P = a.P + slot * a.in_inst, *Q = a.Q + slot * a.in_inst;
+  const int64_t pb = (int64_t)a.K * 2, mo = (int64_t)slot * a.m * a.m;
+  auto rows = [&](const _Float16* x, int64_t r0, int64_t n) {
+    return View{reinterpret_cast<const uint8_t*>(x + r0 * a.K), pb, n, a.K};
+  };
+  const View o0[2] = {rows(P, i0, mrows), rows(Q, j0, ncols)}, o1[2] = {rows(Q, i0, mrows), rows(P, j0, ncols)};
+  Acc<KK> acc;
+  mainloop_two<KK>(smem, o0, o1, a.two, a.K, acc);
+  const _Float16* E = a.E ? a.E + mo : nullptr;
+  _Float16* out = a.out + mo;
+  h4 e[16];
+  auto put = [&](int64_t idx, float4 v, h4 x) {
+    st4<_Float16>(out, idx, a.beta * v.x + a.alpha * (float)x[0], a.beta * v.y + a.alpha * (float)x[1],
+                  a.beta * v.z + a.alpha * (float)x[2], a.beta * v.w + a.alpha * (float)x[3]);
+  };
+  ns_rows_staged<KK, true>(
+      acc, smem, a.m, i0, j0, mrows, ncols, ti != tj,
+      [&](int i, int64_t idx) { e[i] = E ? *reinterpret_cast<const h4*>(E + idx) : h4{}; },
+      [&](int i, int64_t idx, float4 v) { put(idx, v, e[i]); },
+      [&](int64_t idx, float4 v) { put(idx, v, E ? *reinterpret_cast<const h4*>(E + idx) : h4{}); });
+}
+
+template <bool BIG>
+__global__ __launch_bounds__((NsKinds<_Float16, BIG>::TY::THREADS)) void k_ns_dx(const NsDxArgs a) {
+  using KT = typename NsKinds<_Float16, BIG>::TY;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[smem_bytes<_Float16, KT>()];
+  const int bid = xcd_remap(blockIdx.x, a.nblocks);
+  const int tm = (a.n + KT::ROWS_A - 1) / KT::ROWS_A, tn = (a.m + KT::ROWS_B - 1) / KT::ROWS_B;
+  const int slot = bid / (tm * tn), rr = bid - slot * (tm * tn);
+  const int64_t i0 = (int64_t)(rr / tn) * KT::ROWS_A, j0 = (int64_t)(rr % tn) * KT::ROWS_B;
+  const int64_t mrows = a.n - i0, ncols = a.m - j0, yo = (int64_t)slot * a.m * a.n, bo = (int64_t)slot * a.m * a.m;
+  auto ops = [&](int k, int o) {   // tile rows: columns of Y; tile columns: rows of B (symmetric)
+    return o == 0 ? View{reinterpret_cast<const uint8_t*>(a.Y[k] + yo + i0), (int64_t)a.n * 2, mrows, a.m}
+                  : View{reinterpret_cast<const uint8_t*>(a.B[k] + bo + j0 * a.m), (int64_t)a.m * 2, ncols, a.m};
+  };
+  const View o0[2] = {ops(0, 0), ops(0, 1)}, o1[2] = {ops(1, 0), ops(1, 1)};
+  Acc<KT> acc;
+  mainloop_two<KT>(smem, o0, o1, a.two, a.m, acc);
+  const float* x = a.x32 + yo;
+  float* y = a.out32 + yo;
+  _Float16* h = a.out16 ? a.out16 + yo : nullptr;
+  float4 old[16];
+  ns_rows_staged<KT, false>(
+      acc, smem, a.n, i0, j0, mrows, ncols, false,
+      [&](int i, int64_t idx) { old[i] = *reinterpret_cast<const float4*>(x + idx); },
+      [&](int i, int64_t idx, float4 v) {
+        const float4 o = old[i];
+        const float4 r = make_float4(a.ca * o.x + v.x, a.ca * o.y + v.y, a.ca * o.z + v.z, a.ca * o.w + v.w);
+        *reinterpret_cast<float4*>(y + idx) = r;
+        if (h) st4<_Float16>(h, idx, r.x, r.y, r.z, r.w);
+      },
+      [](int64_t, float4) {});
 }
 
 // ---------------------------------------------------------------------------
@@ -3005,48 +3147,8 @@ __global__ __launch_bounds__(256) void k_ns_lin(const NsLinArgs a) {
   }
 }
 
-// out = alpha X + beta (Y + Y^T) per slot of fp16 [m x m] matrices: one
-// 32 x 32 output tile per block, Y's mirror tile through LDS.
-// 64 x 64 tiles, each row segment moved as 16-byte vectors of 8 halves (m is
-// a multiple of 8, so a vector lies wholly inside or outside the matrix);
-// the mirror tile goes through LDS.
-__global__ __launch_bounds__(256) void k_sym(const _Float16* X, float alpha, const _Float16* Y, float beta,
-                                             _Float16* out, int m, int tiles) {
-  typedef __attribute__((ext_vector_type(8))) _Float16 h8;
-  __shared__ float mir[64][65];
-  const int per = tiles * tiles;
-  const int64_t slot = blockIdx.x / per;
-  const int rest = blockIdx.x - (int)slot * per;
-  const int r0 = (rest / tiles) * 64, c0 = (rest % tiles) * 64;
-  const int64_t base = slot * (int64_t)m * m;
-  const int tv = threadIdx.x & 7, ty = threadIdx.x >> 3;   // 8 vectors per 64-wide row, 32 rows per pass
-  for (int k = ty; k < 64; k += 32) {   // mirror tile: mir[k][j] = Y[c0 + k][r0 + j]
-    const int r = c0 + k, c = r0 + 8 * tv;
-    h8 y = {};
-    if (r < m && c < m) y = *reinterpret_cast<const h8*>(Y + base + (int64_t)r * m + c);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) mir[k][8 * tv + j] = (float)y[j];
-  }
-  __syncthreads();
-  for (int k = ty; k < 64; k += 32) {
-    const int r = r0 + k, c = c0 + 8 * tv;
-    if (r >= m || c >= m) continue;
-    const int64_t o = base + (int64_t)r * m + c;
-    const h8 y = *reinterpret_cast<const h8*>(Y + o);
-    h8 x = {};
-    if (X) x = *reinterpret_cast<const h8*>(X + o);
-    h8 v;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float t = beta * ((float)y[j] + mir[8 * tv + j][k]);
-      if (X) t += alpha * (float)x[j];
-      v[j] = (_Float16)t;
-    }
-    *reinterpret_cast<h8*>(out + o) = v;
-  }
-}
-
-// The fp32 form of k_sym: 64 x 64 tiles, float4 vectors (m a multiple of 4).
+// out = alpha X + beta (Y + Y^T) per slot of fp32 [m x m] matrices: 64 x 64
+// tiles of float4 vectors (m a multiple of 4), Y's mirror tile through LDS.
 __global__ __launch_bounds__(256) void k_sym32(const float* X, float alpha, const float* Y, float beta, float* out,
                                                int m, int tiles) {
   __shared__ float mir[64][65];
@@ -3548,10 +3650,25 @@ hipError_t launch_mom_adv(const float* M, const float* bbar, int64_t bbar_inst, 
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_f16(const BwdArgs& a, hipStream_t s) {
-  if (a.total_blocks <= 0) return hipSuccess;
-  if (a.narrow) k_bwd<_Float16, true><<<a.total_blocks, KOutN16::THREADS, 0, s>>>(a);
-  else k_bwd<_Float16, false><<<a.total_blocks, KOut16::THREADS, 0, s>>>(a);
+hipError_t launch_ns_sym(NsSymArgs a, hipStream_t s) {
+  const int64_t t = (a.m + KNsK16S::ROWS_A - 1) / KNsK16S::ROWS_A, n = a.S * (t * (t + 1) / 2);
+  if (n <= 0) return hipSuccess;
+  if (n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  a.nblocks = (int)n;
+  k_ns_sym<<<(unsigned)n, KNsK16S::THREADS, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+// 256 x 256 tiles where the slots' side fills them (as the forward's update product)
+hipError_t launch_ns_dx(NsDxArgs a, hipStream_t s) {
+  const bool big = a.m > 128;
+  const int64_t tr = big ? KNsTY16B::ROWS_A : KNsTY16S::ROWS_A;
+  const int64_t n = a.S * ((a.n + tr - 1) / tr) * ((a.m + tr - 1) / tr);
+  if (n <= 0) return hipSuccess;
+  if (n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  a.nblocks = (int)n;
+  if (big) k_ns_dx<true><<<(unsigned)n, KNsTY16B::THREADS, 0, s>>>(a);
+  else k_ns_dx<false><<<(unsigned)n, KNsTY16S::THREADS, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -3569,17 +3686,6 @@ hipError_t launch_ns_lin(const NsLinArgs& a, hipStream_t s) {
   if (need <= 0) return hipSuccess;
   const int64_t blocks = need < 8192 ? need : 8192;
   k_ns_lin<<<(unsigned)blocks, 256, 0, s>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t launch_sym(const _Float16* X, float alpha, const _Float16* Y, float beta, _Float16* out, int S, int m,
-                      hipStream_t s) {
-  if (m % 8) return hipErrorInvalidValue;
-  const int tiles = (m + 63) / 64;
-  const int64_t blocks = (int64_t)S * tiles * tiles;
-  if (blocks <= 0) return hipSuccess;
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  k_sym<<<(unsigned)blocks, 256, 0, s>>>(X, alpha, Y, beta, out, m, tiles);
   return hipGetLastError();
 }
 

@@ -1782,6 +1782,18 @@ def test_swiglu_muon_backward_small_matrices(order):
     check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
 
 
+@pytest.mark.parametrize("d,h", [(32, 64), (96, 160), (160, 96), (160, 288), (288, 256)])
+def test_swiglu_muon_backward_product_tiles(d, h):
+    # the Newton-Schulz products of the backward at the edges of their tiles:
+    # one partial 128 x 128 tile, a second one of a few rows (160 = 128 + 32,
+    # the symmetric products' mirrored tiles), 256 x 256 step tiles that the
+    # slot does not fill, either orientation; one whole-rank update
+    C = 4 * max(d, h)
+    cfg = CONFIGS["lm32k_muon"].with_(name="muon_bwd_tiles", B=1, H=2, d=d, h=h, n_kv=C, n_q=C + 50, chunk=C, order=1)
+    x, ct = make_inputs(cfg, 86), make_cotangents(cfg, 86)
+    check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
+
+
 def test_swiglu_muon_backward_lm_shape_two_chunks():
     # d = h = 512 (the LM's Gram size), two chunks of 2048
     cfg = CONFIGS["lm32k_muon"].with_(name="swiglu_muon_bwd_lm", B=1, H=2, n_kv=4096, n_q=4096)
