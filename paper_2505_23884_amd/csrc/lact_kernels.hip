@@ -2388,38 +2388,58 @@ __device__ __forceinline__ int fsw(int row) { return ((row & 7) << 1) | ((row >>
 __device__ __forceinline__ uint32_t fs_off(int row, int chunk, int pitch) {
   return (uint32_t)(row * pitch + ((chunk ^ fsw(row)) << 4));
 }
-// K-contiguous fragment: row `row`, 8 K from chunk `chunk`.
-__device__ __forceinline__ u32x4_t fs_frag_k(uint32_t base, int row, int chunk, int pitch) {
-  return lds_read_b128(base + fs_off(row, chunk, pitch));
+// Fragment addresses of this lane, computed once: substep s of a K-contiguous
+// operand (row `row` of the matrix at `base`) is an XOR away (the swizzle only
+// permutes the 16 chunks of a 256-byte window, and 2 s + half = half ^ 2 s), a
+// 32-row block 32 pitches; the matrices are aligned to their pitch.
+__device__ __forceinline__ uint32_t fs_addr_k(uint32_t base, int row, int lane, int pitch) {
+  return base + fs_off(row, lane >> 5, pitch);
 }
-// Transposed fragment (8 consecutive K of column rb + lane%32 of a tile whose
-// K runs down the rows, substep s).
-__device__ __forceinline__ u32x4_t fs_frag_tr(uint32_t base, int rb, int s, int pitch) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, sl = lane & 15;
-  const int mn = rb + 16 * (g & 1) + 4 * (sl & 3);
-  const int c = mn >> 3, hb = (mn >> 2) & 1;
+__device__ __forceinline__ u32x4_t fs_frag_k(uint32_t a, int s) { return lds_read_b128(a ^ (uint32_t)(s << 5)); }
+// Transposed fragments (8 consecutive K of columns rb .. rb + 31, rb a
+// multiple of 64, or of 32 where no neighbour block is taken) of a matrix
+// whose K runs down the rows: two reads, 4 K rows apart with a swizzle of
+// their own; substep s is 16 rows further, columns 32 further flip chunk bit 2.
+struct FsTr {
+  uint32_t lo, hi;
+};
+__device__ __forceinline__ FsTr fs_addr_tr(uint32_t base, int rb, int lane, int pitch) {
+  const int g = lane >> 4, sl = lane & 15;
+  const int mn = rb + 16 * (g & 1) + 4 * (sl & 3), kr = 8 * (g >> 1) + (sl >> 2);
+  const uint32_t hb = ((mn >> 2) & 1) << 3;
+  return FsTr{base + fs_off(kr, mn >> 3, pitch) + hb, base + fs_off(kr + 4, mn >> 3, pitch) + hb};
+}
+__device__ __forceinline__ u32x4_t fs_frag_tr(FsTr a, int blk, int s, int pitch) {
   u32x2_t lo, hi;
-  {
-    const int kr = 16 * s + 8 * (g >> 1) + (sl >> 2);
-    const uint32_t a = base + kr * pitch + ((c ^ fsw(kr)) << 4) + (hb << 3);
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(a));
-  }
-  {
-    const int kr = 16 * s + 8 * (g >> 1) + 4 + (sl >> 2);
-    const uint32_t a = base + kr * pitch + ((c ^ fsw(kr)) << 4) + (hb << 3);
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(hi) : "v"(a));
-  }
+  const uint32_t x = (uint32_t)(blk << 6), o = (uint32_t)(16 * s * pitch);
+  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"((a.lo ^ x) + o));
+  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(hi) : "v"((a.hi ^ x) + o));
   return u32x4_t{lo[0], lo[1], hi[0], hi[1]};
 }
-// Wait for every LDS read of this wave and make the fragments depend on the
-// wait, so that no MFMA reading them can be scheduled above it.
-template <int NA, int NB>
-__device__ __forceinline__ void lds_ready(u32x4_t (&fa)[NA], u32x4_t (&fb)[NB]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+// One product over S substeps of 16 K: the fragments of substep s + 1 are read
+// while substep s multiplies (R: LDS instructions of one substep). With every
+// substep waiting for its own reads the three products of a step spent most
+// of their time on LDS latency.
+template <int S, int R, int NA, int NB, class LD, class MM>
+__device__ __forceinline__ void fs_loop(LD&& load, MM&& mul) {
+  u32x4_t fa[2][NA], fb[2][NB];
+  load(0, fa[0], fb[0]);
 #pragma unroll
-  for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(fa[i]));
+  for (int s = 0; s < S; ++s) {
+    const int b = s & 1;
+    if (s + 1 < S) {
+      load(s + 1, fa[b ^ 1], fb[b ^ 1]);
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fa[b][0]) : "n"(R));
+    } else {
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[b][0]));
+    }
 #pragma unroll
-  for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(fb[i]));
+    for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(fa[b][i]));
+#pragma unroll
+    for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(fb[b][i]));
+    mul(fa[b], fb[b]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 __device__ __forceinline__ f32x16_t mfma16(u32x4_t a, u32x4_t b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0,
@@ -2438,7 +2458,8 @@ __device__ __forceinline__ void fs_put4(uint8_t* base, int row, int col, int pit
 constexpr int kNsFusedX = kNsFusedM * kNsFusedN * 2, kNsFusedA = kNsFusedM * kNsFusedM * 2;
 
 template <bool TALL>
-__device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8_t* xs, uint8_t* as_, uint8_t* bs) {
+__device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8_t* smem) {
+  uint8_t *const xs = smem, *const as_ = smem + kNsFusedX, *const bs = as_ + kNsFusedA;
   constexpr int M = kNsFusedM, N = kNsFusedN;
   constexpr int SR = TALL ? N : M, SC = TALL ? M : N;   // padded stored orientation
   constexpr int PX = SC * 2, PA = M * 2;                // LDS pitches (bytes)
@@ -2448,16 +2469,47 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   const int64_t slot = (int64_t)(q / a.group) * a.spi + a.slot_off[q % a.group];
   const int sr = a.rows, sc = a.cols;                   // valid stored rows, columns
 
-  // LDS copy of X zero padded (written below)
-  for (int i = tid; i < SR * PX / 16; i += 512) *reinterpret_cast<u32x4_t*>(xs + i * 16) = u32x4_t{0u, 0u, 0u, 0u};
-  __syncthreads();
   // The summed gradient into registers, in the tile layout of the update
-  // product: tile rows = stored columns (TR rows), tile columns = stored rows (TC)
+  // product: tile rows = stored columns (TR rows), tile columns = stored rows
+  // (TC). It comes through LDS (all of it: the padded fp32 matrix takes the
+  // three buffers), so that lanes read whole rows: straight from the tile
+  // layout each lane took 16 bytes of another row, 11.9 us of a workgroup's 49.
+  // 16-byte chunks are XORed with the row, for the reads down the rows.
   constexpr int WM3 = TALL ? 2 : 4, WN3 = TALL ? 4 : 2;   // waves: 64 x 64 each
   const int r3 = (w / WN3) * 64, c3 = (w % WN3) * 64;
+  constexpr int C4 = SC / 4;   // 16-byte chunks per fp32 row
+  static_assert(SR * SC * 4 == kNsFusedX + 2 * kNsFusedA && SR * C4 == 16 * 512, "fp32 matrix in LDS");
+  auto f32_at = [&](int row, int c4) {
+    return reinterpret_cast<float4*>(smem + row * (SC * 4) + ((c4 ^ (row & 31)) << 4));
+  };
   const float* xin = a.src + slot * a.ystride;
-  const int nin = a.nsplit;
   f32x16_t x32[2][2];
+  {
+    float4 v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
+      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (row < sr && c < sc) v[i] = *reinterpret_cast<const float4*>(xin + (int64_t)row * sc + c);
+    }
+    for (int sp = 1; sp < a.nsplit; ++sp) {
+      const float* xp = xin + sp * a.part_split;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
+        if (row < sr && c < sc) {
+          const float4 p = *reinterpret_cast<const float4*>(xp + (int64_t)row * sc + c);
+          v[i] = make_float4(v[i].x + p.x, v[i].y + p.y, v[i].z + p.z, v[i].w + p.w);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int f = i * 512 + tid;
+      *f32_at(f / C4, f % C4) = v[i];
+    }
+  }
+  __syncthreads();
 #pragma unroll
   for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -2466,18 +2518,14 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int r = r3 + mi * 32 + 8 * g + 4 * half;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c < sr && r < sc)
-          for (int sp = 0; sp < nin; ++sp) {
-            const float4 p = *reinterpret_cast<const float4*>(xin + sp * a.part_split + (int64_t)c * sc + r);
-            v = make_float4(v.x + p.x, v.y + p.y, v.z + p.z, v.w + p.w);
-          }
+        const float4 v = *f32_at(c, r >> 2);
         x32[mi][ni][4 * g] = v.x;
         x32[mi][ni][4 * g + 1] = v.y;
         x32[mi][ni][4 * g + 2] = v.z;
         x32[mi][ni][4 * g + 3] = v.w;
       }
     }
+  __syncthreads();   // the fp32 copy is read
   {
     // X0 = G / (||G||_F + eps): the whole matrix is in this workgroup's
     // registers (padding is zero); the partial sums go through the start of
@@ -2518,33 +2566,46 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   // Gram tile layout: waves 2 x 4 of 64 x 32
   const int r1 = (w >> 2) * 64, c1 = (w & 3) * 32;
   for (int step = 0; step < a.steps; ++step) {
+    // the lane as a value of this step: the LDS addresses are cheap to form,
+    // and kept over the steps they would not fit the registers
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int half = ln >> 5;
     // ---- A = X X^T (K = N) ----
     f32x16_t a32[2];
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
       for (int e = 0; e < 16; ++e) a32[mi][e] = 0.f;
-    for (int s = 0; s < N / 16; ++s) {
-      u32x4_t fa[2], fb[1];
-      if constexpr (!TALL) {
+    auto mul1 = [&](const u32x4_t (&fa)[2], const u32x4_t (&fb)[1], f32x16_t (&acc)[2]) {
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi) fa[mi] = fs_frag_k(xb, r1 + mi * 32 + (lane & 31), 2 * s + half, PX);
-        fb[0] = fs_frag_k(xb, c1 + (lane & 31), 2 * s + half, PX);
-      } else {
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi) fa[mi] = fs_frag_tr(xb, r1 + mi * 32, s, PX);
-        fb[0] = fs_frag_tr(xb, c1, s, PX);
-      }
-      lds_ready(fa, fb);
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi) a32[mi] = mfma16(fa[mi], fb[0], a32[mi]);
+      for (int mi = 0; mi < 2; ++mi) acc[mi] = mfma16(fa[mi], fb[0], acc[mi]);
+    };
+    if constexpr (!TALL) {
+      const uint32_t ra = fs_addr_k(xb, r1 + (ln & 31), ln, PX), ca = fs_addr_k(xb, c1 + (ln & 31), ln, PX);
+      fs_loop<N / 16, 3, 2, 1>(
+          [&](int s, u32x4_t (&fa)[2], u32x4_t (&fb)[1]) {
+            fa[0] = fs_frag_k(ra, s);
+            fa[1] = fs_frag_k(ra + 32 * PX, s);
+            fb[0] = fs_frag_k(ca, s);
+          },
+          [&](const u32x4_t (&fa)[2], const u32x4_t (&fb)[1]) { mul1(fa, fb, a32); });
+    } else {
+      const FsTr ra = fs_addr_tr(xb, r1, ln, PX), ca = fs_addr_tr(xb, c1, ln, PX);
+      fs_loop<N / 16, 6, 2, 1>(
+          [&](int s, u32x4_t (&fa)[2], u32x4_t (&fb)[1]) {
+            fa[0] = fs_frag_tr(ra, 0, s, PX);
+            fa[1] = fs_frag_tr(ra, 1, s, PX);
+            fb[0] = fs_frag_tr(ca, 0, s, PX);
+          },
+          [&](const u32x4_t (&fa)[2], const u32x4_t (&fb)[1]) { mul1(fa, fb, a32); });
     }
     // A is symmetric: lane's rows i..i+3 at column j go to row j, columns i..i+3
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
-        fs_put4(as_, c1 + (lane & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, a32[mi][4 * g], a32[mi][4 * g + 1],
+        fs_put4(as_, c1 + (ln & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, a32[mi][4 * g], a32[mi][4 * g + 1],
                 a32[mi][4 * g + 2], a32[mi][4 * g + 3]);
     lds_barrier();
     // ---- B = b A + c A A (K = M) ----
@@ -2553,14 +2614,15 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
       for (int e = 0; e < 16; ++e) t[mi][e] = 0.f;
-    for (int s = 0; s < M / 16; ++s) {
-      u32x4_t fa[2], fb[1];
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi) fa[mi] = fs_frag_k(ab, r1 + mi * 32 + (lane & 31), 2 * s + half, PA);
-      fb[0] = fs_frag_k(ab, c1 + (lane & 31), 2 * s + half, PA);
-      lds_ready(fa, fb);
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi) t[mi] = mfma16(fa[mi], fb[0], t[mi]);
+    {
+      const uint32_t ra = fs_addr_k(ab, r1 + (ln & 31), ln, PA), ca = fs_addr_k(ab, c1 + (ln & 31), ln, PA);
+      fs_loop<M / 16, 3, 2, 1>(
+          [&](int s, u32x4_t (&fa)[2], u32x4_t (&fb)[1]) {
+            fa[0] = fs_frag_k(ra, s);
+            fa[1] = fs_frag_k(ra + 32 * PA, s);
+            fb[0] = fs_frag_k(ca, s);
+          },
+          [&](const u32x4_t (&fa)[2], const u32x4_t (&fb)[1]) { mul1(fa, fb, t); });
     }
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
@@ -2569,7 +2631,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
         float v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = a.cb * a32[mi][4 * g + e] + a.cc * t[mi][4 * g + e];
-        fs_put4(bs, c1 + (lane & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, v[0], v[1], v[2], v[3]);
+        fs_put4(bs, c1 + (ln & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, v[0], v[1], v[2], v[3]);
       }
     lds_barrier();
     // ---- X <- a X + B X (K = M), tile rows = stored columns ----
@@ -2580,30 +2642,38 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
       for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
         for (int e = 0; e < 16; ++e) u[mi][ni][e] = 0.f;
-    for (int s = 0; s < M / 16; ++s) {
-      u32x4_t fa[2], fb[2];
+    {
+      // rows: X[k][j] down the rows, or B[i][k]; columns: B[i][k], or Y[j][k] = X[k][j]
+      const FsTr rx = fs_addr_tr(xb, r3, ln, PX);
+      const uint32_t rb = fs_addr_k(bb, (TALL ? r3 : c3) + (ln & 31), ln, PA);
+      const uint32_t cx = fs_addr_k(xb, c3 + (ln & 31), ln, PX);
+      fs_loop<M / 16, TALL ? 4 : 6, 2, 2>(
+          [&](int s, u32x4_t (&fa)[2], u32x4_t (&fb)[2]) {
+            if constexpr (!TALL) {
+              fa[0] = fs_frag_tr(rx, 0, s, PX);
+              fa[1] = fs_frag_tr(rx, 1, s, PX);
+              fb[0] = fs_frag_k(rb, s);
+              fb[1] = fs_frag_k(rb + 32 * PA, s);
+            } else {
+              fa[0] = fs_frag_k(rb, s);
+              fa[1] = fs_frag_k(rb + 32 * PA, s);
+              fb[0] = fs_frag_k(cx, s);
+              fb[1] = fs_frag_k(cx + 32 * PX, s);
+            }
+          },
+          [&](const u32x4_t (&fa)[2], const u32x4_t (&fb)[2]) {
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi) {
-        if constexpr (!TALL) fa[mi] = fs_frag_tr(xb, r3 + mi * 32, s, PX);   // X[k][j], k down the rows
-        else fa[mi] = fs_frag_k(bb, r3 + mi * 32 + (lane & 31), 2 * s + half, PA);   // B[i][k]
-      }
+            for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        if constexpr (!TALL) fb[ni] = fs_frag_k(bb, c3 + ni * 32 + (lane & 31), 2 * s + half, PA);   // B[i][k]
-        else fb[ni] = fs_frag_k(xb, c3 + ni * 32 + (lane & 31), 2 * s + half, PX);   // Y[j][k] = X[k][j]
-      }
-      lds_ready(fa, fb);
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) u[mi][ni] = mfma16(fa[mi], fb[ni], u[mi][ni]);
+              for (int ni = 0; ni < 2; ++ni) u[mi][ni] = mfma16(fa[mi], fb[ni], u[mi][ni]);
+          });
     }
     lds_barrier();   // every wave is done reading X before it is overwritten
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
       for (int ni = 0; ni < 2; ++ni) {
-        const int c = c3 + ni * 32 + (lane & 31);
+        const int c = c3 + ni * 32 + (ln & 31);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int r = r3 + mi * 32 + 8 * g + 4 * half;
@@ -2620,80 +2690,67 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   }
   {
     // The weight update of this matrix with X as the step (§3.2 weight
-    // normalisation; Muon's update, App. A): a lane holds 32 columns of stored
-    // rows c (ni = 0, 1); row sums over the lane, its partner half (lane ^ 32)
-    // and the WM3 wave rows (through LDS, free after the last step's barrier)
+    // normalisation; Muon's update, App. A): X through LDS as the gradient
+    // came, so that 64 (32 for rows of 128) lanes stream a row of W in 16-byte
+    // vectors and sum its squares by shuffles
     const int j = a.slot_off[q % a.group];
     const int64_t woff = (int64_t)(q / a.group) * a.ystride;
     float* Wj = a.W[j] + woff;
     __bf16* Wbj = reinterpret_cast<__bf16*>(a.Wb[j]) + woff;
-    float sw[2] = {0.f, 0.f}, su[2] = {0.f, 0.f};
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const int c = c3 + ni * 32 + (lane & 31);
+    for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
+      for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int r = r3 + mi * 32 + 8 * g + 4 * half;
-          float4 wv = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (c < sr && r < sc) wv = *reinterpret_cast<const float4*>(Wj + (int64_t)c * sc + r);
-          const float wa[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float u = wa[e] + x32[mi][ni][4 * g + e];
-            x32[mi][ni][4 * g + e] = u;
-            sw[ni] = fmaf(wa[e], wa[e], sw[ni]);
-            su[ni] = fmaf(u, u, su[ni]);
-          }
-        }
-      sw[ni] += __shfl_xor(sw[ni], 32, 64);
-      su[ni] += __shfl_xor(su[ni], 32, 64);
-    }
-    float* red = reinterpret_cast<float*>(as_);   // [WM3][SR][2]
-    const int wr = w / WN3;
-    if (half == 0)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int c = c3 + ni * 32 + (lane & 31);
-        red[(wr * SR + c) * 2] = sw[ni];
-        red[(wr * SR + c) * 2 + 1] = su[ni];
-      }
-    __syncthreads();
+        for (int g = 0; g < 4; ++g)
+          *f32_at(c3 + ni * 32 + (lane & 31), (r3 + mi * 32 + 8 * g + 4 * half) >> 2) =
+              make_float4(x32[mi][ni][4 * g], x32[mi][ni][4 * g + 1], x32[mi][ni][4 * g + 2], x32[mi][ni][4 * g + 3]);
     typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+    const int c4 = lane % C4, row0 = w * (64 / C4) + lane / C4;   // C4 lanes a row
+    const bool cok = c4 * 4 < sc;
+    constexpr int STEP = 8 * (64 / C4), U = 8;
+    auto load = [&](int row) {
+      return cok && row < sr ? *reinterpret_cast<const float4*>(Wj + (int64_t)row * sc + c4 * 4)
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    float4 wv[U];
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const int c = c3 + ni * 32 + (lane & 31);
-      float tw = 0.f, tu = 0.f;
+    for (int i = 0; i < U; ++i) wv[i] = load(row0 + i * STEP);
+    __syncthreads();
 #pragma unroll
-      for (int k = 0; k < WM3; ++k) {
-        tw += red[(k * SR + c) * 2];
-        tu += red[(k * SR + c) * 2 + 1];
+    for (int b = 0; b < SR; b += U * STEP) {
+      if (b) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) wv[i] = load(row0 + b + i * STEP);
       }
-      const float f = sqrtf(tw) / sqrtf(tu);
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
+      for (int i = 0; i < U; ++i) {
+        const int row = row0 + b + i * STEP;
+        const float4 x = *f32_at(row, c4), o = wv[i];
+        const float4 u = make_float4(o.x + x.x, o.y + x.y, o.z + x.z, o.w + x.w);
+        float sw = o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
+        float su = cok ? u.x * u.x + u.y * u.y + u.z * u.z + u.w * u.w : 0.f;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int r = r3 + mi * 32 + 8 * g + 4 * half;
-          if (c < sr && r < sc) {
-            const float4 x = make_float4(x32[mi][ni][4 * g] * f, x32[mi][ni][4 * g + 1] * f,
-                                         x32[mi][ni][4 * g + 2] * f, x32[mi][ni][4 * g + 3] * f);
-            *reinterpret_cast<float4*>(Wj + (int64_t)c * sc + r) = x;
-            *reinterpret_cast<bf16x4_t*>(Wbj + (int64_t)c * sc + r) =
-                bf16x4_t{(__bf16)x.x, (__bf16)x.y, (__bf16)x.z, (__bf16)x.w};
-          }
+        for (int off = 1; off < C4; off <<= 1) {
+          sw += __shfl_xor(sw, off, 64);
+          su += __shfl_xor(su, off, 64);
         }
+        const float f = sqrtf(sw) / sqrtf(su);
+        if (cok && row < sr) {
+          const float4 y = make_float4(u.x * f, u.y * f, u.z * f, u.w * f);
+          *reinterpret_cast<float4*>(Wj + (int64_t)row * sc + c4 * 4) = y;
+          *reinterpret_cast<bf16x4_t*>(Wbj + (int64_t)row * sc + c4 * 4) =
+              bf16x4_t{(__bf16)y.x, (__bf16)y.y, (__bf16)y.z, (__bf16)y.w};
+        }
+      }
     }
   }
 }
 
 template <bool TALL>
 __global__ __launch_bounds__(512) void k_ns_fused(const NsFusedArgs a) {
-  __shared__ __attribute__((aligned(16))) uint8_t xs[kNsFusedX];
-  __shared__ __attribute__((aligned(16))) uint8_t as_[kNsFusedA];
-  __shared__ __attribute__((aligned(16))) uint8_t bs[kNsFusedA];
-  ns_fused_body<TALL>(a, blockIdx.x, xs, as_, bs);
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kNsFusedX + 2 * kNsFusedA];
+  ns_fused_body<TALL>(a, blockIdx.x, smem);
 }
 
 // Both matrix groups of an instance set in one launch (W1 and W3, then W2, in
@@ -2701,12 +2758,10 @@ __global__ __launch_bounds__(512) void k_ns_fused(const NsFusedArgs a) {
 // that the matrices of both orientations fill the chip together.
 template <bool TALL0, bool TALL1>
 __global__ __launch_bounds__(512) void k_ns_fused_pair(const NsFusedArgs a0, const NsFusedArgs a1) {
-  __shared__ __attribute__((aligned(16))) uint8_t xs[kNsFusedX];
-  __shared__ __attribute__((aligned(16))) uint8_t as_[kNsFusedA];
-  __shared__ __attribute__((aligned(16))) uint8_t bs[kNsFusedA];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kNsFusedX + 2 * kNsFusedA];
   const int q = blockIdx.x;
-  if (q < a0.nblocks) ns_fused_body<TALL0>(a0, q, xs, as_, bs);
-  else ns_fused_body<TALL1>(a1, q - a0.nblocks, xs, as_, bs);
+  if (q < a0.nblocks) ns_fused_body<TALL0>(a0, q, smem);
+  else ns_fused_body<TALL1>(a1, q - a0.nblocks, smem);
 }
 
 // The small-matrix Newton-Schulz of both groups together with the output
@@ -2721,11 +2776,11 @@ __global__ __launch_bounds__(512) void k_ns_fused_pair_out(const NsFusedArgs a0,
                                                            const BwdArgs out) {
   static_assert(KOutN16::THREADS == 512, "one block size");
   constexpr int kNs = kNsFusedX + 2 * kNsFusedA;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[cmax(kNs, bwd_smem<__bf16, true>())];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[cmax(kNs, bwd_smem<__bf16, true>())];
   const int q = blockIdx.x;
-  if (q < a0.nblocks) ns_fused_body<TALL0>(a0, q, smem, smem + kNsFusedX, smem + kNsFusedX + kNsFusedA);
+  if (q < a0.nblocks) ns_fused_body<TALL0>(a0, q, smem);
   else if (q < a0.nblocks + a1.nblocks)
-    ns_fused_body<TALL1>(a1, q - a0.nblocks, smem, smem + kNsFusedX, smem + kNsFusedX + kNsFusedA);
+    ns_fused_body<TALL1>(a1, q - a0.nblocks, smem);
   else bwd_body<__bf16, true>(out, q - a0.nblocks - a1.nblocks, smem);
 }
 
