@@ -26,14 +26,15 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Tiles of the first launch: narrow (128 x 128) for d <= 128, and for 16-bit
-// launches whose wide tiles (128 x 256) would leave at least half of the 256
-// CUs idle: `segs` segments of n tokens ([1, 4, 5003, 512], chunks of 1024:
-// first launch 33.4 us in 128 wide tiles, 30.7 us in 256 narrow ones).
-bool fwd_narrow(bool narrow, bool bf16, int BH, int h, int64_t n, int segs) {
+// Tiles of the first launch (FwdArgs::narrow): narrow (128 x 128) for d <= 128;
+// for 16-bit launches whose wide tiles (128 x 256) would leave at least half
+// of the 256 CUs idle, the deep form of the narrow ones, at most one per CU:
+// `segs` segments of n tokens ([1, 4, 5003, 512], chunks of 1024: first launch
+// 33.4 us in 128 wide tiles, 30.7 us in 256 narrow ones, 26.8 us deep).
+int fwd_shape(bool narrow, bool bf16, int BH, int h, int64_t n, int segs) {
   if (narrow || !bf16) return narrow;
   const TileShape t = fwd_tile(FWD_APPLY, true, false);
-  return segs * BH * cdiv(h, t.rows) * cdiv(n, t.cols) <= 128;
+  return segs * BH * cdiv(h, t.rows) * cdiv(n, t.cols) <= 128 ? 2 : 0;
 }
 
 // Shape-derived plan shared by lact_workspace_bytes and lact_forward.
@@ -365,7 +366,7 @@ int apply_rows(Ctx& c, int64_t s0, int64_t s1) {
     const int64_t n = std::min<int64_t>(p.cap, s1 - a);
     FwdArgs f{};
     FwdSeg& g = f.seg[0];
-    f.narrow = fwd_narrow(p.narrow, p.bf16, p.BH, p.h, n, 1);
+    f.narrow = fwd_shape(p.narrow, p.bf16, p.BH, p.h, n, 1);
     g.kind = FWD_APPLY;
     g.tiles_m = (int)cdiv(p.h, fwd_tile(FWD_APPLY, p.bf16, f.narrow).rows);
     g.tiles_n = (int)cdiv(n, fwd_tile(FWD_APPLY, p.bf16, f.narrow).cols);
@@ -633,7 +634,7 @@ int update_chunk(Ctx& c, int64_t s0, int64_t s1, bool apply_too) {
   const int64_t n = s1 - s0;
   const int64_t dh = (int64_t)p.d * p.h;
   FwdArgs f{};
-  f.narrow = fwd_narrow(p.narrow, p.bf16, p.BH, p.h, n, apply_too ? 2 : 1);
+  f.narrow = fwd_shape(p.narrow, p.bf16, p.BH, p.h, n, apply_too ? 2 : 1);
   int ns = 0;
   {
     FwdSeg& g = f.seg[ns++];

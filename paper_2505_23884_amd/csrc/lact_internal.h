@@ -50,7 +50,8 @@ struct FwdArgs {
   int d, h;
   Operand w1, w3;       // h x d, kmajor (operand copies of the fast weight)
   Operand w2;           // d x h; the key forward reads it as an mn operand
-  bool narrow;          // 16-bit: 128 x 128 tiles, two workgroups per CU; fp32: 64 x 64 tiles
+  int narrow;           // 16-bit: 128 x 128 tiles, two workgroups per CU (1) or one with deeper stages (2);
+                        // fp32: 64 x 64 tiles (1)
 };
 
 // ---- second launch: apply GEMM-2 and/or the gradient contractions ---------

@@ -200,6 +200,11 @@ LACT_KIND(KGrad2N16, 1, 1, 1, 3u, 2, 4, 2, 2, 4, true, 32, 0 * p, 0 * p);
 // the other workgroup's loop overlaps.
 LACT_KIND(KApplyN16, 2, 1, 2, 0u, 2, 2, 2, 2, 3, true, 32, p, 0 * p);
 LACT_KIND(KDualN16, 1, 1, 1, 1u, 2, 2, 2, 2, 3, true, 32, 0 * p, 0 * p);
+// The same tiles for launches of at most one per CU (fwd_shape in
+// lact_api.hip): nobody shares the CU, so three 64-K stages take its LDS and
+// twice as much is in flight.
+LACT_KIND(KApplyD16, 2, 1, 2, 0u, 2, 2, 2, 2, 3, true, 64, p, 0 * p);
+LACT_KIND(KDualD16, 1, 1, 1, 1u, 2, 2, 2, 2, 3, true, 64, 0 * p, 0 * p);
 // fp32 shapes: 4 waves of 64 x 64 (128 x 128 tiles), register path; the key
 // forward and its hidden backward share one loop (A = W1, W3, W2; B = K, V).
 LACT_KIND(KApply32, 2, 1, 2, 0u, 2, 2, 2, 2, 2, false, 32, p, 0 * p);
@@ -268,24 +273,31 @@ template <> struct Kinds<float> {
   using Grad2 = KGrad2_32;
 };
 
-// Kinds of the first launch: apply, key forward and its hidden backward.
-template <typename T, bool NARROW>
+// Kinds of the first launch: apply, key forward and its hidden backward
+// (shape: FwdArgs::narrow).
+template <typename T, int SHAPE>
 struct FwdKinds {
   using Apply = typename Kinds<T>::Apply;
   using Update = typename Kinds<T>::Update;
   using Dual = KDual16;
 };
 template <>
-struct FwdKinds<float, true> {
+struct FwdKinds<float, 1> {
   using Apply = KApplyS32;
   using Update = KUpdateS32;
   using Dual = KDual16;   // unused
 };
 template <>
-struct FwdKinds<__bf16, true> {
+struct FwdKinds<__bf16, 1> {
   using Apply = KApplyN16;
   using Update = KApplyN16;
   using Dual = KDualN16;
+};
+template <>
+struct FwdKinds<__bf16, 2> {
+  using Apply = KApplyD16;
+  using Update = KApplyD16;
+  using Dual = KDualD16;
 };
 
 // Kinds of the second launch: the narrow shapes for 16-bit I/O with d <= 128.
@@ -1325,9 +1337,9 @@ __device__ __forceinline__ void update_epilogue_staged(const f32x16_t (&z1a)[K::
 // j, columns = tokens i): every lane holds four consecutive hidden units of
 // one token per register group, written as one packed store into the
 // token-major [tokens x h] output.
-template <typename T, bool NARROW>
+template <typename T, int SHAPE>
 constexpr int fwd_smem() {
-  using FK = FwdKinds<T, NARROW>;
+  using FK = FwdKinds<T, SHAPE>;
   using KU = typename FK::Update;
   return cmax(smem_bytes<T, typename FK::Apply>(),
               cmax(smem_bytes<T, KU>(), sizeof(T) == 2 ? cmax(smem_bytes<T, typename FK::Dual>(),
@@ -1335,12 +1347,12 @@ constexpr int fwd_smem() {
                                                        : 0));
 }
 
-template <typename T, bool NARROW, bool KEEP = false>
+template <typename T, int SHAPE, bool KEEP = false>
 __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
-  using KA = typename FwdKinds<T, NARROW>::Apply;
-  using KU = typename FwdKinds<T, NARROW>::Update;
+  using KA = typename FwdKinds<T, SHAPE>::Apply;
+  using KU = typename FwdKinds<T, SHAPE>::Update;
   static_assert(KA::THREADS == KU::THREADS, "one block size per launch");
-  constexpr int kSmem = fwd_smem<T, NARROW>();
+  constexpr int kSmem = fwd_smem<T, SHAPE>();
   constexpr int esz = sizeof(T);
   int bid = blockIdx.x;
   const bool first = bid < args.seg[0].nblocks;
@@ -1413,7 +1425,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
     if constexpr (sizeof(T) == 2) {
       // Z1^T, Z3^T first, then D^T with the Z accumulators held: one
       // accumulator set per loop keeps the loops free of register spills.
-      using KD = typename FwdKinds<T, NARROW>::Dual;
+      using KD = typename FwdKinds<T, SHAPE>::Dual;
       static_assert(KD::ROWS_A == KU::ROWS_A && KD::ROWS_B == KU::ROWS_B && KD::WM == KU::WM &&
                         KD::MI == KU::MI && KD::NI == KU::NI, "accumulator layouts match");
       Acc<KU> az;
@@ -1436,25 +1448,35 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
 
 template <typename T>
 __global__ __launch_bounds__(Kinds<T>::Apply::THREADS) void k_fwd(const FwdArgs args) {
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<T, false>()];
-  fwd_body<T, false>(args, smem);
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<T, 0>()];
+  fwd_body<T, 0>(args, smem);
 }
 
 // d <= 128, 16-bit: two workgroups per CU (at most 256 VGPRs per wave).
 __global__ __launch_bounds__(KApplyN16::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_fwd_narrow(
     const FwdArgs args) {
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, true>()];
-  fwd_body<__bf16, true>(args, smem);
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, 1>()];
+  fwd_body<__bf16, 1>(args, smem);
+}
+
+// 16-bit launches of at most a tile per CU.
+__global__ __launch_bounds__(KApplyD16::THREADS) void k_fwd_deep(const FwdArgs args) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, 2>()];
+  fwd_body<__bf16, 2>(args, smem);
+}
+__global__ __launch_bounds__(KApplyD16::THREADS) void k_fwd_deep_keep(const FwdArgs args) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, 2>()];
+  fwd_body<__bf16, 2, true>(args, smem);
 }
 
 // fp32, small calls: 64 x 64 tiles.
 __global__ __launch_bounds__(KApplyS32::THREADS) void k_fwd_small(const FwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<float, true>()];
-  fwd_body<float, true>(args, smem);
+  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<float, 1>()];
+  fwd_body<float, 1>(args, smem);
 }
 __global__ __launch_bounds__(KApplyS32::THREADS) void k_fwd_small_keep(const FwdArgs args) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<float, true>()];
-  fwd_body<float, true, true>(args, smem);
+  __shared__ __attribute__((aligned(16))) uint8_t smem[fwd_smem<float, 1>()];
+  fwd_body<float, 1, true>(args, smem);
 }
 
 // The same two kernels with the key forward's Z1, Z3 and D written out too
@@ -1462,14 +1484,14 @@ __global__ __launch_bounds__(KApplyS32::THREADS) void k_fwd_small_keep(const Fwd
 // them instead of computing the three products again.
 template <typename T>
 __global__ __launch_bounds__(Kinds<T>::Apply::THREADS) void k_fwd_keep(const FwdArgs args) {
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<T, false>()];
-  fwd_body<T, false, true>(args, smem);
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<T, 0>()];
+  fwd_body<T, 0, true>(args, smem);
 }
 
 __global__ __launch_bounds__(KApplyN16::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_fwd_narrow_keep(
     const FwdArgs args) {
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, true>()];
-  fwd_body<__bf16, true, true>(args, smem);
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[fwd_smem<__bf16, 1>()];
+  fwd_body<__bf16, 1, true>(args, smem);
 }
 
 // The weight update of a GRAD_UPD tile from its accumulators P (= -g):
@@ -3546,13 +3568,15 @@ hipError_t launch_fwd(const FwdArgs& a, bool io_bf16, hipStream_t s) {
   bool keep = false;
   for (int i = 0; i < a.nseg; ++i) keep = keep || (a.seg[i].kind == FWD_UPDATE && a.seg[i].keep[0]);
   if (keep) {
-    if (io_bf16 && a.narrow) k_fwd_narrow_keep<<<a.total_blocks, KApplyN16::THREADS, 0, s>>>(a);
+    if (io_bf16 && a.narrow == 2) k_fwd_deep_keep<<<a.total_blocks, KApplyD16::THREADS, 0, s>>>(a);
+    else if (io_bf16 && a.narrow) k_fwd_narrow_keep<<<a.total_blocks, KApplyN16::THREADS, 0, s>>>(a);
     else if (io_bf16) k_fwd_keep<__bf16><<<a.total_blocks, KApply16::THREADS, 0, s>>>(a);
     else if (a.narrow) k_fwd_small_keep<<<a.total_blocks, KApplyS32::THREADS, 0, s>>>(a);
     else k_fwd_keep<float><<<a.total_blocks, KApply32::THREADS, 0, s>>>(a);
     return hipGetLastError();
   }
-  if (io_bf16 && a.narrow) k_fwd_narrow<<<a.total_blocks, KApplyN16::THREADS, 0, s>>>(a);
+  if (io_bf16 && a.narrow == 2) k_fwd_deep<<<a.total_blocks, KApplyD16::THREADS, 0, s>>>(a);
+  else if (io_bf16 && a.narrow) k_fwd_narrow<<<a.total_blocks, KApplyN16::THREADS, 0, s>>>(a);
   else if (io_bf16) k_fwd<__bf16><<<a.total_blocks, KApply16::THREADS, 0, s>>>(a);
   else if (a.narrow) k_fwd_small<<<a.total_blocks, KApplyS32::THREADS, 0, s>>>(a);
   else k_fwd<float><<<a.total_blocks, KApply32::THREADS, 0, s>>>(a);

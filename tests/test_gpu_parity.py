@@ -138,7 +138,7 @@ def test_bf16_split_stage_loop_edges(heads, d, h, chunk):
     # whose second one is partly or wholly past the matrix; 13 and 17 heads
     # of 256 < d, h <= 512 take the gradient-and-update kind. The first launch
     # takes wide tiles where both segments' are more than 128 (34 x 4, 14 x 20,
-    # 17 x 8 and 13 x 12 tiles), narrow ones of 32-K stages else
+    # 17 x 8 and 13 x 12 tiles), narrow ones in three 64-K stages else
     cfg = CONFIGS["lm32k"].with_(name="split", B=1, H=heads, d=d, h=h, n_kv=2 * chunk + 7, n_q=2 * chunk + 40,
                                  chunk=chunk)
     x = make_inputs(cfg, 11)
