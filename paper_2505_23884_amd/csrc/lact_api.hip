@@ -1123,9 +1123,10 @@ int run_schedule(const lact_desc* desc, const lact_segment* segs, int64_t nseg, 
 //   dB = dX' X^T,  S = dB + dB^T,  M = b S + c (S A + (S A)^T)  (= dA + dA^T),
 //   dX = a dX' + B dX' + M X,
 // and through the scaling X_0 = G / (||G|| + eps); fp32 iterates. With bf16
-// I/O the operand copies are fp16 and each product takes its combination in
-// its epilogue (S and M as P Q^T + Q P^T: A, S symmetric): three launches per
-// step and direction. With fp32 I/O they are fp32: the k_bwd kinds (OUT for
+// I/O the operand copies are fp16; slots up to 128 x 256 take the whole replay
+// and the whole reverse in one workgroup each (k_ns_replay, k_ns_reverse),
+// larger ones three launches per step and direction, each product with its
+// combination in its epilogue (S and M as P Q^T + Q P^T: A, S symmetric). With fp32 I/O they are fp32: the k_bwd kinds (OUT for
 // sums along rows, GRAD2 for sums down columns) and elementwise launches.
 struct NsBwdLayout {
   int S, m, n;
@@ -1378,6 +1379,30 @@ struct NsBwd {
     a.n = N.n;
     return timed(LACT_KCLASS_NS, (a.two ? 4.0 : 2.0) * N.S * mm() * N.n, s, [&] { return launch_ns_dx(a, s); });
   }
+  // Slots that one workgroup holds whole (the forward's rule): the iteration,
+  // and its reverse, in a launch each.
+  bool small() const { return !f32() && N.m <= kNsFusedM && N.n <= kNsFusedN; }
+  NsSmallArgs small_args() const {
+    NsSmallArgs a{};
+    a.g = at<float>(N.g);
+    a.x32 = at<float>(N.x32);
+    a.nrm = at<float>(N.nrm);
+    a.X = reinterpret_cast<_Float16*>(Xo(0));
+    a.A = reinterpret_cast<_Float16*>(Ao(0));
+    a.B = reinterpret_cast<_Float16*>(Bo(0));
+    a.S = N.S;
+    a.m = N.m;
+    a.n = N.n;
+    a.steps = steps;
+    a.ca = (float)kNsA;
+    a.cb = (float)kNsB;
+    a.cc = (float)kNsC;
+    a.eps = (float)kNsEps;
+    return a;
+  }
+  double small_flops(double per) const {
+    return per * steps * N.S * (2.0 * mm() * N.n + 2.0 * mm() * N.m + 2.0 * mm() * N.n);
+  }
   float* pst() const { return at<float>(N.pstep) + (size_t)(ci % N.iters) * N.S * mn(); }   // the step, negated
   bool kept() const { return N.iters > 1; }
 
@@ -1398,6 +1423,11 @@ struct NsBwd {
     float* G = at<float>(N.g);
     float* X = at<float>(N.x32);
     int rc = slabs ? gather_slabs(slabs, 1.0f, G) : gather(P, nsplit, split, -1.0f, G);
+    if (small()) {
+      if (!rc) rc = timed(LACT_KCLASS_NS, small_flops(1.0), s, [&] { return launch_ns_replay(small_args(), s); });
+      if (!rc) rc = scatter(X, -1.0f, pst());
+      return rc;
+    }
     if (!rc) rc = timed(LACT_KCLASS_NS, 0.0, s, [&] { return launch_slot_dot(G, G, N.S, mn(), at<float>(N.nrm), at<float>(N.dotp), s); });
     if (!rc) rc = lin(0, G, nullptr, nullptr, nullptr, at<float>(N.nrm), nullptr, 0.f, X, steps > 0 ? Xo(0) : nullptr);
     for (int k = 0; k < steps && !rc; ++k) {
@@ -1427,6 +1457,11 @@ struct NsBwd {
     float* X = at<float>(N.x32);
     uint8_t* T = buf(N.to);
     int rc = gather(at<float>(N.ustep), 1, 0, -1.0f, X);   // d step = -dU
+    if (small()) {
+      if (!rc) rc = timed(LACT_KCLASS_NS, small_flops(2.0), s, [&] { return launch_ns_reverse(small_args(), s); });
+      if (!rc) rc = scatter(X, -1.0f, at<float>(N.ug));
+      return rc;
+    }
     if (!rc) rc = lin(1, X, nullptr, nullptr, nullptr, nullptr, nullptr, 1.0f, nullptr, T);
     uint8_t* T2 = buf(N.p1);   // the other copy of dX' (fp16: p1 holds no partials)
     for (int k = steps - 1; k >= 0 && !rc; --k) {

@@ -428,6 +428,21 @@ struct NsDxArgs {
   int nblocks;   // set by the launcher
 };
 hipError_t launch_ns_dx(NsDxArgs a, hipStream_t s);
+// The same iteration of small matrices whole, one workgroup per wide slot
+// (m <= kNsFusedM, n <= kNsFusedN): replay keeps every step's fp16 X_k, A_k
+// and B_k (steps S mn or S mm elements apart) and ||G||^2, and writes X; the
+// reverse takes dX (x32) back through the kept steps and the scaling
+// X_0 = G / (||G|| + eps), in place.
+struct NsSmallArgs {
+  const float* g;       // G, [S][m x n]
+  float* x32;           // replay: out; reverse: in and out
+  float* nrm;           // [S] ||G||^2 (replay: out)
+  _Float16 *X, *A, *B;  // the first step's; step k further on as above
+  int S, m, n, steps;
+  float ca, cb, cc, eps;
+};
+hipError_t launch_ns_replay(const NsSmallArgs& a, hipStream_t s);
+hipError_t launch_ns_reverse(const NsSmallArgs& a, hipStream_t s);
 // out = alpha X + beta (Y + Y^T) per slot of fp32 [m x m] matrices (X may be
 // nullptr; fp32 I/O).
 hipError_t launch_sym32(const float* X, float alpha, const float* Y, float beta, float* out, int S, int m,

@@ -2479,8 +2479,12 @@ __device__ __forceinline__ void fs_put4(uint8_t* base, int row, int col, int pit
 // orientations.
 constexpr int kNsFusedX = kNsFusedM * kNsFusedN * 2, kNsFusedA = kNsFusedM * kNsFusedM * 2;
 
-template <bool TALL>
-__device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8_t* smem) {
+// With `keep` (the backward's replay, wide slots): every step's fp16 X, A and B
+// go to memory too, ||G||^2 is left in keep->nrm, and the result X is written
+// to keep->x32 in place of the weight update.
+template <bool TALL, bool KEEP = false>
+__device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8_t* smem,
+                                              const NsSmallArgs* keep = nullptr) {
   uint8_t *const xs = smem, *const as_ = smem + kNsFusedX, *const bs = as_ + kNsFusedA;
   constexpr int M = kNsFusedM, N = kNsFusedN;
   constexpr int SR = TALL ? N : M, SC = TALL ? M : N;   // padded stored orientation
@@ -2568,6 +2572,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
 #pragma unroll
     for (int i = 0; i < 8; ++i) t += red[i];
     const float inv = 1.0f / (sqrtf(t) + a.eps);
+    if (KEEP && tid == 0) keep->nrm[slot] = t;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -2593,6 +2598,19 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int half = ln >> 5;
+    // copy a swizzled LDS matrix of `pitch`-byte rows to rows of `nc` elements
+    auto copy_out = [&](const uint8_t* src, int pitch, _Float16* dst, int nr, int nc) {
+      const int cpr = pitch / 16;
+      for (int f = (w << 6) + ln; f < M * cpr; f += 512) {
+        const int row = f / cpr, c = f % cpr;
+        if (row < nr && c * 8 < nc)
+          *reinterpret_cast<u32x4_t*>(dst + (int64_t)row * nc + c * 8) =
+              *reinterpret_cast<const u32x4_t*>(src + fs_off(row, c, pitch));
+      }
+    };
+    const int64_t kx = ((int64_t)step * (KEEP ? keep->S : 0) + slot) * sr * sc;
+    const int64_t km = ((int64_t)step * (KEEP ? keep->S : 0) + slot) * sr * sr;
+    if constexpr (KEEP) copy_out(xs, PX, keep->X + kx, sr, sc);
     // ---- A = X X^T (K = N) ----
     f32x16_t a32[2];
 #pragma unroll
@@ -2630,6 +2648,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
         fs_put4(as_, c1 + (ln & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, a32[mi][4 * g], a32[mi][4 * g + 1],
                 a32[mi][4 * g + 2], a32[mi][4 * g + 3]);
     lds_barrier();
+    if constexpr (KEEP) copy_out(as_, PA, keep->A + km, sr, sr);
     // ---- B = b A + c A A (K = M) ----
     f32x16_t t[2];
 #pragma unroll
@@ -2656,6 +2675,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
         fs_put4(bs, c1 + (ln & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, v[0], v[1], v[2], v[3]);
       }
     lds_barrier();
+    if constexpr (KEEP) copy_out(bs, PA, keep->B + km, sr, sr);
     // ---- X <- a X + B X (K = M), tile rows = stored columns ----
     f32x16_t u[2][2];
 #pragma unroll
@@ -2711,14 +2731,6 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
     lds_barrier();
   }
   {
-    // The weight update of this matrix with X as the step (§3.2 weight
-    // normalisation; Muon's update, App. A): X through LDS as the gradient
-    // came, so that 64 (32 for rows of 128) lanes stream a row of W in 16-byte
-    // vectors and sum its squares by shuffles
-    const int j = a.slot_off[q % a.group];
-    const int64_t woff = (int64_t)(q / a.group) * a.ystride;
-    float* Wj = a.W[j] + woff;
-    __bf16* Wbj = reinterpret_cast<__bf16*>(a.Wb[j]) + woff;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -2727,6 +2739,24 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
         for (int g = 0; g < 4; ++g)
           *f32_at(c3 + ni * 32 + (lane & 31), (r3 + mi * 32 + 8 * g + 4 * half) >> 2) =
               make_float4(x32[mi][ni][4 * g], x32[mi][ni][4 * g + 1], x32[mi][ni][4 * g + 2], x32[mi][ni][4 * g + 3]);
+    if constexpr (KEEP) {
+      __syncthreads();
+      float* out = keep->x32 + slot * sr * sc;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
+        if (row < sr && c < sc) *reinterpret_cast<float4*>(out + (int64_t)row * sc + c) = *f32_at(row, f % C4);
+      }
+      return;
+    }
+    // The weight update of this matrix with X as the step (§3.2 weight
+    // normalisation; Muon's update, App. A): X through LDS as the gradient
+    // came, so that 64 (32 for rows of 128) lanes stream a row of W in 16-byte
+    // vectors and sum its squares by shuffles
+    const int j = a.slot_off[q % a.group];
+    const int64_t woff = (int64_t)(q / a.group) * a.ystride;
+    float* Wj = a.W[j] + woff;
+    __bf16* Wbj = reinterpret_cast<__bf16*>(a.Wb[j]) + woff;
     typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
     const int c4 = lane % C4, row0 = w * (64 / C4) + lane / C4;   // C4 lanes a row
     const bool cok = c4 * 4 < sc;
@@ -2773,6 +2803,273 @@ template <bool TALL>
 __global__ __launch_bounds__(512) void k_ns_fused(const NsFusedArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kNsFusedX + 2 * kNsFusedA];
   ns_fused_body<TALL>(a, blockIdx.x, smem);
+}
+
+__global__ __launch_bounds__(512) void k_ns_replay(const NsSmallArgs k) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kNsFusedX + 2 * kNsFusedA];
+  NsFusedArgs a{};
+  a.src = k.g;
+  a.nsplit = 1;
+  a.eps = k.eps;
+  a.spi = 1;
+  a.ystride = (int64_t)k.m * k.n;
+  a.group = 1;
+  a.rows = k.m;
+  a.cols = k.n;
+  a.steps = k.steps;
+  a.ca = k.ca;
+  a.cb = k.cb;
+  a.cc = k.cc;
+  ns_fused_body<false, true>(a, blockIdx.x, smem, &k);
+}
+
+// Reverse of the iteration of one small wide slot [m x n] (see NsBwd in
+// lact_api.hip for the algebra). T = dX' and X_k stay in LDS as fp16 (128 x 256
+// each), S and M take the last 32 KiB in turn, A_k and B_k are read as
+// fragments straight from memory (L2), and dX' stays in fp32 registers. The
+// three products per step took three launches of 10 to 13 us over 120 slots of
+// 128 x 256; a chunk's five steps take 107 us here against 171 us, the replay
+// 62 us (k_ns_replay) against 171 us. One workgroup per slot leaves half the
+// CUs idle: what bounds both is the chain of products inside a slot.
+__global__ __launch_bounds__(512) void k_ns_reverse(const NsSmallArgs a) {
+  constexpr int M = kNsFusedM, N = kNsFusedN, PX = N * 2, PA = M * 2, C4 = N / 4;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kNsFusedX + kNsFusedA];
+  uint8_t *const ts = smem, *const xs = smem + kNsFusedX, *const ss = smem + 2 * kNsFusedX;
+  const uint32_t tb = lds_addr(ts), xb = lds_addr(xs), sb = lds_addr(ss);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int64_t slot = blockIdx.x;
+  const int m = a.m, n = a.n;
+  const int64_t mn = (int64_t)m * n, mm = (int64_t)m * m;
+  const int r3 = (w >> 1) * 64, c3 = (w & 1) * 64;   // update products: tile rows = columns of the slot
+  const int r1 = (w >> 2) * 64, c1 = (w & 3) * 32;   // symmetric products
+  auto f32_at = [&](int row, int c4) {   // the fp32 matrix over T and X
+    return reinterpret_cast<float4*>(smem + row * (N * 4) + ((c4 ^ (row & 31)) << 4));
+  };
+  auto load32 = [&](const float* src) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
+      *f32_at(row, f % C4) = row < m && c < n ? *reinterpret_cast<const float4*>(src + (int64_t)row * n + c)
+                                              : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  f32x16_t t32[2][2];
+  load32(a.x32 + slot * mn);
+  __syncthreads();
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = *f32_at(c3 + ni * 32 + (lane & 31), (r3 + mi * 32 + 8 * g + 4 * (lane >> 5)) >> 2);
+        t32[mi][ni][4 * g] = v.x;
+        t32[mi][ni][4 * g + 1] = v.y;
+        t32[mi][ni][4 * g + 2] = v.z;
+        t32[mi][ni][4 * g + 3] = v.w;
+      }
+  __syncthreads();
+  for (int k = a.steps - 1; k >= 0; --k) {
+    int ln = lane;   // the LDS addresses are formed per step (see ns_fused_body)
+    asm volatile("" : "+v"(ln));
+    const int l31 = ln & 31, half = ln >> 5;
+    const _Float16* Xk = a.X + ((int64_t)k * a.S + slot) * mn;
+    const _Float16* Ak = a.A + ((int64_t)k * a.S + slot) * mm;
+    const _Float16* Bk = a.B + ((int64_t)k * a.S + slot) * mm;
+    // fragment of a row-major [m x m] matrix in memory: 8 elements of a row
+    auto gfrag = [&](const _Float16* p, int row, int s) {
+      const int c = (2 * s + half) * 8;
+      u32x4_t v = {0u, 0u, 0u, 0u};
+      if (row < m && c < m) v = *reinterpret_cast<const u32x4_t*>(p + (int64_t)row * m + c);
+      return v;
+    };
+    // T (fp16 of dX') and X_k
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          fs_put4(ts, c3 + ni * 32 + l31, r3 + mi * 32 + 8 * g + 4 * half, PX, t32[mi][ni][4 * g],
+                  t32[mi][ni][4 * g + 1], t32[mi][ni][4 * g + 2], t32[mi][ni][4 * g + 3]);
+#pragma unroll
+    for (int i = 0; i < M * (PX / 16) / 512; ++i) {
+      const int f = i * 512 + (w << 6) + ln, row = f / (PX / 16), c = f % (PX / 16);
+      u32x4_t v = {0u, 0u, 0u, 0u};
+      if (row < m && c * 8 < n) v = *reinterpret_cast<const u32x4_t*>(Xk + (int64_t)row * n + c * 8);
+      *reinterpret_cast<u32x4_t*>(xs + fs_off(row, c, PX)) = v;
+    }
+    __syncthreads();
+    // ---- S = T X^T + X T^T ----
+    f32x16_t sa[2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sa[mi][e] = 0.f;
+    {
+      const uint32_t tr = fs_addr_k(tb, r1 + l31, ln, PX), tc = fs_addr_k(tb, c1 + l31, ln, PX);
+      const uint32_t xr = fs_addr_k(xb, r1 + l31, ln, PX), xc = fs_addr_k(xb, c1 + l31, ln, PX);
+      fs_loop<N / 16, 6, 4, 2>(
+          [&](int s, u32x4_t (&fa)[4], u32x4_t (&fb)[2]) {
+            fa[0] = fs_frag_k(tr, s);
+            fa[1] = fs_frag_k(tr + 32 * PX, s);
+            fa[2] = fs_frag_k(xr, s);
+            fa[3] = fs_frag_k(xr + 32 * PX, s);
+            fb[0] = fs_frag_k(xc, s);
+            fb[1] = fs_frag_k(tc, s);
+          },
+          [&](const u32x4_t (&fa)[4], const u32x4_t (&fb)[2]) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+              for (int mi = 0; mi < 2; ++mi) sa[mi] = mfma16(fa[2 * p + mi], fb[p], sa[mi]);
+          });
+    }
+    // symmetric: the lane's rows at column j go to row j
+    auto put_sym = [&](const f32x16_t (&v)[2]) {
+#pragma unroll
+      for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          fs_put4(ss, c1 + l31, r1 + mi * 32 + 8 * g + 4 * half, PA, v[mi][4 * g], v[mi][4 * g + 1], v[mi][4 * g + 2],
+                  v[mi][4 * g + 3]);
+    };
+    put_sym(sa);
+    lds_barrier();
+    // ---- M = b S + c (S A + A S) ----
+    f32x16_t q[2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) q[mi][e] = 0.f;
+    {
+      const uint32_t sr = fs_addr_k(sb, r1 + l31, ln, PA), sc = fs_addr_k(sb, c1 + l31, ln, PA);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {   // A's fragments of four substeps at a time
+        u32x4_t g[4][3];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          g[s][0] = gfrag(Ak, r1 + l31, 4 * h + s);
+          g[s][1] = gfrag(Ak, r1 + 32 + l31, 4 * h + s);
+          g[s][2] = gfrag(Ak, c1 + l31, 4 * h + s);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          u32x4_t fa[2] = {fs_frag_k(sr, 4 * h + s), fs_frag_k(sr + 32 * PA, 4 * h + s)};
+          u32x4_t fb[1] = {fs_frag_k(sc, 4 * h + s)};
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[0]), "+v"(fa[1]), "+v"(fb[0]));
+#pragma unroll
+          for (int mi = 0; mi < 2; ++mi) {
+            q[mi] = mfma16(fa[mi], g[s][2], q[mi]);
+            q[mi] = mfma16(g[s][mi], fb[0], q[mi]);
+          }
+        }
+      }
+    }
+    lds_barrier();   // every wave is done reading S
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) q[mi][e] = a.cb * sa[mi][e] + a.cc * q[mi][e];
+    put_sym(q);
+    lds_barrier();
+    // ---- dX = a dX' + B T + M X ----
+    f32x16_t u[2][2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) u[mi][ni][e] = 0.f;
+    auto mul4 = [&](const u32x4_t (&fa)[2], const u32x4_t (&fb)[2]) {
+#pragma unroll
+      for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) u[mi][ni] = mfma16(fa[mi], fb[ni], u[mi][ni]);
+    };
+    {
+      const FsTr rx = fs_addr_tr(xb, r3, ln, PX);
+      const uint32_t cm = fs_addr_k(sb, c3 + l31, ln, PA);
+      fs_loop<M / 16, 6, 2, 2>(
+          [&](int s, u32x4_t (&fa)[2], u32x4_t (&fb)[2]) {
+            fa[0] = fs_frag_tr(rx, 0, s, PX);
+            fa[1] = fs_frag_tr(rx, 1, s, PX);
+            fb[0] = fs_frag_k(cm, s);
+            fb[1] = fs_frag_k(cm + 32 * PA, s);
+          },
+          mul4);
+      const FsTr rt = fs_addr_tr(tb, r3, ln, PX);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        u32x4_t g[4][2];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          g[s][0] = gfrag(Bk, c3 + l31, 4 * h + s);
+          g[s][1] = gfrag(Bk, c3 + 32 + l31, 4 * h + s);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          u32x4_t fa[2] = {fs_frag_tr(rt, 0, 4 * h + s, PX), fs_frag_tr(rt, 1, 4 * h + s, PX)};
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa[0]), "+v"(fa[1]));
+          mul4(fa, g[s]);
+        }
+      }
+    }
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) t32[mi][ni][e] = a.ca * t32[mi][ni][e] + u[mi][ni][e];
+    __syncthreads();   // every wave is done with T, X and M
+  }
+  // through X_0 = G / (||G|| + eps): dG = dX_0 / se - <dX_0, G> G / (se^2 ||G||)
+  load32(a.g + slot * mn);
+  __syncthreads();
+  f32x16_t g32[2][2];
+  float dot = 0.f;
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = *f32_at(c3 + ni * 32 + (lane & 31), (r3 + mi * 32 + 8 * g + 4 * (lane >> 5)) >> 2);
+        const float e4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          g32[mi][ni][4 * g + e] = e4[e];
+          dot = fmaf(e4[e], t32[mi][ni][4 * g + e], dot);
+        }
+      }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
+  float* red = reinterpret_cast<float*>(ss);
+  if (lane == 0) red[w] = dot;
+  __syncthreads();
+  dot = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) dot += red[i];
+  const float nrm = sqrtf(a.nrm[slot]), se = nrm + a.eps, f = 1.0f / se, gf = dot / (se * se * nrm);
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = t32[mi][ni][4 * g + e] * f - gf * g32[mi][ni][4 * g + e];
+        *f32_at(c3 + ni * 32 + (lane & 31), (r3 + mi * 32 + 8 * g + 4 * (lane >> 5)) >> 2) =
+            make_float4(o[0], o[1], o[2], o[3]);
+      }
+  __syncthreads();
+  float* out = a.x32 + slot * mn;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int ff = i * 512 + tid, row = ff / C4, c = (ff % C4) * 4;
+    if (row < m && c < n) *reinterpret_cast<float4*>(out + (int64_t)row * n + c) = *f32_at(row, ff % C4);
+  }
 }
 
 // Both matrix groups of an instance set in one launch (W1 and W3, then W2, in
@@ -3726,6 +4023,19 @@ hipError_t launch_mom_adv(const float* M, const float* bbar, int64_t bbar_inst, 
   if (need <= 0) return hipSuccess;
   const int64_t blocks = need < 8192 ? need : 8192;
   k_mom_adv<<<(unsigned)blocks, 256, 0, s>>>(M, bbar, bbar_inst, P, Mout, BH, dh);
+  return hipGetLastError();
+}
+
+hipError_t launch_ns_replay(const NsSmallArgs& a, hipStream_t s) {
+  if (a.S <= 0) return hipSuccess;
+  if (a.m > kNsFusedM || a.n > kNsFusedN || a.m > a.n) return hipErrorInvalidValue;
+  k_ns_replay<<<a.S, 512, 0, s>>>(a);
+  return hipGetLastError();
+}
+hipError_t launch_ns_reverse(const NsSmallArgs& a, hipStream_t s) {
+  if (a.S <= 0) return hipSuccess;
+  if (a.m > kNsFusedM || a.n > kNsFusedN || a.m > a.n) return hipErrorInvalidValue;
+  k_ns_reverse<<<a.S, 512, 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -1782,12 +1782,14 @@ def test_swiglu_muon_backward_small_matrices(order):
     check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
 
 
-@pytest.mark.parametrize("d,h", [(32, 64), (96, 160), (160, 96), (160, 288), (288, 256)])
+@pytest.mark.parametrize("d,h", [(32, 64), (96, 160), (256, 128), (96, 288), (160, 96), (160, 288), (288, 256)])
 def test_swiglu_muon_backward_product_tiles(d, h):
-    # the Newton-Schulz products of the backward at the edges of their tiles:
-    # one partial 128 x 128 tile, a second one of a few rows (160 = 128 + 32,
-    # the symmetric products' mirrored tiles), 256 x 256 step tiles that the
-    # slot does not fill, either orientation; one whole-rank update
+    # the Newton-Schulz replay and reverse of the backward: slots that one
+    # workgroup holds whole (up to 128 x 256, partly filled and full), and the
+    # products at the edges of their tiles: one partial 128 x 128 tile (96 x
+    # 288), a second one of a few rows (160 = 128 + 32, the symmetric products'
+    # mirrored tiles), 256 x 256 step tiles that the slot does not fill, either
+    # orientation; one whole-rank update
     C = 4 * max(d, h)
     cfg = CONFIGS["lm32k_muon"].with_(name="muon_bwd_tiles", B=1, H=2, d=d, h=h, n_kv=C, n_q=C + 50, chunk=C, order=1)
     x, ct = make_inputs(cfg, 86), make_cotangents(cfg, 86)
