@@ -224,9 +224,9 @@ LACT_KIND(KGrad2_S32, 1, 1, 1, 3u, 2, 2, 1, 1, 2, false, 32, 0 * p, 0 * p);
 // or the first row-contiguous (TY: Y read down its columns). fp16 operands:
 // 8 waves of 128 x 64 (256 x 256 tiles) for large Gram matrices, 4 waves of
 // 64 x 64 (128 x 128) for small ones; fp32: 4 waves of 64 x 64.
-LACT_KIND(KNsK16B, 1, 1, 1, 0u, 2, 4, 4, 2, 2, true, 64, 0 * p, 0 * p);
-LACT_KIND(KNsMN16B, 1, 1, 1, 3u, 2, 4, 4, 2, 2, true, 64, 0 * p, 0 * p);
-LACT_KIND(KNsTY16B, 1, 1, 1, 1u, 2, 4, 4, 2, 2, true, 64, 0 * p, 0 * p);
+LACT_SPLIT_KIND(KNsK16B, 0u, 1);
+LACT_SPLIT_KIND(KNsMN16B, 7u, 1);
+LACT_SPLIT_KIND(KNsTY16B, 3u, 1);
 LACT_KIND(KNsK16S, 1, 1, 1, 0u, 2, 2, 2, 2, 2, true, 64, 0 * p, 0 * p);
 LACT_KIND(KNsMN16S, 1, 1, 1, 3u, 2, 2, 2, 2, 2, true, 64, 0 * p, 0 * p);
 LACT_KIND(KNsTY16S, 1, 1, 1, 1u, 2, 2, 2, 2, 2, true, 64, 0 * p, 0 * p);
@@ -1083,6 +1083,25 @@ __device__ __forceinline__ void mainloop(uint8_t* smem, const View (&ops)[K::NOP
   if constexpr (K::SPLIT != 0) mainloop_split<T, K>(smem, ops, nk, acc);
   else if constexpr (sizeof(T) == 2) mainloop_dma<T, K>(smem, ops, nk, acc);
   else mainloop_regs<K>(smem, ops, nk, acc);
+}
+
+// Output rows of a tile whose split operands are two blocks of one matrix's
+// rows, and its product from that matrix's rows (a) and the columns (b):
+// added to acc.
+template <class K>
+constexpr int tile_rows() { return K::NACC * K::ROWS_A; }
+template <typename T, class K>
+__device__ __forceinline__ void add_product(uint8_t* smem, const View& a, const View& b, int64_t nk, Acc<K>& acc) {
+  if constexpr (K::SPLIT == 1) {
+    const View a1{a.p + (K::is_mn(0) ? (int64_t)K::ROWS_A * (int)sizeof(T) : K::ROWS_A * a.ld_b), a.ld_b,
+                  a.nrows - K::ROWS_A, a.nk};
+    const View ops[3] = {a, a1, b};
+    mainloop_split<T, K>(smem, ops, nk, acc);
+  } else {
+    const View ops[2] = {a, b};
+    if constexpr (sizeof(T) == 2) mainloop_dma<T, K>(smem, ops, nk, acc);
+    else mainloop_regs<K>(smem, ops, nk, acc);
+  }
 }
 
 // Two loops on one LDS ring of NSTAGE slots of SLOT bytes: the first hands
@@ -2016,7 +2035,7 @@ __device__ __forceinline__ void ns_epilogue_staged(const Acc<KK>& acc, uint8_t* 
                                                    int64_t ld, int64_t i0, int64_t j0, int64_t mrows, int64_t ncols,
                                                    void* Abw, void* A2w, float* Y32, void* Yout, void* Bbw,
                                                    bool mirror) {
-  constexpr int R = KK::ROWS_A;                  // tile rows = stored columns
+  constexpr int R = tile_rows<KK>();             // tile rows = stored columns
   constexpr int SR = KK::WN * 32;                // staged stored rows per half
   constexpr int CPR = R / 4;                     // 16-byte chunks per staged row
   constexpr int PER = SR * CPR / KK::THREADS;    // chunks per thread per half
@@ -2030,14 +2049,16 @@ __device__ __forceinline__ void ns_epilogue_staged(const Acc<KK>& acc, uint8_t* 
     // stage: lane holds rows r..r+3 (stored columns) of tile column c (stored row)
     const int sr = wave_n<KK>() * 32 + (lane & 31);
 #pragma unroll
-    for (int mi = 0; mi < KK::MI; ++mi)
+    for (int p = 0; p < KK::NACC; ++p)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int r = acc_row<KK>(mi, 4 * g);
-        const f32x16_t& a = acc[0][mi][half];
-        *reinterpret_cast<float4*>(st + sr * R + (((r >> 2) ^ (sr & (CPR - 1))) << 2)) =
-            make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
-      }
+      for (int mi = 0; mi < KK::MI; ++mi)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int r = p * KK::ROWS_A + acc_row<KK>(mi, 4 * g);
+          const f32x16_t& a = acc[p][mi][half];
+          *reinterpret_cast<float4*>(st + sr * R + (((r >> 2) ^ (sr & (CPR - 1))) << 2)) =
+              make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+        }
     lds_barrier();
     int64_t gidx[PER];
     bool ok[PER];
@@ -2139,7 +2160,7 @@ __global__ __launch_bounds__((NsKinds<T, BIG>::K::THREADS)) void k_ns(const NsAr
   static_assert(KK::THREADS == KM::THREADS && KK::THREADS == KT::THREADS && KK::ROWS_A == KM::ROWS_A &&
                     KK::ROWS_A == KT::ROWS_A && KK::ROWS_B == KT::ROWS_B && KK::MI == KT::MI && KK::NI == KM::NI,
                 "one tile and accumulator shape per launch");
-  __shared__ __attribute__((aligned(16)))
+  __shared__ __attribute__((aligned(1024)))
   uint8_t smem[cmax(smem_bytes<T, KK>(), cmax(smem_bytes<T, KM>(), smem_bytes<T, KT>()))];
   constexpr int esz = sizeof(T);
   int bid = blockIdx.x;
@@ -2160,7 +2181,7 @@ __global__ __launch_bounds__((NsKinds<T, BIG>::K::THREADS)) void k_ns(const NsAr
     }
     tj = ti + left;
   }
-  const int64_t i0 = (int64_t)ti * KK::ROWS_A, j0 = (int64_t)tj * KK::ROWS_B;
+  const int64_t i0 = (int64_t)ti * tile_rows<KK>(), j0 = (int64_t)tj * KK::ROWS_B;
   const int64_t slot = (int64_t)(q / sg.group) * args.spi + sg.slot_off[q % sg.group];
   const int m = args.m, ldy = sg.ldy;
   const int64_t mrows = sg.M - i0, ncols = sg.N - j0;
@@ -2175,26 +2196,22 @@ __global__ __launch_bounds__((NsKinds<T, BIG>::K::THREADS)) void k_ns(const NsAr
   void* Bbw = reinterpret_cast<uint8_t*>(args.Bb) + slot * args.astride * esz;
   Acc<KK> acc;   // same accumulator shape for every NS kind
   const int kind = sg.kind;
+  zero_acc<KK>(acc);
   if (kind == NS_GRAM_K) {          // A = Y Y^T (Y wide)
-    const View ops[2] = {View{Yin + i0 * ldy * esz, (int64_t)ldy * esz, mrows, sg.K},
-                         View{Yin + j0 * ldy * esz, (int64_t)ldy * esz, ncols, sg.K}};
-    mainloop<T, KK>(smem, ops, sg.K, acc);
+    add_product<T, KK>(smem, View{Yin + i0 * ldy * esz, (int64_t)ldy * esz, mrows, sg.K},
+                       View{Yin + j0 * ldy * esz, (int64_t)ldy * esz, ncols, sg.K}, sg.K, acc);
   } else if (kind == NS_GRAM_MN) {  // A = Y^T Y (Y tall)
-    const View ops[2] = {View{Yin + i0 * esz, (int64_t)ldy * esz, mrows, sg.K},
-                         View{Yin + j0 * esz, (int64_t)ldy * esz, ncols, sg.K}};
-    mainloop<T, KM>(smem, ops, sg.K, acc);
+    add_product<T, KM>(smem, View{Yin + i0 * esz, (int64_t)ldy * esz, mrows, sg.K},
+                       View{Yin + j0 * esz, (int64_t)ldy * esz, ncols, sg.K}, sg.K, acc);
   } else if (kind == NS_POLY) {     // A (c A + b I) = b A + c A A (both symmetric: A A2^T)
-    const View ops[2] = {View{Ab + i0 * m * esz, (int64_t)m * esz, mrows, sg.K},
-                         View{A2 + j0 * m * esz, (int64_t)m * esz, ncols, sg.K}};
-    mainloop<T, KK>(smem, ops, sg.K, acc);
+    add_product<T, KK>(smem, View{Ab + i0 * m * esz, (int64_t)m * esz, mrows, sg.K},
+                       View{A2 + j0 * m * esz, (int64_t)m * esz, ncols, sg.K}, sg.K, acc);
   } else if (kind == NS_UPD_BY) {   // (B Y)^T = Y^T B (Y wide, B symmetric): rows = Y columns
-    const View ops[2] = {View{Yin + i0 * esz, (int64_t)ldy * esz, mrows, sg.K},
-                         View{Bb + j0 * m * esz, (int64_t)m * esz, ncols, sg.K}};
-    mainloop<T, KT>(smem, ops, sg.K, acc);
+    add_product<T, KT>(smem, View{Yin + i0 * esz, (int64_t)ldy * esz, mrows, sg.K},
+                       View{Bb + j0 * m * esz, (int64_t)m * esz, ncols, sg.K}, sg.K, acc);
   } else {                          // (Y B)^T = B Y^T (Y tall): rows = Y columns
-    const View ops[2] = {View{Bb + i0 * m * esz, (int64_t)m * esz, mrows, sg.K},
-                         View{Yin + j0 * ldy * esz, (int64_t)ldy * esz, ncols, sg.K}};
-    mainloop<T, KK>(smem, ops, sg.K, acc);
+    add_product<T, KK>(smem, View{Bb + i0 * m * esz, (int64_t)m * esz, mrows, sg.K},
+                       View{Yin + j0 * ldy * esz, (int64_t)ldy * esz, ncols, sg.K}, sg.K, acc);
   }
   const bool gram = kind == NS_GRAM_K || kind == NS_GRAM_MN;
   const int64_t ld = (gram || kind == NS_POLY) ? m : ldy;
@@ -2251,7 +2268,7 @@ template <class KK, bool MIRROR, class PRE, class ROW, class MIR>
 __device__ __forceinline__ void ns_rows_staged(const Acc<KK>& acc, uint8_t* smem, int64_t ld, int64_t i0, int64_t j0,
                                                int64_t mrows, int64_t ncols, bool mirror, PRE&& pre, ROW&& row,
                                                MIR&& mir) {
-  constexpr int R = KK::ROWS_A, SR = KK::WN * 32, CPR = R / 4, PER = SR * CPR / KK::THREADS;
+  constexpr int R = tile_rows<KK>(), SR = KK::WN * 32, CPR = R / 4, PER = SR * CPR / KK::THREADS;
   static_assert(KK::NI == 2 && SR * R * 4 <= KK::NSTAGE * KK::STAGE && (SR * CPR) % KK::THREADS == 0 &&
                     (CPR & (CPR - 1)) == 0, "staging shape");
   float* st = reinterpret_cast<float*>(smem);
@@ -2260,14 +2277,16 @@ __device__ __forceinline__ void ns_rows_staged(const Acc<KK>& acc, uint8_t* smem
   for (int half = 0; half < 2; ++half) {
     const int sr = wave_n<KK>() * 32 + (lane & 31);
 #pragma unroll
-    for (int mi = 0; mi < KK::MI; ++mi)
+    for (int p = 0; p < KK::NACC; ++p)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int r = acc_row<KK>(mi, 4 * g);
-        const f32x16_t& a = acc[0][mi][half];
-        *reinterpret_cast<float4*>(st + sr * R + (((r >> 2) ^ (sr & (CPR - 1))) << 2)) =
-            make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
-      }
+      for (int mi = 0; mi < KK::MI; ++mi)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int r = p * KK::ROWS_A + acc_row<KK>(mi, 4 * g);
+          const f32x16_t& a = acc[p][mi][half];
+          *reinterpret_cast<float4*>(st + sr * R + (((r >> 2) ^ (sr & (CPR - 1))) << 2)) =
+              make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+        }
     lds_barrier();
     int64_t idx[PER];
     bool ok[PER];
@@ -2308,18 +2327,21 @@ __device__ __forceinline__ void ns_rows_staged(const Acc<KK>& acc, uint8_t* smem
   }
 }
 
-// acc = A0 B0^T [+ A1 B1^T]: the second product's first tile is handed over.
+// acc = A0 B0^T [+ A1 B1^T].
 template <class KK>
 __device__ __forceinline__ void mainloop_two(uint8_t* smem, const View (&o0)[2], const View (&o1)[2], bool two,
                                              int64_t nk, Acc<KK>& acc) {
   zero_acc<KK>(acc);
-  if (!two) {
-    mainloop_dma<_Float16, KK>(smem, o0, nk, acc);
-    return;
+  if constexpr (KK::SPLIT == 0) {   // the second product's first tile is handed over
+    if (two) {
+      ChainNext<KK, KK::STAGE> nx(smem, o1);
+      mainloop_dma<_Float16, KK, KK::STAGE, ChainNext<KK, KK::STAGE>>(smem, o0, nk, acc, 0, false, &nx);
+      mainloop_dma<_Float16, KK>(smem, o1, nk, acc, nx.slot < 0 ? 0 : nx.slot, nx.slot >= 0);
+      return;
+    }
   }
-  ChainNext<KK, KK::STAGE> nx(smem, o1);
-  mainloop_dma<_Float16, KK, KK::STAGE, ChainNext<KK, KK::STAGE>>(smem, o0, nk, acc, 0, false, &nx);
-  mainloop_dma<_Float16, KK>(smem, o1, nk, acc, nx.slot < 0 ? 0 : nx.slot, nx.slot >= 0);
+  add_product<_Float16, KK>(smem, o0[0], o0[1], nk, acc);
+  if (two) add_product<_Float16, KK>(smem, o1[0], o1[1], nk, acc);
 }
 
 __global__ __launch_bounds__(KNsK16S::THREADS) void k_ns_sym(const NsSymArgs a) {
@@ -2361,11 +2383,11 @@ __global__ __launch_bounds__(KNsK16S::THREADS) void k_ns_sym(const NsSymArgs a) 
 template <bool BIG>
 __global__ __launch_bounds__((NsKinds<_Float16, BIG>::TY::THREADS)) void k_ns_dx(const NsDxArgs a) {
   using KT = typename NsKinds<_Float16, BIG>::TY;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[smem_bytes<_Float16, KT>()];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes<_Float16, KT>()];
   const int bid = xcd_remap(blockIdx.x, a.nblocks);
-  const int tm = (a.n + KT::ROWS_A - 1) / KT::ROWS_A, tn = (a.m + KT::ROWS_B - 1) / KT::ROWS_B;
+  const int tm = (a.n + tile_rows<KT>() - 1) / tile_rows<KT>(), tn = (a.m + KT::ROWS_B - 1) / KT::ROWS_B;
   const int slot = bid / (tm * tn), rr = bid - slot * (tm * tn);
-  const int64_t i0 = (int64_t)(rr / tn) * KT::ROWS_A, j0 = (int64_t)(rr % tn) * KT::ROWS_B;
+  const int64_t i0 = (int64_t)(rr / tn) * tile_rows<KT>(), j0 = (int64_t)(rr % tn) * KT::ROWS_B;
   const int64_t mrows = a.n - i0, ncols = a.m - j0, yo = (int64_t)slot * a.m * a.n, bo = (int64_t)slot * a.m * a.m;
   auto ops = [&](int k, int o) {   // tile rows: columns of Y; tile columns: rows of B (symmetric)
     return o == 0 ? View{reinterpret_cast<const uint8_t*>(a.Y[k] + yo + i0), (int64_t)a.n * 2, mrows, a.m}
@@ -3770,7 +3792,7 @@ TileShape bwd_tile(int kind, bool io_bf16, bool narrow) {
 TileShape grad_upd_tile() { return TileShape{KGradU16::ROWS_A, 2 * KGradU16::ROWS_B, KGradU16::THREADS}; }
 
 TileShape ns_tile(bool fp16, bool big) {
-  if (fp16 && big) return TileShape{KNsK16B::ROWS_A, KNsK16B::ROWS_B, KNsK16B::THREADS};
+  if (fp16 && big) return TileShape{tile_rows<KNsK16B>(), KNsK16B::ROWS_B, KNsK16B::THREADS};
   if (fp16) return TileShape{KNsK16S::ROWS_A, KNsK16S::ROWS_B, KNsK16S::THREADS};
   return TileShape{KNsK32::ROWS_A, KNsK32::ROWS_B, KNsK32::THREADS};
 }
@@ -4051,7 +4073,7 @@ hipError_t launch_ns_sym(NsSymArgs a, hipStream_t s) {
 // 256 x 256 tiles where the slots' side fills them (as the forward's update product)
 hipError_t launch_ns_dx(NsDxArgs a, hipStream_t s) {
   const bool big = a.m > 128;
-  const int64_t tr = big ? KNsTY16B::ROWS_A : KNsTY16S::ROWS_A;
+  const int64_t tr = big ? tile_rows<KNsTY16B>() : tile_rows<KNsTY16S>();
   const int64_t n = a.S * ((a.n + tr - 1) / tr) * ((a.m + tr - 1) / tr);
   if (n <= 0) return hipSuccess;
   if (n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
