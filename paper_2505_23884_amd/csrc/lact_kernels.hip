@@ -18,10 +18,13 @@
 //               to memory
 // (for d <= 128 both launches have narrow shapes: OUT, GRAD13 and GRAD2 whose
 // feature dimension fills the tile, and k_fwd_narrow, whose 128 x 128 tiles
-// let two workgroups share a CU)
+// let two workgroups share a CU; first launches too small for the wide tiles
+// take 128 x 128 tiles too, k_fwd_deep, and small fp32 calls 64 x 64 ones)
 //   NS_*        Newton-Schulz products (Muon, §3.2; App. A); k_ns_fused and
 //               k_ns_fused_pair run the whole iteration of a small matrix in
-//               one workgroup
+//               one workgroup; in the backward k_ns_sym and k_ns_dx do the
+//               reverse's products with their combinations, k_ns_replay and
+//               k_ns_reverse all of it for a small matrix
 // plus the separate weight update with its row normalisation and momentum
 // (k_update, wherever neither the gradient and update kind, k_ns_final nor
 // the fused small-matrix Newton-Schulz applies it),
@@ -36,8 +39,10 @@
 // ring of NSTAGE stages of BK K each. An operand is either K-contiguous in HBM
 // ("k": row-major [rows x K], kept as BK*2-byte rows in LDS, BK = 64 so that
 // every DMA fetches whole 128-byte lines, except in k_fwd_narrow) or row-contiguous ("mn": row-major
-// [K x rows], the token-major layout; BK = 32 K rows in LDS, read with
-// ds_read_b64_tr_b16, which returns MFMA fragments of the transposed operand).
+// [K x rows], the token-major layout; BK K rows in LDS, 64 or, in the narrow
+// gradient kinds, 32, read with ds_read_b64_tr_b16, which returns MFMA
+// fragments of the transposed operand). The wide kinds hand a stage over in
+// halves (mainloop_split), the others whole (mainloop).
 // fp32 I/O runs on v_mfma_f32_32x32x2_f32 with a register-staged double
 // buffer (the transposition of mn operands happens in registers there).
 #include "lact_internal.h"
@@ -164,11 +169,10 @@ struct KindBase {
     static constexpr int pb(int p) { return PB; }                                  \
   }
 
-// 16-bit shapes: 8 waves (2 per SIMD); two-accumulator kinds use 64 x 64
-// waves (128 x 256 tiles), one-accumulator kinds 128 x 64 (256 x 256).
-// Kinds whose operands are all K-contiguous take 64 K per stage, so that every
-// DMA fetches whole 128-byte lines; the gradient kinds (row-contiguous, 512
-// bytes and more per K row) keep 32 K and twice the stages.
+// 16-bit shapes: 8 waves (2 per SIMD), each 2 x (64 x 64) outputs: both
+// accumulators of a 128 x 256 tile, or two 64 x 64 blocks of a 256 x 256 one.
+// The split-stage kinds take 64 K per stage in two stages, so that every DMA
+// of a K-contiguous operand fetches whole 128-byte lines.
 // Apply GEMM-1 and the key forward, hidden-major: A = W1, W3 (hidden rows),
 // B = Q or K (token rows).
 LACT_SPLIT_KIND(KApply16, 0u, 1);
@@ -184,7 +188,7 @@ LACT_SPLIT_KIND(KGrad13_16, 7u, 1);
 LACT_SPLIT_KIND(KGrad2_16, 7u, 1);
 // Gradient with the weight update of whole rows (GRAD_UPD): A = eta dz1,
 // eta dz3 or V (128 rows of W1, W3 or W2), B = K or eta hidden (every column,
-// up to 512), token-major; waves of 64 x 128, 4 stages of 40 KiB.
+// up to 512), token-major; waves of 2 x (64 x 64), 2 stages of 80 KiB.
 LACT_SPLIT_KIND(KGradU16, 7u, 2);
 // Narrow shapes (16-bit, d <= 128): the feature dimension fills 128 tile rows
 // instead of half of 256. Apply GEMM-2: 128 features x 512 tokens; gradients
@@ -222,7 +226,7 @@ LACT_KIND(KGrad2_S32, 1, 1, 1, 3u, 2, 2, 1, 1, 2, false, 32, 0 * p, 0 * p);
 // Newton-Schulz products, each computed in the orientation whose transpose is
 // stored (see k_ns): both operands K-contiguous (K), both row-contiguous (MN),
 // or the first row-contiguous (TY: Y read down its columns). fp16 operands:
-// 8 waves of 128 x 64 (256 x 256 tiles) for large Gram matrices, 4 waves of
+// 8 waves of 2 x (64 x 64) (256 x 256 tiles) for large Gram matrices, 4 waves of
 // 64 x 64 (128 x 128) for small ones; fp32: 4 waves of 64 x 64.
 LACT_SPLIT_KIND(KNsK16B, 0u, 1);
 LACT_SPLIT_KIND(KNsMN16B, 7u, 1);
@@ -233,7 +237,7 @@ LACT_KIND(KNsTY16S, 1, 1, 1, 1u, 2, 2, 2, 2, 2, true, 64, 0 * p, 0 * p);
 LACT_KIND(KNsK32, 1, 1, 1, 0u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
 // Last Newton-Schulz step with the weight update (k_ns_final): A = B (rows of
 // the polynomial, K-contiguous), B = X4 read down its columns; 128 rows x up
-// to 512 columns, waves of 64 x 128, 2 stages of 80 KiB.
+// to 512 columns, waves of 2 x (64 x 64), 2 stages of 80 KiB.
 LACT_SPLIT_KIND(KNsRow16, 6u, 2);
 LACT_KIND(KNsMN32, 1, 1, 1, 3u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
 LACT_KIND(KNsTY32, 1, 1, 1, 1u, 2, 2, 2, 2, 2, false, 32, 0 * p, 0 * p);
