@@ -2854,8 +2854,8 @@ __global__ __launch_bounds__(512) void k_ns_replay(const NsSmallArgs k) {
 // each), S and M take the last 32 KiB in turn, A_k and B_k are read as
 // fragments straight from memory (L2), and dX' stays in fp32 registers. The
 // three products per step took three launches of 10 to 13 us over 120 slots of
-// 128 x 256; a chunk's five steps take 107 us here against 171 us, the replay
-// 62 us (k_ns_replay) against 171 us. One workgroup per slot leaves half the
+// 128 x 256; a chunk's five steps take 115 us here against 171 us, the replay
+// 44 us (k_ns_replay) against 171 us. One workgroup per slot leaves half the
 // CUs idle: what bounds both is the chain of products inside a slot.
 __global__ __launch_bounds__(512) void k_ns_reverse(const NsSmallArgs a) {
   constexpr int M = kNsFusedM, N = kNsFusedN, PX = N * 2, PA = M * 2, C4 = N / 4;
