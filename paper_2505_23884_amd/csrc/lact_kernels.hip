@@ -2673,6 +2673,18 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
       for (int g = 0; g < 4; ++g)
         fs_put4(as_, c1 + (ln & 31), r1 + mi * 32 + 8 * g + 4 * half, PA, a32[mi][4 * g], a32[mi][4 * g + 1],
                 a32[mi][4 * g + 2], a32[mi][4 * g + 3]);
+    if constexpr (KEEP) {
+      // b A from the rounded A too, as k_ns_sym takes it: A's rounding then
+      // enters B by b + 2 c A, -0.7 where the singular values gather (A = 1),
+      // instead of by 2 c A = 4.1. Against 64 bits the video backward's
+      // cotangents are 1 to 2% closer (1 to 1.5% closer than the product and
+      // its combination in launches of their own; with the fp32 A 0.3% worse),
+      // at the same time (2101 us).
+#pragma unroll
+      for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) a32[mi][e] = (float)(_Float16)a32[mi][e];
+    }
     lds_barrier();
     if constexpr (KEEP) copy_out(as_, PA, keep->A + km, sr, sr);
     // ---- B = b A + c A A (K = M) ----
