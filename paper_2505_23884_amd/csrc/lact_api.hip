@@ -1989,6 +1989,7 @@ int run_backward_linear(const lact_desc* desc, const void* q, const void* k, con
     BwdArgs b{};
     lin_out_seg(b.seg[0], p, op(kb + s0 * d * esz, d, n_kv * d), op(ub, d, dd), (uint8_t*)dv + s0 * d * esz,
                 n_kv * d, n);   // Y = K Uh^T
+    b.seg[0].reread = true;     // by k_lin_tokens
     lin_out_seg(b.seg[1], p, op(vb + s0 * d * esz, d, n_kv * d), op(ut, d, dd), (uint8_t*)dk + s0 * d * esz,
                 n_kv * d, n);   // dk = eta (V Uh)
     b.seg[1].row_scale = eta + s0;
@@ -2305,6 +2306,7 @@ int run_backward_swiglu(const lact_desc* desc, const void* q, const void* k, con
     void* out;
     int64_t out_inst;
     int64_t K;
+    bool reread = false;   // by the row kernel that follows (BwdSeg::reread)
   };
   struct Pending {
     BwdArgs b{};
@@ -2330,6 +2332,7 @@ int run_backward_swiglu(const lact_desc* desc, const void* q, const void* k, con
       g.out = o[i].out;
       g.out_inst = o[i].out_inst;
       g.klen = o[i].K;
+      g.reread = o[i].reread;
       fl += 2.0 * BH * n * rows_out * o[i].K;
     }
     b.nseg = np + nseg;
@@ -2409,9 +2412,9 @@ int run_backward_swiglu(const lact_desc* desc, const void* q, const void* k, con
   // the caller's OUT launch (Pq against the transposed weights)
   auto apply_back = [&](int64_t a, int64_t n, const size_t* u, int64_t split_len, Pending* into = nullptr) -> int {
     const Operand qo = op(qb + a * d * esz, d, n_q * d), doo = op(ob + a * d * esz, d, n_q * d);
-    const Out h3[3] = {{qo, op(ws + u[0], d, dh), zb[0], zi, d},
-                       {qo, op(ws + u[1], d, dh), zb[1], zi, d},
-                       {doo, op(ws + u[2], d, dh), zb[2], zi, d}};
+    const Out h3[3] = {{qo, op(ws + u[0], d, dh), zb[0], zi, d, true},
+                       {qo, op(ws + u[1], d, dh), zb[1], zi, d, true},
+                       {doo, op(ws + u[2], d, dh), zb[2], zi, d, true}};
     int r = outs(h3, 3, n, (int)h);
     if (r) return r;
     r = timed(LACT_KCLASS_UPDATE, 0.0, s, [&] {
@@ -2576,9 +2579,9 @@ int run_backward_swiglu(const lact_desc* desc, const void* q, const void* k, con
     // Z1 = K W1^T, Z3 = K W3^T and C = V W2 of this update: kept by its replay
     uint8_t* kz = ws + L.off_keep + (size_t)u * L.keep_slot;
     const size_t kzm = (size_t)p.BH * p.C * h * esz;
-    const Out x3[3] = {{ko, op(ur[0], d, dh), zb[3], zi, d},
-                       {ko, op(ur[1], d, dh), zb[4], zi, d},
-                       {vo, op(ur[2], d, dh), zb[5], zi, d}};
+    const Out x3[3] = {{ko, op(ur[0], d, dh), zb[3], zi, d, true},
+                       {ko, op(ur[1], d, dh), zb[4], zi, d, true},
+                       {vo, op(ur[2], d, dh), zb[5], zi, d, true}};
     rc = outs(x3, 3, n, (int)h);
     if (rc) return rc;
     SwigluRowsArgs ra{};

@@ -72,6 +72,7 @@ struct BwdSeg {
   const float* row_scale;  // OUT (or nullptr): token t's row is scaled by row_scale[inst * scale_inst + t]
   int64_t scale_inst;
   int64_t klen;         // OUT: contraction length (0: the launch's h)
+  bool reread;          // OUT, 16-bit: the next launch reads the rows back, so ordinary stores
   // GRAD_UPD (16-bit I/O, whole rows per tile, no split): the gradients of
   // W1 (a0 = eta dz1, b0 = K), W3 (a1 = eta dz3, b0) and W2 (a2 = V,
   // b1 = eta hidden) and the weight update in one pass; tiles_m counts the

@@ -1193,11 +1193,26 @@ __device__ __forceinline__ void stage_put(uint8_t* buf, int tok, int row, float 
 // forward 717 -> 685 us, LM shape backward 12424 -> 12162 us, NVS 256K 5627 ->
 // 5568 us, LM shape forward within its noise. The gradients' fp32 partials,
 // which the update reads back at once, stay ordinary stores: video 679 -> 688
-// us otherwise).
+// us otherwise). reread: rows that a row kernel reads back in the very next
+// launch are stored plainly, so that it finds part of them cached (linear
+// forward and backward, 16001 tokens: 1883 -> 1866 us).
 template <int R, int C, int THREADS, typename E = __bf16>
-__device__ __forceinline__ void stage_flush(const uint8_t* buf, E* out, int64_t ld, int64_t ntok, int64_t nrow) {
+__device__ __forceinline__ void stage_flush(const uint8_t* buf, E* out, int64_t ld, int64_t ntok, int64_t nrow,
+                                            bool reread = false) {
   constexpr int CPR = R / 8, TOTAL = C * CPR;
   static_assert(CPR >= 16 && TOTAL % THREADS == 0, "staging shape");
+  if (reread) {
+    asm volatile("" ::: "memory");   // keeps the two kinds of store apart
+#pragma unroll
+    for (int i = 0; i < TOTAL / THREADS; ++i) {
+      const int q = i * THREADS + threadIdx.x;
+      const int tok = q / CPR, c = q % CPR;
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(buf + tok * (2 * R) + ((c ^ (tok & 15)) << 4));
+      if (tok < ntok && c * 8 < nrow) *reinterpret_cast<u32x4_t*>(out + tok * ld + c * 8) = v;
+    }
+    asm volatile("" ::: "memory");
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < TOTAL / THREADS; ++i) {
     const int q = i * THREADS + threadIdx.x;
@@ -1765,7 +1780,7 @@ __device__ __forceinline__ void bwd_body(const BwdArgs& args, int blk, uint8_t* 
             }
       lds_barrier();
       stage_flush<TR, KO::ROWS_B, KO::THREADS, T>(smem, reinterpret_cast<T*>(sg.out) + ob + t0 * d + m0, d, ntok,
-                                                  mrows);
+                                                  mrows, sg.reread);
       return;
     }
 #pragma unroll
@@ -3614,47 +3629,79 @@ __global__ __launch_bounds__(256) void k_accum(float* G, int64_t g_inst, const f
   }
 }
 
-// Linear fast weight, one wave per key token t of a chunk (grid stride over
-// BH x n tokens). On entry dv holds Y = K Uh^T (rows t); it leaves as
-// dv_t = eta_t Y_t, with deta_t = v_t . Y_t (= v_t^T Uh k_t).
+// The row kernels of the backward below, bound by HBM (5.4 to 5.9 TB/s at the
+// LM shape): a group of G lanes per token, 16 bytes per lane and access, 256 /
+// G tokens per workgroup. Their inputs are read for the last time, so the loads
+// are non-temporal and leave the caches to the results, which the products
+// that follow read. With ordinary stores of the inputs (BwdSeg::reread), one
+// process: video backward 2095 -> 2060 us, linear forward and backward (16001
+// tokens) 1879 -> 1858 us, LM + Muon backward 4036 -> 4025 us, LM backward
+// within its noise (11775 us). The wider loads and lane groups alone: video
+// 2097 -> 2088 us, the others within their noise.
 template <typename T>
-__global__ __launch_bounds__(256) void k_lin_tokens(const T* V, const float* eta, T* dv, float* deta, int BH,
-                                                    int64_t n, int d, int64_t tok_inst, int64_t eta_inst) {
-  const int lane = threadIdx.x & 63;
-  const int64_t total = (int64_t)BH * n;
-  for (int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); wave < total; wave += (int64_t)gridDim.x * 4) {
-    const int64_t inst = wave / n, t = wave - inst * n;
+struct Row {
+  static constexpr int EPV = 16 / (int)sizeof(T);
+  typedef __attribute__((ext_vector_type(16 / sizeof(T)))) T V;
+  __device__ static __forceinline__ void ld(const void* base, int64_t idx, float (&v)[EPV]) {
+    const V x = __builtin_nontemporal_load(reinterpret_cast<const V*>(reinterpret_cast<const T*>(base) + idx));
+#pragma unroll
+    for (int q = 0; q < EPV; ++q) v[q] = (float)x[q];
+  }
+  __device__ static __forceinline__ void st(void* base, int64_t idx, const float (&v)[EPV]) {
+    V x;
+#pragma unroll
+    for (int q = 0; q < EPV; ++q) x[q] = (T)v[q];
+    *reinterpret_cast<V*>(reinterpret_cast<T*>(base) + idx) = x;
+  }
+};
+
+__device__ __forceinline__ float lanes_sum(float v, int G) {
+  for (int off = G >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Lanes per token for rows of len elements: halved from 64 while the last pass
+// over the row leaves a fifth of all lanes idle (h = 256 in 16 bits: 32 lanes,
+// two tokens per wave; 768: three passes of 32 lanes, not one and a half of 64).
+int row_group(int64_t len, bool io_bf16) {
+  const int64_t nv = len / (io_bf16 ? 8 : 4);
+  int G = 64;
+  while (G > 8 && (nv + G - 1) / G * G * 4 >= nv * 5) G /= 2;
+  return G;
+}
+
+// Linear fast weight, one group of lanes per key token t of a chunk. On entry
+// dv holds Y = K Uh^T (rows t); it leaves as dv_t = eta_t Y_t, with
+// deta_t = v_t . Y_t (= v_t^T Uh k_t).
+template <typename T>
+__global__ __launch_bounds__(256) void k_lin_tokens(const T* V, const float* eta, T* dv, float* deta, int64_t n, int d,
+                                                    int64_t tok_inst, int64_t eta_inst, int G, int64_t per,
+                                                    int64_t nblk) {
+  constexpr int EPV = Row<T>::EPV;
+  const int lane = threadIdx.x & (G - 1), grp = threadIdx.x / G;
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int64_t inst = b / per, t = (b - inst * per) * (256 / G) + grp;
+    if (t >= n) continue;
     const int64_t o = inst * tok_inst + t * d;
     const float e = eta[inst * eta_inst + t];
     float dot = 0.0f;
-    for (int c = 4 * lane; c < d; c += 256) {
-      float y[4];
+    for (int c = EPV * lane; c < d; c += EPV * G) {
+      float y[EPV], x[EPV];
+      Row<T>::ld(dv, o + c, y);
+      Row<T>::ld(V, o + c, x);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        y[q] = (float)dv[o + c + q];
-        dot += (float)V[o + c + q] * y[q];
+      for (int q = 0; q < EPV; ++q) {
+        dot += x[q] * y[q];
+        y[q] *= e;
       }
-      st4<T>(dv, o + c, e * y[0], e * y[1], e * y[2], e * y[3]);
+      Row<T>::st(dv, o + c, y);
     }
-    dot = wave_sum(dot);
+    dot = lanes_sum(dot, G);
     if (lane == 0) deta[inst * eta_inst + t] = dot;
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void ld4(const void* base, int64_t idx, float* v) {
-  const T* p = reinterpret_cast<const T*>(base) + idx;
-  if constexpr (sizeof(T) == 2) {
-    typedef __attribute__((ext_vector_type(4))) T t4;
-    const t4 x = *reinterpret_cast<const t4*>(p);
-    v[0] = (float)x[0]; v[1] = (float)x[1]; v[2] = (float)x[2]; v[3] = (float)x[3];
-  } else {
-    const float4 x = *reinterpret_cast<const float4*>(p);
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-  }
-}
-
-// SwiGLU chunk-gradient reverse, one wave per key token (grid stride). With
+// SwiGLU chunk-gradient reverse, one group of lanes per key token. With
 // S = SiLU(Z1), S1 = SiLU'(Z1), S2 = SiLU''(Z1), A = S Z3 and the token's
 // rates e1, e2, e3 of W1, W2, W3 (one rate: all three the same):
 //   dA  = e2 Y2,  dC = e3 X3 S + e1 X1 Z3 S1,  dZ3 = e1 X1 C S1 + dA S,
@@ -3662,30 +3709,31 @@ __device__ __forceinline__ void ld4(const void* base, int64_t idx, float* v) {
 //   and, summed over the hidden units, de1 = X1 C Z3 S1, de2 = A Y2,
 //   de3 = X3 C S (one rate: deta = their sum).
 template <typename T>
-__global__ __launch_bounds__(256) void k_swiglu_rows(const SwigluRowsArgs a) {
-  const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(256) void k_swiglu_rows(const SwigluRowsArgs a, int G, int64_t per, int64_t nblk) {
+  constexpr int EPV = Row<T>::EPV;
+  const int lane = threadIdx.x & (G - 1), grp = threadIdx.x / G;
   const int h = a.h;
   const bool per_matrix = a.eta_cols == 3;
-  const int64_t total = (int64_t)a.BH * a.n;
-  for (int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); wave < total; wave += (int64_t)gridDim.x * 4) {
-    const int64_t inst = wave / a.n, t = wave - inst * a.n;
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int64_t inst = b / per, t = (b - inst * per) * (256 / G) + grp;
+    if (t >= a.n) continue;
     const int64_t io = inst * a.in_inst + t * h, zo = inst * (a.z_inst ? a.z_inst : a.in_inst) + t * h;
     const int64_t ko = inst * a.pk_inst + t * 4 * h, vo = inst * a.pv_inst + t * 2 * h;
     const int64_t eo = (inst * a.eta_inst + t) * a.eta_cols;
     const float e1 = a.eta[eo];
     const float e2 = per_matrix ? a.eta[eo + 1] : e1, e3 = per_matrix ? a.eta[eo + 2] : e1;
     float d1 = 0.0f, d2 = 0.0f, d3 = 0.0f;
-    for (int j = 4 * lane; j < h; j += 256) {
-      float z1[4], z3[4], c[4], x1[4], x3[4], y2[4];
-      ld4<T>(a.Z1, zo + j, z1);
-      ld4<T>(a.Z3, zo + j, z3);
-      ld4<T>(a.C, zo + j, c);
-      ld4<T>(a.X1, io + j, x1);
-      ld4<T>(a.X3, io + j, x3);
-      ld4<T>(a.Y2, io + j, y2);
-      float r3[4], r1[4], dz1[4], dz3[4], ea[4], dc[4];
+    for (int j = EPV * lane; j < h; j += EPV * G) {
+      float z1[EPV], z3[EPV], c[EPV], x1[EPV], x3[EPV], y2[EPV];
+      Row<T>::ld(a.Z1, zo + j, z1);
+      Row<T>::ld(a.Z3, zo + j, z3);
+      Row<T>::ld(a.C, zo + j, c);
+      Row<T>::ld(a.X1, io + j, x1);
+      Row<T>::ld(a.X3, io + j, x3);
+      Row<T>::ld(a.Y2, io + j, y2);
+      float r3[EPV], r1[EPV], dz1[EPV], dz3[EPV], ea[EPV], dc[EPV];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < EPV; ++q) {
         const float sg = sigmoidf_fast(z1[q]);
         const float S = z1[q] * sg, S1 = sg + z1[q] * sg * (1.0f - sg);
         const float S2 = sg * (1.0f - sg) * (2.0f + z1[q] * (1.0f - 2.0f * sg));
@@ -3701,56 +3749,57 @@ __global__ __launch_bounds__(256) void k_swiglu_rows(const SwigluRowsArgs a) {
         d2 += A * y2[q];
         d3 += t3;
       }
-      st4<T>(a.Pk, ko + j, r3[0], r3[1], r3[2], r3[3]);
-      st4<T>(a.Pk, ko + h + j, r1[0], r1[1], r1[2], r1[3]);
-      st4<T>(a.Pk, ko + 2 * h + j, dz1[0], dz1[1], dz1[2], dz1[3]);
-      st4<T>(a.Pk, ko + 3 * h + j, dz3[0], dz3[1], dz3[2], dz3[3]);
-      st4<T>(a.Pv, vo + j, ea[0], ea[1], ea[2], ea[3]);
-      st4<T>(a.Pv, vo + h + j, dc[0], dc[1], dc[2], dc[3]);
+      Row<T>::st(a.Pk, ko + j, r3);
+      Row<T>::st(a.Pk, ko + h + j, r1);
+      Row<T>::st(a.Pk, ko + 2 * h + j, dz1);
+      Row<T>::st(a.Pk, ko + 3 * h + j, dz3);
+      Row<T>::st(a.Pv, vo + j, ea);
+      Row<T>::st(a.Pv, vo + h + j, dc);
     }
     if (per_matrix) {
-      d1 = wave_sum(d1);
-      d2 = wave_sum(d2);
-      d3 = wave_sum(d3);
+      d1 = lanes_sum(d1, G);
+      d2 = lanes_sum(d2, G);
+      d3 = lanes_sum(d3, G);
       if (lane == 0) {
         a.deta[eo] = d1;
         a.deta[eo + 1] = d2;
         a.deta[eo + 2] = d3;
       }
     } else {
-      const float dsum = wave_sum(d2 + d3 + d1);
+      const float dsum = lanes_sum(d2 + d3 + d1, G);
       if (lane == 0) a.deta[eo] = dsum;
     }
   }
 }
 
-// SwiGLU apply reverse, one wave per query token (grid stride):
+// SwiGLU apply reverse, one group of lanes per query token:
 // Hq = SiLU(Zq1) Zq3, dZq3 = Dh SiLU(Zq1), dZq1 = Dh Zq3 SiLU'(Zq1).
 template <typename T>
 __global__ __launch_bounds__(256) void k_swiglu_apply_rows(const T* Z1, const T* Z3, const T* Dh, int64_t in_inst, T* Pq,
-                                                           int64_t pq_inst, T* Hq, int64_t hq_inst, int BH, int64_t n,
-                                                           int h) {
-  const int lane = threadIdx.x & 63;
-  const int64_t total = (int64_t)BH * n;
-  for (int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); wave < total; wave += (int64_t)gridDim.x * 4) {
-    const int64_t inst = wave / n, t = wave - inst * n;
+                                                           int64_t pq_inst, T* Hq, int64_t hq_inst, int64_t n, int h,
+                                                           int G, int64_t per, int64_t nblk) {
+  constexpr int EPV = Row<T>::EPV;
+  const int lane = threadIdx.x & (G - 1), grp = threadIdx.x / G;
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int64_t inst = b / per, t = (b - inst * per) * (256 / G) + grp;
+    if (t >= n) continue;
     const int64_t io = inst * in_inst + t * h, po = inst * pq_inst + t * 2 * h, ho = inst * hq_inst + t * h;
-    for (int j = 4 * lane; j < h; j += 256) {
-      float z1[4], z3[4], dh[4], d1[4], d3[4], hq[4];
-      ld4<T>(Z1, io + j, z1);
-      ld4<T>(Z3, io + j, z3);
-      ld4<T>(Dh, io + j, dh);
+    for (int j = EPV * lane; j < h; j += EPV * G) {
+      float z1[EPV], z3[EPV], dh[EPV], d1[EPV], d3[EPV], hq[EPV];
+      Row<T>::ld(Z1, io + j, z1);
+      Row<T>::ld(Z3, io + j, z3);
+      Row<T>::ld(Dh, io + j, dh);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < EPV; ++q) {
         const float sg = sigmoidf_fast(z1[q]);
         const float S = z1[q] * sg, S1 = sg + z1[q] * sg * (1.0f - sg);
         hq[q] = S * z3[q];
         d3[q] = dh[q] * S;
         d1[q] = dh[q] * z3[q] * S1;
       }
-      st4<T>(Pq, po + j, d1[0], d1[1], d1[2], d1[3]);
-      st4<T>(Pq, po + h + j, d3[0], d3[1], d3[2], d3[3]);
-      st4<T>(Hq, ho + j, hq[0], hq[1], hq[2], hq[3]);
+      Row<T>::st(Pq, po + j, d1);
+      Row<T>::st(Pq, po + h + j, d3);
+      Row<T>::st(Hq, ho + j, hq);
     }
   }
 }
@@ -4140,24 +4189,26 @@ hipError_t launch_lin_tokens(const void* V, const float* eta, void* dv, float* d
                              int64_t tok_inst, int64_t eta_inst, bool io_bf16, hipStream_t s) {
   const int64_t rows = (int64_t)BH * n;
   if (rows <= 0) return hipSuccess;
-  const int64_t need = (rows + 3) / 4;
-  const unsigned blocks = (unsigned)(need < ((int64_t)1 << 20) ? need : ((int64_t)1 << 20));
+  const int G = row_group(d, io_bf16);
+  const int64_t per = (n + 256 / G - 1) / (256 / G), nblk = per * BH;
+  const unsigned blocks = (unsigned)(nblk < ((int64_t)1 << 20) ? nblk : ((int64_t)1 << 20));
   if (io_bf16)
     k_lin_tokens<__bf16><<<blocks, 256, 0, s>>>(reinterpret_cast<const __bf16*>(V), eta, reinterpret_cast<__bf16*>(dv),
-                                                deta, BH, n, d, tok_inst, eta_inst);
+                                                deta, n, d, tok_inst, eta_inst, G, per, nblk);
   else
     k_lin_tokens<float><<<blocks, 256, 0, s>>>(reinterpret_cast<const float*>(V), eta, reinterpret_cast<float*>(dv),
-                                               deta, BH, n, d, tok_inst, eta_inst);
+                                               deta, n, d, tok_inst, eta_inst, G, per, nblk);
   return hipGetLastError();
 }
 
 hipError_t launch_swiglu_rows(const SwigluRowsArgs& a, bool io_bf16, hipStream_t s) {
   const int64_t rows = (int64_t)a.BH * a.n;
   if (rows <= 0) return hipSuccess;
-  const int64_t need = (rows + 3) / 4;
-  const unsigned blocks = (unsigned)(need < ((int64_t)1 << 20) ? need : ((int64_t)1 << 20));
-  if (io_bf16) k_swiglu_rows<__bf16><<<blocks, 256, 0, s>>>(a);
-  else k_swiglu_rows<float><<<blocks, 256, 0, s>>>(a);
+  const int G = row_group(a.h, io_bf16);
+  const int64_t per = (a.n + 256 / G - 1) / (256 / G), nblk = per * a.BH;
+  const unsigned blocks = (unsigned)(nblk < ((int64_t)1 << 20) ? nblk : ((int64_t)1 << 20));
+  if (io_bf16) k_swiglu_rows<__bf16><<<blocks, 256, 0, s>>>(a, G, per, nblk);
+  else k_swiglu_rows<float><<<blocks, 256, 0, s>>>(a, G, per, nblk);
   return hipGetLastError();
 }
 
@@ -4166,13 +4217,14 @@ hipError_t launch_swiglu_apply_rows(const void* Z1, const void* Z3, const void* 
                                     hipStream_t s) {
   const int64_t rows = (int64_t)BH * n;
   if (rows <= 0) return hipSuccess;
-  const int64_t need = (rows + 3) / 4;
-  const unsigned blocks = (unsigned)(need < ((int64_t)1 << 20) ? need : ((int64_t)1 << 20));
+  const int G = row_group(h, io_bf16);
+  const int64_t per = (n + 256 / G - 1) / (256 / G), nblk = per * BH;
+  const unsigned blocks = (unsigned)(nblk < ((int64_t)1 << 20) ? nblk : ((int64_t)1 << 20));
   auto go = [&](auto tag) {
     using T = decltype(tag);
     k_swiglu_apply_rows<T><<<blocks, 256, 0, s>>>(reinterpret_cast<const T*>(Z1), reinterpret_cast<const T*>(Z3),
                                                   reinterpret_cast<const T*>(Dh), in_inst, reinterpret_cast<T*>(Pq),
-                                                  pq_inst, reinterpret_cast<T*>(Hq), hq_inst, BH, n, h);
+                                                  pq_inst, reinterpret_cast<T*>(Hq), hq_inst, n, h, G, per, nblk);
   };
   if (io_bf16) go(__bf16{});
   else go(float{});

@@ -1727,6 +1727,23 @@ def test_swiglu_backward_fp32_small(order):
     check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct, with_dW=False), with_dW=False)
 
 
+@pytest.mark.parametrize("io,d,h,linear", [
+    ("bf16", 32, 32, 0), ("bf16", 64, 96, 0), ("bf16", 32, 544, 0), ("bf16", 64, 576, 0), ("bf16", 96, 96, 1),
+    ("bf16", 576, 576, 1), ("fp32", 8, 8, 0), ("fp32", 16, 264, 0), ("fp32", 72, 72, 1)])
+def test_backward_row_groups(io, d, h, linear):
+    # the row kernels' lanes per token: 8 (rows of 2, 4, 12 and 18 16-byte
+    # vectors) and 16 (66, 68 and 72), rows shorter than one pass, a last pass
+    # partly filled; token counts that no workgroup's tokens (16, 32) divide
+    # (32 and 64 lanes: h = 256, 768 and 512 elsewhere)
+    base = CONFIGS["lm32k"] if io == "bf16" else CONFIGS["tiny_fp32"]
+    cfg = base.with_(name="bwd_rows", B=1, H=3, d=d, h=h, n_kv=77, n_q=131, chunk=45, order=0, linear=linear)
+    x, ct = make_inputs(cfg, 78), make_cotangents(cfg, 78)
+    if linear:
+        check_linear_bwd(cfg, x, ct, run_gpu_linear_bwd(cfg, x, ct))
+    else:
+        check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
+
+
 def test_swiglu_backward_narrow_tiles_without_tail():
     # d = 128 (the narrow bf16 tiles), the video head shape, n_q == n_kv, a last chunk of one token
     cfg = CONFIGS["video"].with_(name="swiglu_bwd_narrow", B=1, H=3, n_kv=513, n_q=513, chunk=128, use_muon=0)
