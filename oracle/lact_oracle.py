@@ -501,7 +501,8 @@ def newton_schulz_vjp(G, dX, steps: int = NS_STEPS_DEFAULT, coeffs=NS_COEFFS, ep
         dB = dX' X^T,  dA = b dB + c (dB A + A dB),
         dX = a dX' + B dX' + (dA + dA^T) X,
     and the scaling X_0 = G / (s + eps), s = ||G||_F, as
-        dG = dX_0 / (s + eps) - <dX_0, G> G / ((s + eps)^2 s).
+        dG = dX_0 / (s + eps) - <dX_0, G> G / ((s + eps)^2 s)
+    (a zero G: the first term, with 0 as the norm's subgradient).
     """
     a, b, c = coeffs
     G = np.asarray(G, dtype=np.float64)
@@ -522,7 +523,9 @@ def newton_schulz_vjp(G, dX, steps: int = NS_STEPS_DEFAULT, coeffs=NS_COEFFS, ep
         dB = dX @ X.T
         dA = b * dB + c * (dB @ A + A @ dB)
         dX = a * dX + Bm.T @ dX + (dA + dA.T) @ X
-    dG = dX / (s + eps) - (np.sum(dX * G) / ((s + eps) ** 2 * s)) * G
+    dG = dX / (s + eps)
+    if s > 0:
+        dG = dG - (np.sum(dX * G) / ((s + eps) ** 2 * s)) * G
     return dG.T if transposed else dG
 
 

@@ -389,6 +389,7 @@ hipError_t launch_slot_dot(const float* x, const float* y, int S, int64_t len, f
 //   mode 0: out = x / (sqrt(sc) + eps)
 //   mode 1: out = a x + p1 (+ p2 when given)
 //   mode 2: out = x / (sqrt(sc) + eps) - sc2 / ((sqrt(sc) + eps)^2 sqrt(sc)) y
+//           (without the second term where sc is 0: the norm's subgradient there)
 // into out32 and/or its fp16 copy out16.
 struct NsLinArgs {
   int mode;

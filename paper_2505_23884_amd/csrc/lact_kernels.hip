@@ -3103,7 +3103,9 @@ __global__ __launch_bounds__(512) void k_ns_reverse(const NsSmallArgs a) {
   dot = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) dot += red[i];
-  const float nrm = sqrtf(a.nrm[slot]), se = nrm + a.eps, f = 1.0f / se, gf = dot / (se * se * nrm);
+  // (a zero G, whose step is zero, or one whose squares underflow: the norm's part is 0, as its subgradient)
+  const float nrm = sqrtf(a.nrm[slot]), se = nrm + a.eps, f = 1.0f / se;
+  const float gf = nrm == 0.0f ? 0.0f : dot / (se * se * nrm);
 #pragma unroll
   for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
@@ -3564,7 +3566,7 @@ __global__ __launch_bounds__(256) void k_ns_lin(const NsLinArgs a) {
       }
     } else {
       const float nrm = sqrtf(a.sc[slot]), se = nrm + a.eps;
-      const float f = 1.0f / se, gf = a.sc2[slot] / (se * se * nrm);
+      const float f = 1.0f / se, gf = nrm == 0.0f ? 0.0f : a.sc2[slot] / (se * se * nrm);   // as k_ns_reverse
       const float4 y = reinterpret_cast<const float4*>(a.y)[q];
       r = make_float4(x.x * f - gf * y.x, x.y * f - gf * y.y, x.z * f - gf * y.z, x.w * f - gf * y.w);
     }

@@ -1813,6 +1813,23 @@ def test_swiglu_muon_backward_product_tiles(d, h):
     check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
 
 
+@pytest.mark.parametrize("io,d,h", [("bf16", 64, 96), ("bf16", 160, 288), ("fp32", 40, 56)])
+def test_swiglu_muon_backward_zero_gradient(io, d, h):
+    # one head whose last chunk has zero rates: a zero gradient, so a zero step,
+    # and a finite reverse (the norm's subgradient at 0 is 0) that must not
+    # reach the other cotangents of this chunk or the earlier one; a slot of one
+    # workgroup, a larger one, and fp32
+    C = 4 * max(d, h)
+    base = CONFIGS["lm32k_muon"] if io == "bf16" else CONFIGS["tiny_fp32"]
+    cfg = base.with_(name="muon_bwd_zero", B=1, H=2, d=d, h=h, n_kv=2 * C, n_q=2 * C, chunk=C, order=0, use_muon=1)
+    x, ct = make_inputs(cfg, 89), make_cotangents(cfg, 89)
+    x["eta"][0, C:] = 0.0
+    got = run_gpu_swiglu_bwd(cfg, x, ct)
+    assert all(np.isfinite(g).all() for g in got)
+    for i in range(2):
+        check_swiglu_bwd(cfg, x, ct, got, instances=[i])
+
+
 def test_swiglu_muon_backward_lm_shape_two_chunks():
     # d = h = 512 (the LM's Gram size), two chunks of 2048
     cfg = CONFIGS["lm32k_muon"].with_(name="swiglu_muon_bwd_lm", B=1, H=2, n_kv=4096, n_q=4096)

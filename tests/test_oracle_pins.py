@@ -1106,6 +1106,16 @@ def test_newton_schulz_vjp_matches_autograd(shape):
     assert np.allclose(O.newton_schulz_vjp(G, dX), Gt.grad.numpy(), rtol=1e-9, atol=1e-11)
 
 
+def test_newton_schulz_vjp_of_a_zero_matrix():
+    # the norm's subgradient at 0 is 0 (as autograd takes it): a^5 dX / eps
+    dX = _rng(123).standard_normal((6, 9))
+    Gt = torch.zeros(6, 9, dtype=torch.float64, requires_grad=True)
+    (_torch_newton_schulz(Gt) * torch.tensor(dX)).sum().backward()
+    got = O.newton_schulz_vjp(np.zeros((6, 9)), dX)
+    assert np.allclose(got, Gt.grad.numpy(), rtol=1e-9)
+    assert np.allclose(got, O.NS_COEFFS[0] ** 5 * dX / O.NS_EPS, rtol=1e-9)
+
+
 def test_newton_schulz_vjp_finite_differences():
     rng = _rng(124)
     G, dX = rng.standard_normal((5, 8)), rng.standard_normal((5, 8))
