@@ -497,9 +497,10 @@ int lact_rmsnorm_out(const lact_desc* desc, const void* o, const float* weight, 
  * [B*H, n_q, d] (io_dtype) and, when dweight is not NULL (weight must then be
  * given), dweight [H, d] (fp32). With r = 1 / sqrt(mean_d(o^2) + eps) and
  * g = weight * dy per element: d_o = r g - (r^3 / d) o (g . o), and dweight
- * sums dy o r over the batch and the tokens (a second pass, in a fixed order;
- * its workspace, lact_rmsnorm_out_backward_workspace_bytes(desc, 1), holds
- * the per-vector r and the pass's partial sums; 0 bytes without dweight).
+ * sums dy o r over the batch and the tokens, in a fixed order: in the same
+ * pass, or for long d in a second one. Its workspace,
+ * lact_rmsnorm_out_backward_workspace_bytes(desc, 1), holds the sums' partials
+ * and, for the second pass, the per-vector r; 0 bytes without dweight.
  */
 int lact_prologue_backward(const lact_desc* desc, const void* qkv, const float* lr_raw, float lr_bias,
                            const float* beta_raw, const void* dq, const void* dk, const void* dv,

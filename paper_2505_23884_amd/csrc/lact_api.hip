@@ -2879,9 +2879,8 @@ size_t lact_rmsnorm_out_backward_workspace_bytes(const lact_desc* desc, int with
   if (err) *err = rc;
   if (rc) return 0;
   if (!with_weight) return 0;
-  const size_t r = align_up((size_t)desc->B * desc->n_q * desc->H * 4);
-  const size_t part = (size_t)rms_dw_splits(desc->B, desc->n_q, desc->H, desc->d) * desc->H * desc->d * 4;
-  return align_up(r + part);
+  const bool bf16 = desc->io_dtype == LACT_IO_BF16;
+  return align_up((size_t)rms_dw_plan(desc->B, desc->n_q, desc->H, desc->d, bf16).floats * 4);
 }
 
 int lact_rmsnorm_out_backward(const lact_desc* desc, const void* o, const float* weight, float eps, const void* dy,
@@ -2902,8 +2901,7 @@ int lact_rmsnorm_out_backward(const lact_desc* desc, const void* o, const float*
   a.dy = dy;
   a.d_o = d_o;
   a.dweight = dweight;
-  a.part = dweight ? reinterpret_cast<float*>(workspace) : nullptr;
-  a.part_room = (int64_t)(need / 4);
+  a.work = dweight ? reinterpret_cast<float*>(workspace) : nullptr;
   a.eps = eps;
   a.B = desc->B;
   a.H = desc->H;

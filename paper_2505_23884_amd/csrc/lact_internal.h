@@ -283,21 +283,27 @@ struct PrologueBwdArgs {
 };
 hipError_t launch_prologue_bwd(PrologueBwdArgs a, bool io_bf16, hipStream_t s);
 // Reverse of the output RMSNorm: do from dy, and with dweight its cotangent,
-// summed over token splits (part: at least rms_dw_splits(...) * H * hd floats).
+// summed over token splits (work: at least rms_dw_plan(...).floats floats).
 struct RmsBwdArgs {
   const void* o;           // [B*H, L, hd]
   const float* weight;     // [H, hd] or nullptr
   const void* dy;          // [B, L, H, hd]
   void* d_o;               // [B*H, L, hd]
   float* dweight;          // [H, hd] or nullptr
-  float* part;             // scratch (with dweight): partial sums, part_room floats
-  int64_t part_room;
+  float* work;             // scratch (with dweight)
+  float *r, *part;         // set by the launcher: parts of it (each vector's r [B, L, H]; partial sums)
   float eps;
   int B, H, hd;
   int64_t L;
   int group;               // set by the launcher
 };
-int rms_dw_splits(int B, int64_t L, int H, int hd);
+struct RmsDwPlan {
+  bool one_pass;           // the weight's cotangent in the same pass as d_o, else in one after it
+  int64_t nsplit, per;     // token splits and their tokens
+  int64_t r_floats;        // two passes: room for each vector's r
+  int64_t floats;          // the whole workspace (no less for one pass)
+};
+RmsDwPlan rms_dw_plan(int B, int64_t L, int H, int hd, bool io_bf16);
 hipError_t launch_rmsnorm_out_bwd(RmsBwdArgs a, bool io_bf16, hipStream_t s);
 
 // Workgroup tile of a contraction kind: output rows x output columns, threads.

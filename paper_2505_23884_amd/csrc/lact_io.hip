@@ -285,7 +285,8 @@ __global__ __launch_bounds__(256) void k_prologue_bwd(const PrologueBwdArgs a) {
 }
 
 // Reverse of k_rmsnorm_out, one group per output vector (b, l, h): with r =
-// 1 / sqrt(mean(o^2) + eps) and g = w dy, do = r g - (r^3 / hd) o (g . o).
+// 1 / sqrt(mean(o^2) + eps) and g = w dy, do = r g - (r^3 / hd) o (g . o);
+// with a.r the vector's r goes there, for k_rms_dw_part.
 template <typename T, int NV, typename IX>
 __global__ __launch_bounds__(256) void k_rmsnorm_out_bwd(const RmsBwdArgs a) {
   constexpr int EPV = Io<T>::EPV;
@@ -330,6 +331,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_out_bwd(const RmsBwdArgs a) {
       for (int e = 0; e < EPV; ++e) o[e] = r * gv[j][e] - c * x[j][e];
       Io<T>::store(reinterpret_cast<T*>(a.d_o) + oo + (lane_g + j * G) * EPV, o);
     }
+    if (a.r && lane_g == 0) a.r[g] = r;
   }
 }
 
@@ -406,6 +408,51 @@ __global__ __launch_bounds__(256) void k_rmsnorm_out_bwd_dw(const RmsBwdArgs a, 
   }
 }
 
+// The weight's cotangent of long vectors, in a pass of its own after
+// k_rmsnorm_out_bwd: workgroup (head, 512 columns, token split) sums dy o r
+// over its split's tokens into part[split][head][col]. Each lane owns 8
+// columns, each of the 4 waves every 4th token; the waves' sums are then added
+// in order.
+template <typename T>
+__global__ __launch_bounds__(256) void k_rms_dw_part(const RmsBwdArgs a, int nsplit, int64_t per) {
+  constexpr int EPV = Io<T>::EPV;
+  __shared__ float red[4][512];
+  const int cchunks = (a.hd + 511) / 512;
+  const int sp = blockIdx.x % nsplit, rest = blockIdx.x / nsplit;
+  const int hh = rest / cchunks, c0 = (rest - hh * cchunks) * 512;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int col = c0 + 8 * lane;
+  const bool on = col < a.hd;   // hd is a multiple of 8: a lane's columns are all in or all out
+  const int64_t ntok = (int64_t)a.B * a.L;
+  const int64_t t0 = sp * per, t1 = t0 + per < ntok ? t0 + per : ntok;
+  float acc[8 / EPV][8] = {};
+  if (on) {
+    for (int64_t t = t0 + w; t < t1; t += 4) {
+      const int64_t b = t / a.L, l = t - b * a.L;
+      const T* dy = reinterpret_cast<const T*>(a.dy) + (t * a.H + hh) * a.hd + col;
+      const T* o = reinterpret_cast<const T*>(a.o) + ((b * a.H + hh) * a.L + l) * a.hd + col;
+      const float r = a.r[t * a.H + hh];
+#pragma unroll
+      for (int j = 0; j < 8 / EPV; ++j) {
+        float x[8], y[8];
+        Io<T>::load(dy + j * EPV, y);
+        Io<T>::load(o + j * EPV, x);
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) acc[j][e] += y[e] * x[e] * r;
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[w][8 * lane + e] = acc[e / EPV][e % EPV];
+  __syncthreads();
+  if (w == 0 && on) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      a.part[((int64_t)sp * a.H + hh) * a.hd + col + e] =
+          (red[0][8 * lane + e] + red[1][8 * lane + e]) + (red[2][8 * lane + e] + red[3][8 * lane + e]);
+  }
+}
+
 // dweight = the splits' partials: workgroup of 32 columns, 8 threads a column
 // each over an eighth of the splits, their sums then added in order (one
 // thread per column over all the splits was a chain of 256 loads: 71 us at
@@ -451,7 +498,8 @@ hipError_t launch_nv(const A& a, int nv, hipStream_t s) {
     case 2: KER<T, 2>::launch(a, s); break;
     case 4: KER<T, 4>::launch(a, s); break;
     case 8: KER<T, 8>::launch(a, s); break;
-    default: KER<T, 16>::launch(a, s); break;
+    default:   // fp32 only: 4096 16-bit elements are 8 accesses per lane
+      if constexpr (sizeof(T) == 4) KER<T, 16>::launch(a, s);
   }
   return hipGetLastError();
 }
@@ -492,7 +540,7 @@ template <typename T, int NV> struct RmsBwdK {
   }
 };
 
-// hd <= 4096: at most 1024 accesses of 16 bytes per vector, 16 per lane
+// hd <= 4096: at most 1024 accesses of 16 bytes per vector, 16 per lane (16 bits: 512, 8)
 int round_nv(int nv) { return nv <= 1 ? 1 : nv <= 2 ? 2 : nv <= 4 ? 4 : nv <= 8 ? 8 : 16; }
 
 }  // namespace
@@ -505,27 +553,51 @@ hipError_t launch_prologue_bwd(PrologueBwdArgs a, bool io_bf16, hipStream_t s) {
   return io_bf16 ? launch_nv<PrologueBwdK, __bf16>(a, nv, s) : launch_nv<PrologueBwdK, float>(a, nv, s);
 }
 
-// Token splits whose partial sums the workspace has room for.
-int rms_dw_splits(int B, int64_t L, int H, int hd) {
-  const int64_t ntok = (int64_t)B * L, tiles = (int64_t)H * ((hd + 511) / 512);
-  int64_t sp = (2048 + tiles - 1) / tiles;
-  if (sp > 256) sp = 256;
-  if (sp > ntok) sp = ntok;
-  return (int)(sp < 1 ? 1 : sp);
+// How the reverse of the output norm sums the weight's cotangent, and the
+// workspace it takes. Vectors of at most 4 accesses per lane (hd <= 2048 in 16
+// bits, 1024 in fp32) take one pass that holds its columns' sums in registers,
+// about 2048 workgroups of (head, token split). Longer ones would need so many
+// registers (one wave per SIMD) and so long partials that too few workgroups
+// are left: they take a pass of their own, split over the columns too. One
+// pass against two, [1, 16, 2048, d]: bf16 d = 2048 124 and 140 us, 2560 218
+// and 195; fp32 d = 1536 252 and 196 us, 4096 809 and 517.
+RmsDwPlan rms_dw_plan(int B, int64_t L, int H, int hd, bool io_bf16) {
+  RmsDwPlan p{};
+  int group, nv;
+  io_shape(hd, io_bf16 ? 2 : 4, group, nv);
+  const int64_t ntok = (int64_t)B * L, n = (int64_t)H * hd, tiles = (int64_t)H * ((hd + 511) / 512);
+  // the two passes: about 2048 workgroups of (head, 512 columns, token split)
+  const int64_t two = std::max<int64_t>(1, std::min<int64_t>({(2048 + tiles - 1) / tiles, 256, ntok}));
+  p.r_floats = (ntok * H + 63) / 64 * 64;   // each vector's r
+  p.floats = p.r_floats + two * n;
+  p.one_pass = nv <= 4;
+  if (p.one_pass) {   // a round of its groups per workgroup at least, as many as the same room holds partials
+    const int64_t ng = 256 / group;
+    const int64_t want = std::min<int64_t>((2048 + H - 1) / H, (ntok + ng - 1) / ng);
+    p.nsplit = std::max<int64_t>(1, std::min<int64_t>(want, p.floats / n));
+  } else {
+    p.nsplit = two;
+  }
+  p.per = std::max<int64_t>(1, (ntok + p.nsplit - 1) / p.nsplit);
+  if (p.one_pass) p.nsplit = (ntok + p.per - 1) / p.per;
+  return p;
 }
 
 template <typename T, int NV> struct RmsBwdDwK {
   static void launch(const RmsBwdArgs& a, hipStream_t s) {
-    // about 2048 workgroups of one head's tokens each, a round of its groups
-    // at least, as many as there is room for partial sums
-    const int64_t ntok = (int64_t)a.B * a.L, ng = 256 / a.group;
-    const int64_t want = std::min<int64_t>((2048 + a.H - 1) / a.H, (ntok + ng - 1) / ng);
-    int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>(want, a.part_room / ((int64_t)a.H * a.hd)));
-    const int64_t per = (ntok + nsplit - 1) / nsplit;
-    nsplit = (ntok + per - 1) / per;
+    const RmsDwPlan p = rms_dw_plan(a.B, a.L, a.H, a.hd, sizeof(T) == 2);
     const int64_t n = (int64_t)a.H * a.hd;
-    k_rmsnorm_out_bwd_dw<T, NV><<<(unsigned)(nsplit * a.H), 256, (size_t)ng * a.hd * 4, s>>>(a, per);
-    k_rms_dw_sum<<<(unsigned)((n + 31) / 32), 256, 0, s>>>(a.part, a.dweight, (int)nsplit, n);
+    RmsBwdArgs b = a;
+    if constexpr (NV <= 4) {
+      b.part = a.work;
+      k_rmsnorm_out_bwd_dw<T, NV><<<(unsigned)(p.nsplit * a.H), 256, (size_t)(256 / a.group) * a.hd * 4, s>>>(b, p.per);
+    } else {
+      b.r = a.work;
+      b.part = a.work + p.r_floats;
+      RmsBwdK<T, NV>::launch(b, s);
+      k_rms_dw_part<T><<<(unsigned)(p.nsplit * a.H * ((a.hd + 511) / 512)), 256, 0, s>>>(b, (int)p.nsplit, p.per);
+    }
+    k_rms_dw_sum<<<(unsigned)((n + 31) / 32), 256, 0, s>>>(b.part, a.dweight, (int)p.nsplit, n);
   }
 };
 

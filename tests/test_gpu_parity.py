@@ -1311,6 +1311,27 @@ def test_output_rmsnorm_weight_cotangent_splits(B, H, L, d, io):
     assert rel(dw.cpu().numpy(), rdw) <= 1e-5
 
 
+@pytest.mark.parametrize("io,d", [("fp32", 1024), ("fp32", 1032), ("bf16", 2048), ("bf16", 2080)])
+def test_output_rmsnorm_weight_cotangent_long_vectors(io, d):
+    # either side of the length at which the weight's cotangent takes a pass of
+    # its own: token splits and columns that 512 does not divide
+    B, H, L = 2, 3, 150
+    rng = np.random.default_rng(97 + d)
+    from lact_synth import round_to_bf16
+    rnd = round_to_bf16 if io == "bf16" else (lambda a: a)
+    o = rnd(rng.standard_normal((B, H, L, d), dtype=np.float32))
+    dy = rnd(rng.standard_normal((B, L, H, d), dtype=np.float32))
+    w = rng.standard_normal((H, d), dtype=np.float32)
+    dt = torch.bfloat16 if io == "bf16" else torch.float32
+    print(f"[gpu] rmsnorm backward long vectors io={io} B={B} H={H} L={L} d={d}", flush=True)
+    d_o, dw = P.rmsnorm_out_backward(torch.from_numpy(o).to("cuda", dt), torch.from_numpy(dy).to("cuda", dt),
+                                     torch.from_numpy(w).cuda())
+    torch.cuda.synchronize()
+    rdo, rdw = O.rmsnorm_out_vjp(o.reshape(B * H, L, d), B, H, dy, w)
+    assert rel(d_o.float().cpu().numpy().reshape(B * H, L, d), rdo) <= TOL[io]
+    assert rel(dw.cpu().numpy(), rdw) <= 1e-5
+
+
 def test_output_rmsnorm_backward_lm_tokens():
     # the LM head layout (B = H = 4, d = 512) over 4096 tokens: the weight's
     # cotangent sums 16384 vectors per head in token splits
