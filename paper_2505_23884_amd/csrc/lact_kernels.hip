@@ -2541,7 +2541,8 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   // (TC). It comes through LDS (all of it: the padded fp32 matrix takes the
   // three buffers), so that lanes read whole rows: straight from the tile
   // layout each lane took 16 bytes of another row, 11.9 us of a workgroup's 49.
-  // 16-byte chunks are XORed with the row, for the reads down the rows.
+  // 16-byte chunks are XORed with the row, for the reads down the rows. Rows past
+  // the matrix (both dimensions are multiples of 32) don't take part.
   constexpr int WM3 = TALL ? 2 : 4, WN3 = TALL ? 4 : 2;   // waves: 64 x 64 each
   const int r3 = (w / WN3) * 64, c3 = (w % WN3) * 64;
   constexpr int C4 = SC / 4;   // 16-byte chunks per fp32 row
@@ -2552,28 +2553,38 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   const float* xin = a.src + slot * a.ystride;
   f32x16_t x32[2][2];
   {
+    // every split's loads go out together, from element 0 outside the matrix (a
+    // load under a condition of its own waits for its sum: 3.6 us a split. [1,
+    // 1, 1024, 128], h = 256, 4 splits: 110 -> 102 us; d = h = 32, with the rows
+    // past the matrix left out: 81 -> 77 us; bitwise the same)
     float4 v[16];
+    auto at = [&](int i, bool& in) {
+      const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
+      in = row < sr && c < sc;
+      return in ? row * sc + c : 0;
+    };
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
-      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (row < sr && c < sc) v[i] = *reinterpret_cast<const float4*>(xin + (int64_t)row * sc + c);
+      bool in;
+      const float4 p = *reinterpret_cast<const float4*>(xin + at(i, in));
+      v[i] = in ? p : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     for (int sp = 1; sp < a.nsplit; ++sp) {
       const float* xp = xin + sp * a.part_split;
+      float4 p[16];
+      bool in;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) p[i] = *reinterpret_cast<const float4*>(xp + at(i, in));
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
-        if (row < sr && c < sc) {
-          const float4 p = *reinterpret_cast<const float4*>(xp + (int64_t)row * sc + c);
-          v[i] = make_float4(v[i].x + p.x, v[i].y + p.y, v[i].z + p.z, v[i].w + p.w);
-        }
+        at(i, in);
+        if (in) v[i] = make_float4(v[i].x + p[i].x, v[i].y + p[i].y, v[i].z + p[i].z, v[i].w + p[i].w);
       }
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int f = i * 512 + tid;
-      *f32_at(f / C4, f % C4) = v[i];
+      if (i * (512 / C4) < sr) *f32_at(f / C4, f % C4) = v[i];
     }
   }
   __syncthreads();
@@ -2582,10 +2593,11 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni) {
       const int c = c3 + ni * 32 + (lane & 31);
+      const bool in = c3 + ni * 32 < sr;   // the 32 rows are all the matrix's, or none
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int r = r3 + mi * 32 + 8 * g + 4 * half;
-        const float4 v = *f32_at(c, r >> 2);
+        const float4 v = in ? *f32_at(c, r >> 2) : make_float4(0.f, 0.f, 0.f, 0.f);
         x32[mi][ni][4 * g] = v.x;
         x32[mi][ni][4 * g + 1] = v.y;
         x32[mi][ni][4 * g + 2] = v.z;
@@ -2787,11 +2799,13 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
+      for (int ni = 0; ni < 2; ++ni) {
+        if (c3 + ni * 32 >= sr) continue;
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           *f32_at(c3 + ni * 32 + (lane & 31), (r3 + mi * 32 + 8 * g + 4 * half) >> 2) =
               make_float4(x32[mi][ni][4 * g], x32[mi][ni][4 * g + 1], x32[mi][ni][4 * g + 2], x32[mi][ni][4 * g + 3]);
+      }
     if constexpr (KEEP) {
       __syncthreads();
       float* out = keep->x32 + slot * sr * sc;
@@ -2824,12 +2838,14 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < SR; b += U * STEP) {
+      if (b >= sr) break;
       if (b) {
 #pragma unroll
         for (int i = 0; i < U; ++i) wv[i] = load(row0 + b + i * STEP);
       }
 #pragma unroll
       for (int i = 0; i < U; ++i) {
+        if (b + i * STEP >= sr) break;   // the whole workgroup's rows
         const int row = row0 + b + i * STEP;
         const float4 x = *f32_at(row, c4), o = wv[i];
         const float4 u = make_float4(o.x + x.x, o.y + x.y, o.z + x.z, o.w + x.w);
@@ -2837,6 +2853,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
         float su = cok ? u.x * u.x + u.y * u.y + u.z * u.z + u.w * u.w : 0.f;
 #pragma unroll
         for (int off = 1; off < C4; off <<= 1) {
+          if (4 * off >= sc) break;   // the other lanes hold zeros
           sw += __shfl_xor(sw, off, 64);
           su += __shfl_xor(su, off, 64);
         }

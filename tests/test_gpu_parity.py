@@ -736,6 +736,15 @@ def test_muon_small_wide_then_tall_in_one_launch():
     assert n_upd == 0
 
 
+@pytest.mark.parametrize("d,h", [(32, 32), (32, 256), (256, 32), (96, 160)])
+def test_muon_small_partly_filled(d, h):
+    # matrices that leave rows, columns or both of the one-workgroup kernel's
+    # 128 x 256 empty, the gradient in four split partials
+    cfg = CONFIGS["video"].with_(name="muon_small_part", B=1, H=2, d=d, h=h, n_kv=1123, n_q=1123, chunk=1123)
+    x = make_inputs(cfg, 17)
+    teacher_forced(cfg, x, [0, 1])
+
+
 def test_muon_small_gram_long_side_unfused():
     # Gram size 96 <= 128 but the long side 384 > 256: the per-product
     # Newton-Schulz launches with 128 x 128 tiles (not the one-workgroup kernel)
