@@ -37,6 +37,17 @@ int fwd_shape(bool narrow, bool bf16, int BH, int h, int64_t n, int segs) {
   return segs * BH * cdiv(h, t.rows) * cdiv(n, t.cols) <= 128 ? 2 : 0;
 }
 
+// Ordinary stores (FwdArgs::reread) for a forward's narrow first launch whose
+// outputs, `bytes` in all, take at most half of the 256 MiB last-level cache:
+// the second launch, short for d <= 128, then finds them there. Forward,
+// non-temporal against ordinary: [1, 3, 2048, 64], h = 544 (27 MB) 63 and 57
+// us; [1, 16, 9360, 128], h = 256, chunks of 3120 (102 MB) 300 and 283; 24
+// heads (153 MB) 422 and 411; 40 heads (256 MB) 645 and 649, with Muon 672 and
+// 701. Wider matrices ([1, 16, 8192, 512]: 882 and 893) and the backward's
+// replay, which writes three more arrays that are read much later ([1, 8, 9360,
+// 128]: 715 and 723), keep the non-temporal ones.
+bool fwd_reread(int64_t bytes) { return bytes <= ((int64_t)128 << 20); }
+
 // Shape-derived plan shared by lact_workspace_bytes and lact_forward.
 struct Plan {
   int BH, d, h;
@@ -382,6 +393,7 @@ int apply_rows(Ctx& c, int64_t s0, int64_t s1) {
     f.w1 = c.wop[0];
     f.w2 = c.wop[1];
     f.w3 = c.wop[2];
+    f.reread = fwd_reread(p.BH * n * p.h * p.esz);
     const double fl1 = 4.0 * p.BH * n * p.d * p.h;
     int rc = timed(LACT_KCLASS_FWD, fl1, c.s, [&] { return launch_fwd(f, p.bf16, c.s); });
     if (rc) return rc;
@@ -673,6 +685,7 @@ int update_chunk(Ctx& c, int64_t s0, int64_t s1, bool apply_too) {
   f.w1 = c.wop[0];
   f.w2 = c.wop[1];
   f.w3 = c.wop[2];
+  f.reread = fwd_reread((int64_t)(apply_too ? 4 : 3) * p.BH * n * p.h * p.esz);
   const double ffl = (apply_too ? 4.0 : 0.0) * p.BH * n * dh + 6.0 * p.BH * n * dh;
   int rc = timed(LACT_KCLASS_FWD, ffl, c.s, [&] { return launch_fwd(f, p.bf16, c.s); });
   if (rc) return rc;

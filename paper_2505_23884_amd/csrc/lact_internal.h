@@ -52,6 +52,7 @@ struct FwdArgs {
   Operand w2;           // d x h; the key forward reads it as an mn operand
   int narrow;           // 16-bit: 128 x 128 tiles, two workgroups per CU (1) or one with deeper stages (2);
                         // fp32: 64 x 64 tiles (1)
+  bool reread;          // 16-bit narrow == 1 without keep: ordinary stores of the outputs (fwd_reread)
 };
 
 // ---- second launch: apply GEMM-2 and/or the gradient contractions ---------

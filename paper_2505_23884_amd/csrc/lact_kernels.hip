@@ -1186,19 +1186,19 @@ __device__ __forceinline__ void stage_put(uint8_t* buf, int tok, int row, float 
 
 // Copy the staged tile to out (element (token 0, row 0) of the tile, ld
 // elements between tokens): tokens < ntok, rows < nrow (a multiple of 8).
-// The stores are non-temporal: a launch writes far more than an L2 holds, all
-// its workgroups at the same moments, and nothing of it is read before the
-// next launch; written through without staying in L2 the epilogues stall less
-// and the operands the other tiles share keep their lines (one process: video
-// forward 717 -> 685 us, LM shape backward 12424 -> 12162 us, NVS 256K 5627 ->
-// 5568 us, LM shape forward within its noise. The gradients' fp32 partials,
-// which the update reads back at once, stay ordinary stores: video 679 -> 688
-// us otherwise). reread: rows that a row kernel reads back in the very next
-// launch are stored plainly, so that it finds part of them cached (linear
-// forward and backward, 16001 tokens: 1883 -> 1866 us).
+// The stores are non-temporal where a launch writes more than the caches
+// hold, all its workgroups at the same moments: written through without
+// staying in L2 the epilogues stall less and the operands the other tiles share
+// keep their lines (one process: video backward 2532 -> 2483 us, LM shape
+// backward 12424 -> 12162, NVS 256K forward 5627 -> 5568. The gradients' fp32
+// partials, which the update reads back at once, stay ordinary stores: video
+// 679 -> 688 us otherwise). reread: ordinary stores, for rows that a row kernel
+// reads back in the very next launch (linear forward and backward, 16001
+// tokens: 1883 -> 1866 us) and narrow first launches that the caches hold
+// (fwd_reread in lact_api.hip).
 template <int R, int C, int THREADS, typename E = __bf16>
 __device__ __forceinline__ void stage_flush(const uint8_t* buf, E* out, int64_t ld, int64_t ntok, int64_t nrow,
-                                            bool reread = false) {
+                                            bool reread) {
   constexpr int CPR = R / 8, TOTAL = C * CPR;
   static_assert(CPR >= 16 && TOTAL % THREADS == 0, "staging shape");
   if (reread) {
@@ -1279,7 +1279,7 @@ __device__ __forceinline__ void update_epilogue_staged(const f32x16_t (&z1a)[K::
                                                        const f32x16_t (&z3a)[K::MI][K::NI],
                                                        const f32x16_t (&dda)[K::MI][K::NI], const FwdSeg& sg,
                                                        int inst, int64_t j0, int64_t i0, int64_t hrows,
-                                                       int64_t ntok, int h, uint8_t* smem) {
+                                                       int64_t ntok, int h, uint8_t* smem, bool reread) {
   constexpr int R = K::ROWS_A, C = K::ROWS_B;
   uint8_t* buf0 = smem;
   uint8_t* buf1 = smem + R * C * 2;
@@ -1310,8 +1310,8 @@ __device__ __forceinline__ void update_epilogue_staged(const f32x16_t (&z1a)[K::
           stage_put<R>(buf1, tok, row, z3a[mi][ni][r], z3a[mi][ni][r + 1], z3a[mi][ni][r + 2], z3a[mi][ni][r + 3]);
         }
     lds_barrier();
-    stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.keep[0]) + kt, h, ntok, hrows);
-    stage_flush<R, C, K::THREADS>(buf1, reinterpret_cast<__bf16*>(sg.keep[1]) + kt, h, ntok, hrows);
+    stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.keep[0]) + kt, h, ntok, hrows, reread);
+    stage_flush<R, C, K::THREADS>(buf1, reinterpret_cast<__bf16*>(sg.keep[1]) + kt, h, ntok, hrows, reread);
     lds_barrier();
 #pragma unroll
     for (int ni = 0; ni < K::NI; ++ni)
@@ -1324,7 +1324,7 @@ __device__ __forceinline__ void update_epilogue_staged(const f32x16_t (&z1a)[K::
                        dda[mi][ni][r + 2], dda[mi][ni][r + 3]);
         }
     lds_barrier();
-    stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.keep[2]) + kt, h, ntok, hrows);
+    stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.keep[2]) + kt, h, ntok, hrows, reread);
     lds_barrier();
   }
 #pragma unroll
@@ -1348,8 +1348,8 @@ __device__ __forceinline__ void update_epilogue_staged(const f32x16_t (&z1a)[K::
       }
   lds_barrier();
   const int64_t tile = inst * sg.out_inst + i0 * h + j0;
-  stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.out1) + tile, h, ntok, hrows);
-  stage_flush<R, C, K::THREADS>(buf1, reinterpret_cast<__bf16*>(sg.out2) + tile, h, ntok, hrows);
+  stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.out1) + tile, h, ntok, hrows, reread);
+  stage_flush<R, C, K::THREADS>(buf1, reinterpret_cast<__bf16*>(sg.out2) + tile, h, ntok, hrows, reread);
   lds_barrier();
 #pragma unroll
   for (int ni = 0; ni < K::NI; ++ni)
@@ -1367,7 +1367,7 @@ __device__ __forceinline__ void update_epilogue_staged(const f32x16_t (&z1a)[K::
         stage_put<R>(buf0, acc_col<K>(ni), hrow0 + mi * 32 + 8 * g, vb[0], vb[1], vb[2], vb[3]);
       }
   lds_barrier();
-  stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.out3) + tile, h, ntok, hrows);
+  stage_flush<R, C, K::THREADS>(buf0, reinterpret_cast<__bf16*>(sg.out3) + tile, h, ntok, hrows, reread);
 }
 
 // ===========================================================================
@@ -1402,6 +1402,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
   const int rr = bid - inst * per;
   const int d = args.d, h = args.h;
   const int lane = threadIdx.x & 63;
+  const bool reread = SHAPE == 1 && !KEEP && sizeof(T) == 2 ? args.reread : false;
 
   if (sg.kind == FWD_APPLY) {
     const int64_t j0 = (int64_t)(rr % sg.tiles_m) * KA::ROWS_A;   // hidden tile (fastest)
@@ -1431,7 +1432,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
           }
       lds_barrier();
       stage_flush<KA::ROWS_A, KA::ROWS_B, KA::THREADS>(smem, reinterpret_cast<__bf16*>(out) + i0 * h + j0, h, ntok,
-                                                         hrows);
+                                                         hrows, reread);
       return;
     }
 #pragma unroll
@@ -1474,7 +1475,8 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& args, uint8_t* smem) {
       static_assert(KU::NSTAGE * kSlot <= kSmem, "chained ring fits");
       mainloop_chain<T, KU, KD, kSlot>(smem, opz, d, az, opd, d, ad);
       static_assert(2 * KU::ROWS_A * KU::ROWS_B * 2 <= kSmem, "staging fits");
-      update_epilogue_staged<KU, KEEP>(az[0], az[1], ad[0], sg, inst, j0, i0, hrows, ntok, h, smem);
+      update_epilogue_staged<KU, KEEP>(az[0], az[1], ad[0], sg, inst, j0, i0, hrows, ntok, h, smem,
+                                         reread);
     } else {
       const View ops[5] = {w1, w3, w2, kk, vv};
       Acc<KU> acc;
