@@ -3681,13 +3681,21 @@ __device__ __forceinline__ float lanes_sum(float v, int G) {
   return v;
 }
 
-// Lanes per token for rows of len elements: halved from 64 while the last pass
-// over the row leaves a fifth of all lanes idle (h = 256 in 16 bits: 32 lanes,
-// two tokens per wave; 768: three passes of 32 lanes, not one and a half of 64).
-int row_group(int64_t len, bool io_bf16) {
+// Lanes per token for `rows` rows of len elements. Rows of up to 64 16-byte
+// vectors: halved from 64 while the last pass over the row leaves a fifth of all
+// lanes idle, to at most three passes, and while the half still gives 4
+// workgroups per CU (with few tokens the passes of a row, one after the other,
+// are the launch's time). Backward in 64 lanes against these: h = 96 (8 lanes)
+// 570 and 474 us, 160 (8) 698 and 643, video (32) 1739 and 1659. Longer
+// rows: 64 lanes (h = 544 in 16 lanes and 5 passes 1052 us, in 64 and 2 1034;
+// 768 in 32 and 3 2820, in 64 and 2 2809).
+int row_group(int64_t len, int64_t rows, bool io_bf16) {
   const int64_t nv = len / (io_bf16 ? 8 : 4);
   int G = 64;
-  while (G > 8 && (nv + G - 1) / G * G * 4 >= nv * 5) G /= 2;
+  if (nv > 64) return G;
+  while (G > 8 && (nv + G - 1) / G * G * 4 >= nv * 5 && (nv + G / 2 - 1) / (G / 2) <= 3 &&
+         rows * (G / 2) >= 1024 * 256)
+    G /= 2;
   return G;
 }
 
@@ -4210,7 +4218,7 @@ hipError_t launch_lin_tokens(const void* V, const float* eta, void* dv, float* d
                              int64_t tok_inst, int64_t eta_inst, bool io_bf16, hipStream_t s) {
   const int64_t rows = (int64_t)BH * n;
   if (rows <= 0) return hipSuccess;
-  const int G = row_group(d, io_bf16);
+  const int G = row_group(d, rows, io_bf16);
   const int64_t per = (n + 256 / G - 1) / (256 / G), nblk = per * BH;
   const unsigned blocks = (unsigned)(nblk < ((int64_t)1 << 20) ? nblk : ((int64_t)1 << 20));
   if (io_bf16)
@@ -4225,7 +4233,7 @@ hipError_t launch_lin_tokens(const void* V, const float* eta, void* dv, float* d
 hipError_t launch_swiglu_rows(const SwigluRowsArgs& a, bool io_bf16, hipStream_t s) {
   const int64_t rows = (int64_t)a.BH * a.n;
   if (rows <= 0) return hipSuccess;
-  const int G = row_group(a.h, io_bf16);
+  const int G = row_group(a.h, rows, io_bf16);
   const int64_t per = (a.n + 256 / G - 1) / (256 / G), nblk = per * a.BH;
   const unsigned blocks = (unsigned)(nblk < ((int64_t)1 << 20) ? nblk : ((int64_t)1 << 20));
   if (io_bf16) k_swiglu_rows<__bf16><<<blocks, 256, 0, s>>>(a, G, per, nblk);
@@ -4238,7 +4246,7 @@ hipError_t launch_swiglu_apply_rows(const void* Z1, const void* Z3, const void* 
                                     hipStream_t s) {
   const int64_t rows = (int64_t)BH * n;
   if (rows <= 0) return hipSuccess;
-  const int G = row_group(h, io_bf16);
+  const int G = row_group(h, rows, io_bf16);
   const int64_t per = (n + 256 / G - 1) / (256 / G), nblk = per * BH;
   const unsigned blocks = (unsigned)(nblk < ((int64_t)1 << 20) ? nblk : ((int64_t)1 << 20));
   auto go = [&](auto tag) {

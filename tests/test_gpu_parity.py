@@ -1774,6 +1774,21 @@ def test_backward_row_groups(io, d, h, linear):
         check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
 
 
+@pytest.mark.parametrize("io,d,h,linear", [
+    ("bf16", 32, 32, 0), ("bf16", 32, 96, 0), ("bf16", 32, 160, 0), ("bf16", 32, 256, 0), ("bf16", 32, 288, 0),
+    ("bf16", 160, 160, 1), ("fp32", 8, 40, 0)])
+def test_backward_row_groups_of_many_tokens(io, d, h, linear):
+    # tokens enough for 8, 16 and 32 lanes per token (rows of 4, 12, 20, 32, 36
+    # and 10 16-byte vectors, one to three passes)
+    base = CONFIGS["lm32k"] if io == "bf16" else CONFIGS["tiny_fp32"]
+    cfg = base.with_(name="bwd_rows_many", B=1, H=41, d=d, h=h, n_kv=811, n_q=811, chunk=811, order=0, linear=linear)
+    x, ct = make_inputs(cfg, 79), make_cotangents(cfg, 79)
+    if linear:
+        check_linear_bwd(cfg, x, ct, run_gpu_linear_bwd(cfg, x, ct))
+    else:
+        check_swiglu_bwd(cfg, x, ct, run_gpu_swiglu_bwd(cfg, x, ct))
+
+
 def test_swiglu_backward_narrow_tiles_without_tail():
     # d = 128 (the narrow bf16 tiles), the video head shape, n_q == n_kv, a last chunk of one token
     cfg = CONFIGS["video"].with_(name="swiglu_bwd_narrow", B=1, H=3, n_kv=513, n_q=513, chunk=128, use_muon=0)
