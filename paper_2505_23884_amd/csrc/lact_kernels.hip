@@ -4164,9 +4164,14 @@ hipError_t launch_ns_sym(NsSymArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 256 x 256 tiles where the slots' side fills them (as the forward's update product)
+// 256 x 256 tiles where the slots fill more than half of the 256 CUs with them,
+// else 128 x 128, four times as many (bitwise the same). Backward of the linear
+// fast weight with Muon, one chunk, big against small tiles: 1 slot of 256 x 256
+// 819 and 693 us, 32 of 512 x 512 (128 tiles) 1750 and 1645, 48 of 320 x 320
+// (75 tiles' worth) 1368 and 1266; 16 of 768 x 768 (144) 2106 and 2171, 48 of
+// 512 x 512 (192) 2182 and 2268.
 hipError_t launch_ns_dx(NsDxArgs a, hipStream_t s) {
-  const bool big = a.m > 128;
+  const bool big = a.m > 128 && (int64_t)a.S * a.m * a.n > 128 * 256 * 256;
   const int64_t tr = big ? tile_rows<KNsTY16B>() : tile_rows<KNsTY16S>();
   const int64_t n = a.S * ((a.n + tr - 1) / tr) * ((a.m + tr - 1) / tr);
   if (n <= 0) return hipSuccess;
