@@ -3683,18 +3683,19 @@ __device__ __forceinline__ float lanes_sum(float v, int G) {
 
 // Lanes per token for `rows` rows of len elements. Rows of up to 64 16-byte
 // vectors: halved from 64 while the last pass over the row leaves a fifth of all
-// lanes idle, to at most three passes, and while the half still gives 4
-// workgroups per CU (with few tokens the passes of a row, one after the other,
-// are the launch's time). Backward in 64 lanes against these: h = 96 (8 lanes)
-// 570 and 474 us, 160 (8) 698 and 643, video (32) 1739 and 1659. Longer
+// lanes idle and the half needs no more passes, or at most three and 4
+// workgroups per CU are left (with few tokens the passes of a row, one after the
+// other, are the launch's time). Backward in 64 lanes against these: h = 96 (8
+// lanes) 570 and 474 us, 160 (8) 698 and 643, video (32) 1739 and 1659. Longer
 // rows: 64 lanes (h = 544 in 16 lanes and 5 passes 1052 us, in 64 and 2 1034;
 // 768 in 32 and 3 2820, in 64 and 2 2809).
 int row_group(int64_t len, int64_t rows, bool io_bf16) {
   const int64_t nv = len / (io_bf16 ? 8 : 4);
+  auto passes = [&](int64_t G) { return (nv + G - 1) / G; };
   int G = 64;
   if (nv > 64) return G;
-  while (G > 8 && (nv + G - 1) / G * G * 4 >= nv * 5 && (nv + G / 2 - 1) / (G / 2) <= 3 &&
-         rows * (G / 2) >= 1024 * 256)
+  while (G > 8 && passes(G) * G * 4 >= nv * 5 &&
+         (passes(G / 2) == passes(G) || (passes(G / 2) <= 3 && rows * (G / 2) >= 1024 * 256)))
     G /= 2;
   return G;
 }
