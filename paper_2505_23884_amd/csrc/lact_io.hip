@@ -556,11 +556,13 @@ hipError_t launch_prologue_bwd(PrologueBwdArgs a, bool io_bf16, hipStream_t s) {
 // How the reverse of the output norm sums the weight's cotangent, and the
 // workspace it takes. Vectors of at most 4 accesses per lane (hd <= 2048 in 16
 // bits, 1024 in fp32) take one pass that holds its columns' sums in registers,
-// about 2048 workgroups of (head, token split). Longer ones would need so many
-// registers (one wave per SIMD) and so long partials that too few workgroups
-// are left: they take a pass of their own, split over the columns too. One
-// pass against two, [1, 16, 2048, d]: bf16 d = 2048 124 and 140 us, 2560 218
-// and 195; fp32 d = 1536 252 and 196 us, 4096 809 and 517.
+// up to 2048 workgroups of (head, token split), if more than two accesses leave
+// at least 2 workgroups per CU. Longer ones would need so many registers (one
+// wave per SIMD) and so long partials that too few workgroups are left: they
+// take a pass of their own, split over the columns too. One pass against two,
+// [1, 16, 2048, d]: bf16 d = 2048 124 and 140 us, 2560 218 and 195; fp32
+// d = 1536 252 and 196 us, 4096 809 and 517; one head, [1, 1, 32000, 1024]:
+// bf16 72 and 71, fp32 200 and 117 (287 workgroups).
 RmsDwPlan rms_dw_plan(int B, int64_t L, int H, int hd, bool io_bf16) {
   RmsDwPlan p{};
   int group, nv;
@@ -570,14 +572,11 @@ RmsDwPlan rms_dw_plan(int B, int64_t L, int H, int hd, bool io_bf16) {
   const int64_t two = std::max<int64_t>(1, std::min<int64_t>({(2048 + tiles - 1) / tiles, 256, ntok}));
   p.r_floats = (ntok * H + 63) / 64 * 64;   // each vector's r
   p.floats = p.r_floats + two * n;
-  p.one_pass = nv <= 4;
-  if (p.one_pass) {   // a round of its groups per workgroup at least, as many as the same room holds partials
-    const int64_t ng = 256 / group;
-    const int64_t want = std::min<int64_t>((2048 + H - 1) / H, (ntok + ng - 1) / ng);
-    p.nsplit = std::max<int64_t>(1, std::min<int64_t>(want, p.floats / n));
-  } else {
-    p.nsplit = two;
-  }
+  // one pass: a round of its groups per workgroup at least, as many as the same room holds partials
+  const int64_t ng = 256 / group, want = std::min<int64_t>((2048 + H - 1) / H, (ntok + ng - 1) / ng);
+  const int64_t one = std::max<int64_t>(1, std::min<int64_t>(want, p.floats / n));
+  p.one_pass = nv <= 2 || (nv <= 4 && one * H >= 512);
+  p.nsplit = p.one_pass ? one : two;
   p.per = std::max<int64_t>(1, (ntok + p.nsplit - 1) / p.nsplit);
   if (p.one_pass) p.nsplit = (ntok + p.per - 1) / p.per;
   return p;
@@ -589,9 +588,13 @@ template <typename T, int NV> struct RmsBwdDwK {
     const int64_t n = (int64_t)a.H * a.hd;
     RmsBwdArgs b = a;
     if constexpr (NV <= 4) {
-      b.part = a.work;
-      k_rmsnorm_out_bwd_dw<T, NV><<<(unsigned)(p.nsplit * a.H), 256, (size_t)(256 / a.group) * a.hd * 4, s>>>(b, p.per);
-    } else {
+      if (p.one_pass) {
+        b.part = a.work;
+        k_rmsnorm_out_bwd_dw<T, NV>
+            <<<(unsigned)(p.nsplit * a.H), 256, (size_t)(256 / a.group) * a.hd * 4, s>>>(b, p.per);
+      }
+    }
+    if (!p.one_pass) {
       b.r = a.work;
       b.part = a.work + p.r_floats;
       RmsBwdK<T, NV>::launch(b, s);

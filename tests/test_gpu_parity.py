@@ -1320,11 +1320,13 @@ def test_output_rmsnorm_weight_cotangent_splits(B, H, L, d, io):
     assert rel(dw.cpu().numpy(), rdw) <= 1e-5
 
 
-@pytest.mark.parametrize("io,d", [("fp32", 1024), ("fp32", 1032), ("bf16", 2048), ("bf16", 2080)])
-def test_output_rmsnorm_weight_cotangent_long_vectors(io, d):
-    # either side of the length at which the weight's cotangent takes a pass of
-    # its own: token splits and columns that 512 does not divide
-    B, H, L = 2, 3, 150
+@pytest.mark.parametrize("io,d,H,L", [("fp32", 1024, 16, 256), ("fp32", 1024, 3, 150), ("fp32", 1032, 16, 256),
+                                      ("bf16", 2048, 16, 256), ("bf16", 2048, 3, 150), ("bf16", 2080, 16, 256)])
+def test_output_rmsnorm_weight_cotangent_long_vectors(io, d, H, L):
+    # either side of the length, and of the number of workgroups, at which the
+    # weight's cotangent takes a pass of its own: token splits and columns that
+    # 512 does not divide
+    B = 1
     rng = np.random.default_rng(97 + d)
     from lact_synth import round_to_bf16
     rnd = round_to_bf16 if io == "bf16" else (lambda a: a)
