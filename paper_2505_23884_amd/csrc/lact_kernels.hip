@@ -2543,7 +2543,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   // (TC). It comes through LDS (all of it: the padded fp32 matrix takes the
   // three buffers), so that lanes read whole rows: straight from the tile
   // layout each lane took 16 bytes of another row, 11.9 us of a workgroup's 49.
-  // 16-byte chunks are XORed with the row, for the reads down the rows. Rows past
+  // 16-byte chunks are XORed with the row, for the reads down the rows. Blocks past
   // the matrix (both dimensions are multiples of 32) don't take part.
   constexpr int WM3 = TALL ? 2 : 4, WN3 = TALL ? 4 : 2;   // waves: 64 x 64 each
   const int r3 = (w / WN3) * 64, c3 = (w % WN3) * 64;
@@ -2555,38 +2555,35 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
   const float* xin = a.src + slot * a.ystride;
   f32x16_t x32[2][2];
   {
-    // every split's loads go out together, from element 0 outside the matrix (a
-    // load under a condition of its own waits for its sum: 3.6 us a split. [1,
-    // 1, 1024, 128], h = 256, 4 splits: 110 -> 102 us; d = h = 32, with the rows
-    // past the matrix left out: 81 -> 77 us; bitwise the same)
+    // 16-byte chunk i * 512 + tid of the matrix; every split's loads go out
+    // together (a load under a condition of its own waits for its sum: 3.6 us a
+    // split. [1, 1, 1024, 128], h = 256, 4 splits: 110 -> 102 us; d = h = 32, with
+    // what lies past the matrix left out: 81 -> 77 us; bitwise the same)
+    const int n4 = sr * sc / 4, sc4 = sc / 4;
+    const float rsc4 = 1.0f / (float)sc4;
     float4 v[16];
-    auto at = [&](int i, bool& in) {
-      const int f = i * 512 + tid, row = f / C4, c = (f % C4) * 4;
-      in = row < sr && c < sc;
-      return in ? row * sc + c : 0;
-    };
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      bool in;
-      const float4 p = *reinterpret_cast<const float4*>(xin + at(i, in));
-      v[i] = in ? p : make_float4(0.f, 0.f, 0.f, 0.f);
+      const int f = i * 512 + tid;
+      v[i] = reinterpret_cast<const float4*>(xin)[f < n4 ? f : 0];   // element 0 past the matrix: dropped below
     }
     for (int sp = 1; sp < a.nsplit; ++sp) {
-      const float* xp = xin + sp * a.part_split;
+      const float4* xp = reinterpret_cast<const float4*>(xin + sp * a.part_split);
       float4 p[16];
-      bool in;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) p[i] = *reinterpret_cast<const float4*>(xp + at(i, in));
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        at(i, in);
-        if (in) v[i] = make_float4(v[i].x + p[i].x, v[i].y + p[i].y, v[i].z + p[i].z, v[i].w + p[i].w);
+        const int f = i * 512 + tid;
+        p[i] = xp[f < n4 ? f : 0];
       }
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        v[i] = make_float4(v[i].x + p[i].x, v[i].y + p[i].y, v[i].z + p[i].z, v[i].w + p[i].w);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int f = i * 512 + tid;
-      if (i * (512 / C4) < sr) *f32_at(f / C4, f % C4) = v[i];
+      const int row = (int)(((float)f + 0.5f) * rsc4);   // f / sc4 (f < 2^13, so the product is never off by a whole)
+      if (f < n4) *f32_at(row, f - row * sc4) = v[i];
     }
   }
   __syncthreads();
@@ -2595,7 +2592,7 @@ __device__ __forceinline__ void ns_fused_body(const NsFusedArgs& a, int q, uint8
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni) {
       const int c = c3 + ni * 32 + (lane & 31);
-      const bool in = c3 + ni * 32 < sr;   // the 32 rows are all the matrix's, or none
+      const bool in = c3 + ni * 32 < sr && r3 + mi * 32 < sc;   // the whole 32 x 32 block, or none of it
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int r = r3 + mi * 32 + 8 * g + 4 * half;
