@@ -113,10 +113,14 @@ int check_desc(const lact_desc* d) {
 // quarter of the fp32 MFMA time per tile (a 128 x 128 tile multiplies 16 K in
 // 2048 clocks per accumulator, mostly padding where d or h is 64) decides the
 // launch. [1, 2, 1024, 64], h = 64, chunks of 256: first launch 24 -> 7 us,
-// second 48 -> 9 us (with the gradient split every 64 tokens).
-bool small_tiles(int BH, int h, int64_t T) {
+// second 48 -> 9 us (with the gradient split every 64 tokens). In the linear
+// fast weight's forward the gradient tiles run in the same launch and fill it
+// earlier for d > 128 ([1, 1, 8192, 512], chunks of 2048, 64 tiles: 231 us in
+// large tiles, 255 in small ones, chunks of 1536, 48 tiles: 227 and 208; [1, 2,
+// 65536, 256], chunks of 2048, 64 tiles: 1291 and 1371).
+bool small_tiles(int BH, int h, int64_t T, bool linear_fwd = false) {
   const TileShape t = fwd_tile(FWD_APPLY, false, false);
-  return BH * cdiv(h, t.rows) * cdiv(std::max<int64_t>(T, 1), t.cols) <= 64;
+  return BH * cdiv(h, t.rows) * cdiv(std::max<int64_t>(T, 1), t.cols) <= (linear_fwd && h > 128 ? 48 : 64);
 }
 
 Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
@@ -132,7 +136,7 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   p.C = std::min<int64_t>(dsc->chunk, dsc->n_kv);
   const int64_t tail = dsc->n_q - dsc->n_kv;
   const int64_t tail_rows = std::min<int64_t>(tail, std::max<int64_t>(p.C, 65536));
-  p.narrow = p.bf16 ? p.d <= 128 : small_tiles(p.BH, p.h, std::max(p.C, tail_rows));
+  p.narrow = p.bf16 ? p.d <= 128 : small_tiles(p.BH, p.h, std::max(p.C, tail_rows), p.linear);
   // Small matrices with Muon (one fused Newton-Schulz workgroup each) and the
   // narrow tile shapes: the output tiles of a chunk's apply run in the
   // Newton-Schulz launch, on the CUs its one workgroup per matrix leaves idle,
@@ -257,6 +261,24 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   return p;
 }
 
+// Tiles of an output launch of the linear fast weight over n token rows: the
+// plan's with 16-bit I/O, with fp32 I/O by the launch itself (a long apply after
+// short chunks, or short chunks before a long tail: backward [1, 4, 34096, 512],
+// 4096 key tokens in chunks of 256, 3883 -> 3592 us), for d <= 64, where large
+// tiles are half padding, by the chunk.
+bool lin_narrow(const Plan& p, int64_t n) {
+  return p.bf16 ? p.narrow : small_tiles(p.BH, p.d, p.d <= 64 ? p.C : n);
+}
+// The gradients of nch chunks in one launch, two products each: small tiles only
+// while the large ones would not fill the 256 CUs (backward [1, 4, 16384, 512],
+// chunks of 256, 8192 large tiles: 4405 us in small ones, 4311 in large; [1, 1,
+// 24576, 128], chunks of 8192, 6 tiles: 489 and 772).
+bool lin_grads_narrow(const Plan& p, int64_t nch) {
+  if (p.bf16) return p.narrow;
+  const int64_t t = cdiv(p.d, bwd_tile(BWD_GRAD2, false, false).rows);
+  return small_tiles(p.BH, p.d, p.C) && (p.d <= 64 || 2 * nch * p.BH * t * t < 256);
+}
+
 bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }
 
 // ---------------------------------------------------------------- timing
@@ -351,10 +373,11 @@ int apply_rows(Ctx& c, int64_t s0, int64_t s1) {
     for (int64_t a = s0; a < s1; a += 65536) {   // bounds the tile count of a launch
       const int64_t n = std::min<int64_t>(65536, s1 - a);
       BwdArgs b{};
+      b.narrow = lin_narrow(p, n);
       BwdSeg& o = b.seg[0];
       o.kind = BWD_OUT;
-      o.tiles_m = (int)cdiv(p.d, bwd_tile(BWD_OUT, p.bf16, p.narrow).rows);
-      o.tiles_n = (int)cdiv(n, bwd_tile(BWD_OUT, p.bf16, p.narrow).cols);
+      o.tiles_m = (int)cdiv(p.d, bwd_tile(BWD_OUT, p.bf16, b.narrow).rows);
+      o.tiles_n = (int)cdiv(n, bwd_tile(BWD_OUT, p.bf16, b.narrow).cols);
       o.nsplit = 1;
       o.nblocks = p.BH * o.tiles_m * o.tiles_n;
       o.rows = n;
@@ -366,7 +389,6 @@ int apply_rows(Ctx& c, int64_t s0, int64_t s1) {
       b.total_blocks = o.nblocks;
       b.d = p.d;
       b.h = p.d;
-      b.narrow = p.narrow;
       const int rc = timed(LACT_KCLASS_BWD, 2.0 * p.BH * n * p.d * p.d, c.s,
                            [&] { return launch_bwd(b, p.bf16, c.s); });
       if (rc) return rc;
@@ -1659,8 +1681,9 @@ int bwd_layout(const lact_desc* dsc, BwdLayout* L, bool mom = false, int64_t nup
 
 // One GRAD2 segment: out[m][j] = sum over rows [0, n) of a[., m] b[., j], in
 // splits of split_len tokens (fp32, BH d^2 floats between splits).
-void lin_grad_seg(BwdSeg& g, const Plan& p, Operand a, Operand b, float* out, int64_t n, int64_t split_len) {
-  const TileShape t = bwd_tile(BWD_GRAD2, p.bf16, p.narrow);
+void lin_grad_seg(BwdSeg& g, const Plan& p, Operand a, Operand b, float* out, int64_t n, int64_t split_len,
+                  bool narrow) {
+  const TileShape t = bwd_tile(BWD_GRAD2, p.bf16, narrow);
   g.kind = BWD_GRAD2;
   g.tiles_m = (int)cdiv(p.d, t.rows);
   g.tiles_n = (int)cdiv(p.d, t.cols);
@@ -1678,8 +1701,9 @@ void lin_grad_seg(BwdSeg& g, const Plan& p, Operand a, Operand b, float* out, in
 
 // One OUT segment: out[t][m] = sum_e a[t][e] b[m][e] for rows t in [0, n)
 // (rows of out d apart, instances out_inst apart).
-void lin_out_seg(BwdSeg& o, const Plan& p, Operand a, Operand b, void* out, int64_t out_inst, int64_t n) {
-  const TileShape t = bwd_tile(BWD_OUT, p.bf16, p.narrow);
+void lin_out_seg(BwdSeg& o, const Plan& p, Operand a, Operand b, void* out, int64_t out_inst, int64_t n,
+                 bool narrow) {
+  const TileShape t = bwd_tile(BWD_OUT, p.bf16, narrow);
   o.kind = BWD_OUT;
   o.tiles_m = (int)cdiv(p.d, t.rows);
   o.tiles_n = (int)cdiv(n, t.cols);
@@ -1692,13 +1716,13 @@ void lin_out_seg(BwdSeg& o, const Plan& p, Operand a, Operand b, void* out, int6
   o.out_inst = out_inst;
 }
 
-int lin_launch(const Plan& p, hipStream_t s, BwdArgs& b, int nseg, double flops) {
+int lin_launch(const Plan& p, hipStream_t s, BwdArgs& b, int nseg, double flops, bool narrow) {
   b.nseg = nseg;
   b.total_blocks = 0;
   for (int i = 0; i < nseg; ++i) b.total_blocks += b.seg[i].nblocks;
   b.d = p.d;
   b.h = p.d;
-  b.narrow = p.narrow;
+  b.narrow = narrow;
   return timed(LACT_KCLASS_BWD, flops, s, [&] { return launch_bwd(b, p.bf16, s); });
 }
 
@@ -1809,36 +1833,39 @@ int run_backward_linear(const lact_desc* desc, const void* q, const void* k, con
     for (const BSeg& g : segs) {
       if (!is_update(g.mode)) continue;
       const int64_t t0 = g.b, n = g.e - g.b, one = cdiv(n, 32) * 32, u = g.before;
+      const bool narrow = lin_grads_narrow(p, 1);
       BwdArgs b{};
       lin_grad_seg(b.seg[0], p, op(vb + t0 * d * esz, d, n_kv * d), op(ek + t0 * d * esz, d, n_kv * d),
-                   Pall + u * psplit, n, one);
+                   Pall + u * psplit, n, one, narrow);
       const bool app = is_apply(g.mode);
       if (app)
         lin_grad_seg(b.seg[1], p, op(ob + t0 * d * esz, d, n_q * d), op(qb + t0 * d * esz, d, n_q * d),
-                     Aall + u * psplit, n, one);
-      rc = lin_launch(p, s, b, app ? 2 : 1, (app ? 4.0 : 2.0) * BH * n * dd);
+                     Aall + u * psplit, n, one, narrow);
+      rc = lin_launch(p, s, b, app ? 2 : 1, (app ? 4.0 : 2.0) * BH * n * dd, narrow);
       if (rc) return rc;
     }
   } else if (L.batched) {
     for (int64_t c0 = 0; c0 < L.nch; c0 += L.group) {
       const int64_t t0 = c0 * C, t1 = std::min(n_kv, (c0 + L.group) * C), n = t1 - t0;
+      const bool narrow = lin_grads_narrow(p, cdiv(n, C));
       BwdArgs b{};
       lin_grad_seg(b.seg[0], p, op(vb + t0 * d * esz, d, n_kv * d), op(ek + t0 * d * esz, d, n_kv * d),
-                   Pall + c0 * psplit, n, C);
+                   Pall + c0 * psplit, n, C, narrow);
       lin_grad_seg(b.seg[1], p, op(ob + t0 * d * esz, d, n_q * d), op(qb + t0 * d * esz, d, n_q * d),
-                   Aall + c0 * psplit, n, C);
-      rc = lin_launch(p, s, b, 2, 4.0 * BH * n * dd);
+                   Aall + c0 * psplit, n, C, narrow);
+      rc = lin_launch(p, s, b, 2, 4.0 * BH * n * dd, narrow);
       if (rc) return rc;
     }
   } else {
     for (int64_t ci = 0; ci < L.nch; ++ci) {
       const int64_t t0 = ci * C, n = std::min(n_kv, t0 + C) - t0, one = cdiv(n, 32) * 32;
+      const bool narrow = lin_grads_narrow(p, 1);
       BwdArgs b{};
       lin_grad_seg(b.seg[0], p, op(vb + t0 * d * esz, d, n_kv * d), op(ek + t0 * d * esz, d, n_kv * d),
-                   Pall + ci * psplit, n, one);
+                   Pall + ci * psplit, n, one, narrow);
       lin_grad_seg(b.seg[1], p, op(ob + t0 * d * esz, d, n_q * d), op(qb + t0 * d * esz, d, n_q * d),
-                   Aall + ci * psplit, n, one);
-      rc = lin_launch(p, s, b, 2, 4.0 * BH * n * dd);
+                   Aall + ci * psplit, n, one, narrow);
+      rc = lin_launch(p, s, b, 2, 4.0 * BH * n * dd, narrow);
       if (rc) return rc;
     }
   }
@@ -1920,12 +1947,13 @@ int run_backward_linear(const lact_desc* desc, const void* q, const void* k, con
       float* tpart = reinterpret_cast<float*>(ws + L.off_tail);
       for (int64_t a = g.b; a < g.e; a += L.tail_len) {
         const int64_t n = std::min(L.tail_len, g.e - a);
+        const bool narrow = lin_narrow(p, n);
         BwdArgs b{};
         lin_grad_seg(b.seg[0], p, op(ob + a * d * esz, d, n_q * d), op(qb + a * d * esz, d, n_q * d), tpart, n,
-                     L.tail_split);
+                     L.tail_split, narrow);
         lin_out_seg(b.seg[1], p, op(ob + a * d * esz, d, n_q * d), op(wt(g.before), d, dd),
-                    (uint8_t*)dq + a * d * esz, n_q * d, n);
-        rc = lin_launch(p, s, b, 2, 4.0 * BH * n * dd);
+                    (uint8_t*)dq + a * d * esz, n_q * d, n, narrow);
+        rc = lin_launch(p, s, b, 2, 4.0 * BH * n * dd, narrow);
         if (!rc) rc = add_g(PartSet{tpart, b.seg[0].nsplit, psplit, dd});
         if (rc) return rc;
       }
@@ -1999,18 +2027,19 @@ int run_backward_linear(const lact_desc* desc, const void* q, const void* k, con
       rc = timed(LACT_KCLASS_NS, 0.0, s, [&] { return launch_copies(&cs, 1, p.BH, p.bf16, s); });
       if (rc) return rc;
     }
+    const bool narrow = lin_narrow(p, n);
     BwdArgs b{};
     lin_out_seg(b.seg[0], p, op(kb + s0 * d * esz, d, n_kv * d), op(ub, d, dd), (uint8_t*)dv + s0 * d * esz,
-                n_kv * d, n);   // Y = K Uh^T
+                n_kv * d, n, narrow);   // Y = K Uh^T
     b.seg[0].reread = true;     // by k_lin_tokens
     lin_out_seg(b.seg[1], p, op(vb + s0 * d * esz, d, n_kv * d), op(ut, d, dd), (uint8_t*)dk + s0 * d * esz,
-                n_kv * d, n);   // dk = eta (V Uh)
+                n_kv * d, n, narrow);   // dk = eta (V Uh)
     b.seg[1].row_scale = eta + s0;
     b.seg[1].scale_inst = n_kv;
     // dq = dO W with the weight the chunk was applied with
     lin_out_seg(b.seg[2], p, op(ob + s0 * d * esz, d, n_q * d), op(wt(then_apply ? ci + 1 : ci), d, dd),
-                (uint8_t*)dq + s0 * d * esz, n_q * d, n);
-    rc = lin_launch(p, s, b, applies ? 3 : 2, (applies ? 6.0 : 4.0) * BH * n * dd);
+                (uint8_t*)dq + s0 * d * esz, n_q * d, n, narrow);
+    rc = lin_launch(p, s, b, applies ? 3 : 2, (applies ? 6.0 : 4.0) * BH * n * dd, narrow);
     if (rc) return rc;
     rc = timed(LACT_KCLASS_UPDATE, 0.0, s, [&] {
       return launch_lin_tokens(vb + s0 * d * esz, eta + s0, (uint8_t*)dv + s0 * d * esz, deta + s0, p.BH, n, p.d,

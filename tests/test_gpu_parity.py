@@ -1592,6 +1592,17 @@ def test_linear_backward_fp32_small(order):
     check_linear_bwd(cfg, x, ct, run_gpu_linear_bwd(cfg, x, ct, with_dW=False), with_dW=False)
 
 
+@pytest.mark.parametrize("tail", [0, 2500])
+def test_linear_fp32_tiles_by_launch(tail):
+    # short chunks (64 x 64 tiles) beside a whole-sequence launch of the reverse
+    # (128 x 128) and an apply-only tail (128 x 128 in the forward), d past a tile
+    cfg = CONFIGS["tiny_fp32"].with_(name="linear_fp32_tiles", B=1, H=2, d=136, h=136, n_kv=2200, n_q=2200 + tail,
+                                     chunk=64, order=0, linear=1)
+    x, ct = make_inputs(cfg, 63), make_cotangents(cfg, 63)
+    check_linear(cfg, x, run_gpu_linear(cfg, x))
+    check_linear_bwd(cfg, x, ct, run_gpu_linear_bwd(cfg, x, ct))
+
+
 def test_linear_backward_narrow_tiles_without_tail():
     # d = 128 (the narrow bf16 tiles), n_q == n_kv, one chunk of a single token at the end
     cfg = CONFIGS["lm32k"].with_(name="linear_bwd_narrow", B=2, H=2, d=128, h=128, n_kv=513, n_q=513, chunk=128,
