@@ -1167,7 +1167,10 @@ struct NsBwdLayout {
   int S, m, n;
   int64_t iters;   // slices of the iterates and steps: 1 (replayed per chunk) or one per chunk (kept)
   int es;          // bytes per operand element: 2 (fp16) or 4 (fp32, with fp32 I/O)
-  size_t g, x32, p1, p2, xo, ao, bo, to, qo, so, mo, dbo, nrm, dot, dotp, pstep, ustep, ug, total;
+  bool small;      // slots that one workgroup holds whole (the forward's rule)
+  // p1, p2, qo, dbo: fp32 operands only; to2: fp16 only; none of them, nor to,
+  // so, mo and dot, with small slots
+  size_t g, x32, p1, p2, xo, ao, bo, to, to2, qo, so, mo, dbo, nrm, dot, dotp, pstep, ustep, ug, total;
 };
 
 // Chunks whose Newton-Schulz iterates and steps the backward keeps (each
@@ -1175,12 +1178,14 @@ struct NsBwdLayout {
 constexpr double kKeepIterBytes = 24.0 * (1 << 30);
 
 size_t ns_bwd_layout(const Plan& p, int steps, size_t o, NsBwdLayout* N, int64_t nch = 1) {
+  *N = NsBwdLayout{};
   N->S = p.BH * p.nmat;
   N->m = std::min(p.d, p.h);
   N->n = std::max(p.d, p.h);
   const size_t mn = (size_t)N->m * N->n, mm = (size_t)N->m * N->m, S = N->S;
   N->es = p.bf16 ? 2 : 4;
   const size_t es = (size_t)N->es;
+  N->small = p.bf16 && N->m <= kNsFusedM && N->n <= kNsFusedN;
   const double per = ((double)std::max(steps, 1) * S * (mn + 2 * mm) * es + (double)S * mn * 4.0);
   N->iters = nch > 1 && per * nch <= kKeepIterBytes ? nch : 1;
   const size_t it = (size_t)N->iters;
@@ -1191,18 +1196,24 @@ size_t ns_bwd_layout(const Plan& p, int steps, size_t o, NsBwdLayout* N, int64_t
   };
   N->g = take(S * mn * 4);
   N->x32 = take(S * mn * 4);
-  N->p1 = take(S * mn * 4);
-  N->p2 = take(S * mn * 4);
   N->xo = take(it * std::max(steps, 1) * S * mn * es);
   N->ao = take(it * std::max(steps, 1) * S * mm * es);
   N->bo = take(it * std::max(steps, 1) * S * mm * es);
-  N->to = take(S * mn * es);
-  N->qo = take(S * mm * es);
-  N->so = take(S * mm * es);
-  N->mo = take(S * mm * es);
-  N->dbo = take(S * mm * es);
+  if (!N->small) {
+    N->to = take(S * mn * es);
+    N->so = take(S * mm * es);
+    N->mo = take(S * mm * es);
+    N->dot = take(S * 4);
+    if (p.bf16) {
+      N->to2 = take(S * mn * es);
+    } else {
+      N->p1 = take(S * mn * 4);
+      N->p2 = take(S * mn * 4);
+      N->qo = take(S * mm * es);
+      N->dbo = take(S * mm * es);
+    }
+  }
   N->nrm = take(S * 4);
-  N->dot = take(S * 4);
   N->dotp = take(S * 32 * 4);   // the dot products' per-workgroup partials
   N->pstep = take(it * S * mn * 4);   // stored layouts [inst][nmat][d h]
   N->ustep = take(S * mn * 4);
@@ -1414,9 +1425,8 @@ struct NsBwd {
     a.n = N.n;
     return timed(LACT_KCLASS_NS, (a.two ? 4.0 : 2.0) * N.S * mm() * N.n, s, [&] { return launch_ns_dx(a, s); });
   }
-  // Slots that one workgroup holds whole (the forward's rule): the iteration,
-  // and its reverse, in a launch each.
-  bool small() const { return !f32() && N.m <= kNsFusedM && N.n <= kNsFusedN; }
+  // With small slots the iteration, and its reverse, in a launch each.
+  bool small() const { return N.small; }
   NsSmallArgs small_args() const {
     NsSmallArgs a{};
     a.g = at<float>(N.g);
@@ -1498,7 +1508,7 @@ struct NsBwd {
       return rc;
     }
     if (!rc) rc = lin(1, X, nullptr, nullptr, nullptr, nullptr, nullptr, 1.0f, nullptr, T);
-    uint8_t* T2 = buf(N.p1);   // the other copy of dX' (fp16: p1 holds no partials)
+    uint8_t* T2 = buf(N.to2);   // fp16: the other copy of dX'
     for (int k = steps - 1; k >= 0 && !rc; --k) {
       if (!f32()) {
         rc = symp(T, Xo(k), N.n, mn(), true, 1.0f, nullptr, 0.0f, buf(N.so));   // S = dX' X^T + X dX'^T

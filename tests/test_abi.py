@@ -484,3 +484,19 @@ def test_prologue_and_norm_backward_errors_before_any_hip_call():
     assert rms(nbytes=1) == -3
     assert rms(do=0x5008) == -2
     assert rms(ws=0x10010) == -2
+
+
+@pytest.mark.parametrize("H,d,h,parts", [(40, 128, 256, 0), (16, 512, 512, 1)])
+def test_muon_backward_workspace_holds_only_what_its_path_uses(H, d, h, parts):
+    # what Muon adds to the 16-bit backward's workspace: the forward plan's
+    # iterate, copies and Gram matrices (and a second set of weight copies for
+    # small matrices), the kept iterates of every chunk, five fp32 matrices per
+    # slot, and for slots of more than one workgroup (parts) two fp16 copies of
+    # the cotangent and of the symmetric products; no buffers of the fp32 path
+    kw = dict(B=1, H=H, d=d, h=h, n_kv=4096, n_q=4096, chunk=2048)
+    extra = P.backward_workspace_bytes(make_desc(**kw, use_muon=True)) - P.backward_workspace_bytes(make_desc(**kw))
+    m, n, S, chunks, steps = min(d, h), max(d, h), 3 * H, 2, 5
+    mn, mm = m * n, m * m
+    plan = S * (mn * 4 + 2 * mn * 2 + 3 * mm * 2 + (0 if parts else mn * 2))
+    used = S * (chunks * (steps * (mn + 2 * mm) * 2 + mn * 4) + 4 * mn * 4 + parts * (2 * mn + 2 * mm) * 2)
+    assert extra <= 1.01 * (plan + used), (extra, plan, used)
