@@ -1406,7 +1406,8 @@ struct NsBwd {
     a.m = N.m;
     a.K = K;
     a.in_inst = in_inst;
-    return timed(LACT_KCLASS_NS, (two ? 2.0 : 1.0) * N.S * mm() * (double)K, s, [&] { return launch_ns_sym(a, s); });
+    // FLOPs: a product, or a sum of two transposes, of which half is computed
+    return timed(LACT_KCLASS_NS, 2.0 * N.S * mm() * (double)K, s, [&] { return launch_ns_sym(a, s); });
   }
   int dx(const void* Y0, const void* B0, const void* Y1, const void* B1, const float* x32, float* out32,
          void* out16) const {
@@ -1445,9 +1446,9 @@ struct NsBwd {
     a.eps = (float)kNsEps;
     return a;
   }
-  double small_flops(double per) const {
-    return per * steps * N.S * (2.0 * mm() * N.n + 2.0 * mm() * N.m + 2.0 * mm() * N.n);
-  }
+  // FLOPs, as the larger slots' launches add up: per step 4 m^2 n + 2 m^3 in the
+  // replay, 6 m^2 n + 2 m^3 in the reverse
+  double small_flops(double mmn) const { return steps * N.S * (mmn * mm() * N.n + 2.0 * mm() * N.m); }
   float* pst() const { return at<float>(N.pstep) + (size_t)(ci % N.iters) * N.S * mn(); }   // the step, negated
   bool kept() const { return N.iters > 1; }
 
@@ -1469,7 +1470,7 @@ struct NsBwd {
     float* X = at<float>(N.x32);
     int rc = slabs ? gather_slabs(slabs, 1.0f, G) : gather(P, nsplit, split, -1.0f, G);
     if (small()) {
-      if (!rc) rc = timed(LACT_KCLASS_NS, small_flops(1.0), s, [&] { return launch_ns_replay(small_args(), s); });
+      if (!rc) rc = timed(LACT_KCLASS_NS, small_flops(4.0), s, [&] { return launch_ns_replay(small_args(), s); });
       if (!rc) rc = scatter(X, -1.0f, pst());
       return rc;
     }
@@ -1503,7 +1504,7 @@ struct NsBwd {
     uint8_t* T = buf(N.to);
     int rc = gather(at<float>(N.ustep), 1, 0, -1.0f, X);   // d step = -dU
     if (small()) {
-      if (!rc) rc = timed(LACT_KCLASS_NS, small_flops(2.0), s, [&] { return launch_ns_reverse(small_args(), s); });
+      if (!rc) rc = timed(LACT_KCLASS_NS, small_flops(6.0), s, [&] { return launch_ns_reverse(small_args(), s); });
       if (!rc) rc = scatter(X, -1.0f, at<float>(N.ug));
       return rc;
     }

@@ -1872,6 +1872,25 @@ def test_swiglu_muon_backward_product_tiles(d, h):
 
 
 @pytest.mark.parametrize("io,d,h", [("bf16", 64, 96), ("bf16", 160, 288), ("fp32", 40, 56)])
+def test_muon_backward_counts_the_same_flops_on_every_path(io, d, h):
+    # per chunk, matrix and step: 4 m^2 n + 2 m^3 replayed, 6 m^2 n + 2 m^3
+    # reversed, in one workgroup per slot, in fused products and in fp32
+    base = CONFIGS["lm32k_muon"] if io == "bf16" else CONFIGS["tiny_fp32"]
+    cfg = base.with_(name="muon_bwd_flops", B=1, H=2, d=d, h=h, n_kv=512, n_q=512, chunk=256, order=0, use_muon=1)
+    x, ct = make_inputs(cfg, 90), make_cotangents(cfg, 90)
+    P.timing_reset()
+    P.timing_enable(True)
+    try:
+        run_gpu_swiglu_bwd(cfg, x, ct)
+    finally:
+        P.timing_enable(False)
+    flops = P.timing_read(P.KCLASS_NAMES.index("ns"))[2]
+    P.timing_reset()
+    m, n = float(min(d, h)), float(max(d, h))
+    assert flops == cfg.n_chunks * cfg.BH * 3 * cfg.ns_steps * (10 * m * m * n + 4 * m ** 3)
+
+
+@pytest.mark.parametrize("io,d,h", [("bf16", 64, 96), ("bf16", 160, 288), ("fp32", 40, 56)])
 def test_swiglu_muon_backward_zero_gradient(io, d, h):
     # one head whose last chunk has zero rates: a zero gradient, so a zero step,
     # and a finite reverse (the norm's subgradient at 0 is 0) that must not
