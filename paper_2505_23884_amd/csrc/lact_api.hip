@@ -93,8 +93,9 @@ int check_desc(const lact_desc* d) {
   if (d->io_dtype == LACT_IO_BF16 && (d->d % 32 || d->h % 32)) return LACT_EUNSUPPORTED;
   if ((int64_t)d->B * d->H > (1 << 20)) return LACT_EUNSUPPORTED;
   if (d->n_q > ((int64_t)1 << 40)) return LACT_EUNSUPPORTED;
-  // Every launch's grid must fit the 32-bit block count: bounds with the
-  // smallest tile edge (128) for the contractions, the most splits for the
+  // Every launch's grid must fit the 32-bit block count: bounds with a tile edge
+  // of 128 for the contractions (64 with small fp32 tiles, which small_tiles
+  // takes for launches of at most 64 larger ones), the most splits for the
   // gradient, one wave per weight row for the update and 4096-element blocks
   // for the Newton-Schulz prologue (such sizes exceed any GPU's memory long
   // before they reach these bounds, but the check keeps the launches exact).
@@ -1161,8 +1162,9 @@ int run_schedule(const lact_desc* desc, const lact_segment* segs, int64_t nseg, 
 // I/O the operand copies are fp16; slots up to 128 x 256 take the whole replay
 // and the whole reverse in one workgroup each (k_ns_replay, k_ns_reverse),
 // larger ones three launches per step and direction, each product with its
-// combination in its epilogue (S and M as P Q^T + Q P^T: A, S symmetric). With fp32 I/O they are fp32: the k_bwd kinds (OUT for
-// sums along rows, GRAD2 for sums down columns) and elementwise launches.
+// combination in its epilogue (S and M as P Q^T + Q P^T: A, S symmetric). With
+// fp32 I/O they are fp32: the k_bwd kinds (OUT for sums along rows, GRAD2 for
+// sums down columns) and elementwise launches.
 struct NsBwdLayout {
   int S, m, n;
   int64_t iters;   // slices of the iterates and steps: 1 (replayed per chunk) or one per chunk (kept)

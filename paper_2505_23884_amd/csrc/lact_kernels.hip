@@ -814,11 +814,12 @@ __device__ __forceinline__ void mainloop_dma(uint8_t* smem, const View (&ops)[K:
 // of an output tile's rows, or of its columns. A 64-K stage is worked in two
 // halves: first S0 against C, keeping C's fragments of all four 16-K substeps
 // in registers, then S1 against the kept fragments. So the LDS of C and S0 is
-// free for the tile after next half a stage before S1's, every DMA has one and
-// a half stages to land in the same two LDS slots (with whole stages it has
-// one), and the DMA instructions are spread over the MFMAs one at a time
-// instead of all at once behind a barrier, where their issue stalls the
-// matrix cores (the memory pipe of a CU takes about 32 KiB in flight).
+// free for the tile after next half a stage before S1's, a DMA has one and a
+// half stages (the first of a half) to one (the last, behind its barrier) to
+// land in the same two LDS slots (with whole stages it has one), and the DMA
+// instructions are spread over the MFMAs one at a time instead of all at once
+// behind a barrier, where their issue stalls the matrix cores (the memory pipe
+// of a CU takes about 32 KiB in flight).
 // Per half: the fragments of substep s+1 are read while s multiplies; before
 // the last multiplies of a half, wait for the next half's tile and barrier.
 // Against whole 64-K stages (32-K for the gradients), one process: NVS 256K
@@ -945,9 +946,8 @@ __device__ __forceinline__ void half_mfma(f32x16_t (&acc)[2][2], const u32x4_t (
   }
 }
 
-template <typename T, class K, int SLOT = K::STAGE, class Next = NoNext>
-__device__ __forceinline__ void mainloop_split(uint8_t* smem, const View (&ops)[3], int64_t nk, Acc<K>& acc,
-                                               Next* next = nullptr) {
+template <typename T, class K, int SLOT = K::STAGE>
+__device__ __forceinline__ void mainloop_split(uint8_t* smem, const View (&ops)[3], int64_t nk, Acc<K>& acc) {
   static_assert(K::BK == 64 && K::MI == 2 && K::NI == 2 && K::NACC == 2 && K::NOPS == 3, "split kinds");
   constexpr int OC = K::SPLIT == 1 ? 2 : 0, O0 = K::SPLIT == 1 ? 0 : 1, O1 = O0 + 1;
   using DC = DmaT<K, OC>;
@@ -1108,8 +1108,9 @@ __device__ __forceinline__ void add_product(uint8_t* smem, const View& a, const 
   }
 }
 
-// Two loops on one LDS ring of NSTAGE slots of SLOT bytes: the first hands
-// its last free stage to the second (16-bit path).
+// Two loops, one after the other, on the same LDS (16-bit path): with whole
+// stages, a ring of NSTAGE slots of SLOT bytes, the first hands its last free
+// stage to the second; a split-stage loop hands nothing over.
 template <typename T, class K1, class K2, int SLOT>
 __device__ __forceinline__ void mainloop_chain(uint8_t* smem, const View (&ops1)[K1::NOPS], int64_t nk1, Acc<K1>& acc1,
                                                const View (&ops2)[K2::NOPS], int64_t nk2, Acc<K2>& acc2) {
@@ -1119,11 +1120,11 @@ __device__ __forceinline__ void mainloop_chain(uint8_t* smem, const View (&ops1)
   if constexpr (K1::SPLIT != 0) {
     mainloop_split<T, K1>(smem, ops1, nk1, acc1);
     mainloop_dma<T, K2>(smem, ops2, nk2, acc2);
-    return;
+  } else {
+    ChainNext<K2, SLOT> nx(smem, ops2);
+    mainloop_dma<T, K1, SLOT, ChainNext<K2, SLOT>>(smem, ops1, nk1, acc1, 0, false, &nx);
+    mainloop_dma<T, K2, SLOT>(smem, ops2, nk2, acc2, nx.slot < 0 ? 0 : nx.slot, nx.slot >= 0);
   }
-  ChainNext<K2, SLOT> nx(smem, ops2);
-  mainloop_dma<T, K1, SLOT, ChainNext<K2, SLOT>>(smem, ops1, nk1, acc1, 0, false, &nx);
-  mainloop_dma<T, K2, SLOT>(smem, ops2, nk2, acc2, nx.slot < 0 ? 0 : nx.slot, nx.slot >= 0);
 }
 
 template <typename T, class K>
@@ -2899,7 +2900,8 @@ __global__ __launch_bounds__(512) void k_ns_replay(const NsSmallArgs k) {
 // three products per step took three launches of 10 to 13 us over 120 slots of
 // 128 x 256; a chunk's five steps take 115 us here against 171 us, the replay
 // 44 us (k_ns_replay) against 171 us. One workgroup per slot leaves half the
-// CUs idle: what bounds both is the chain of products inside a slot.
+// CUs idle: what bounds both is the chain of products inside a slot. (256 VGPRs,
+// 7 of them spilled, 32 bytes per lane.)
 __global__ __launch_bounds__(512) void k_ns_reverse(const NsSmallArgs a) {
   constexpr int M = kNsFusedM, N = kNsFusedN, PX = N * 2, PA = M * 2, C4 = N / 4;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kNsFusedX + kNsFusedA];
