@@ -2900,8 +2900,9 @@ __global__ __launch_bounds__(512) void k_ns_replay(const NsSmallArgs k) {
 // three products per step took three launches of 10 to 13 us over 120 slots of
 // 128 x 256; a chunk's five steps take 115 us here against 171 us, the replay
 // 44 us (k_ns_replay) against 171 us. One workgroup per slot leaves half the
-// CUs idle: what bounds both is the chain of products inside a slot. (256 VGPRs,
-// 7 of them spilled, 32 bytes per lane.)
+// CUs idle: what bounds both is the chain of products inside a slot. It takes
+// all 256 VGPRs; 7 more (32 bytes per lane) are spilled before the steps' loop
+// and read back after it.
 __global__ __launch_bounds__(512) void k_ns_reverse(const NsSmallArgs a) {
   constexpr int M = kNsFusedM, N = kNsFusedN, PX = N * 2, PA = M * 2, C4 = N / 4;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kNsFusedX + kNsFusedA];
