@@ -498,7 +498,7 @@ int lact_rmsnorm_out(const lact_desc* desc, const void* o, const float* weight, 
  * given), dweight [H, d] (fp32). With r = 1 / sqrt(mean_d(o^2) + eps) and
  * g = weight * dy per element: d_o = r g - (r^3 / d) o (g . o), and dweight
  * sums dy o r over the batch and the tokens, in a fixed order: in the same
- * pass, or for long d in a second one. Its workspace,
+ * pass, or for long d or few vectors in a second one. Its workspace,
  * lact_rmsnorm_out_backward_workspace_bytes(desc, 1), holds the sums' partials
  * and, for the second pass, the per-vector r; 0 bytes without dweight.
  */

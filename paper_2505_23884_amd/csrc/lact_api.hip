@@ -45,8 +45,17 @@ int fwd_shape(bool narrow, bool bf16, int BH, int h, int64_t n, int segs) {
 // heads (153 MB) 422 and 411; 40 heads (256 MB) 645 and 649, with Muon 672 and
 // 701. Wider matrices ([1, 16, 8192, 512]: 882 and 893) and the backward's
 // replay, which writes three more arrays that are read much later ([1, 8, 9360,
-// 128]: 715 and 723), keep the non-temporal ones.
-bool fwd_reread(int64_t bytes) { return bytes <= ((int64_t)128 << 20); }
+// 128]: 715 and 723), keep the non-temporal ones. So does an apply and an update
+// in one launch (`both`) of h <= 256 that writes 4 to 64 MiB, where the write of
+// the L2s at its end seems to cost more than the shorter second launch gains. Over
+// 268 calls of h = 128 to 1024 and 2 to 100 MB, non-temporal time / ordinary was
+// 0.96 to 1.02 there (median 0.988; [1, 2, 32675, 64], h = 128, chunks of 7226:
+// 201 and 212 us), 1.013 in the median below, 1.005 above, 1.023 (0.98 to 1.13) for
+// wider h and 1.022 (0.98 to 1.09) for an update alone.
+bool fwd_reread(int64_t bytes, int h, bool both) {
+  if (both && h <= 256 && bytes > ((int64_t)4 << 20) && bytes < ((int64_t)64 << 20)) return false;
+  return bytes <= ((int64_t)128 << 20);
+}
 
 // Shape-derived plan shared by lact_workspace_bytes and lact_forward.
 struct Plan {
@@ -416,7 +425,7 @@ int apply_rows(Ctx& c, int64_t s0, int64_t s1) {
     f.w1 = c.wop[0];
     f.w2 = c.wop[1];
     f.w3 = c.wop[2];
-    f.reread = fwd_reread(p.BH * n * p.h * p.esz);
+    f.reread = fwd_reread(p.BH * n * p.h * p.esz, p.h, false);
     const double fl1 = 4.0 * p.BH * n * p.d * p.h;
     int rc = timed(LACT_KCLASS_FWD, fl1, c.s, [&] { return launch_fwd(f, p.bf16, c.s); });
     if (rc) return rc;
@@ -708,7 +717,7 @@ int update_chunk(Ctx& c, int64_t s0, int64_t s1, bool apply_too) {
   f.w1 = c.wop[0];
   f.w2 = c.wop[1];
   f.w3 = c.wop[2];
-  f.reread = fwd_reread((int64_t)(apply_too ? 4 : 3) * p.BH * n * p.h * p.esz);
+  f.reread = fwd_reread((int64_t)(apply_too ? 4 : 3) * p.BH * n * p.h * p.esz, p.h, apply_too);
   const double ffl = (apply_too ? 4.0 : 0.0) * p.BH * n * dh + 6.0 * p.BH * n * dh;
   int rc = timed(LACT_KCLASS_FWD, ffl, c.s, [&] { return launch_fwd(f, p.bf16, c.s); });
   if (rc) return rc;
