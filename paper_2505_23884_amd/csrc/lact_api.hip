@@ -123,14 +123,10 @@ int check_desc(const lact_desc* d) {
 // quarter of the fp32 MFMA time per tile (a 128 x 128 tile multiplies 16 K in
 // 2048 clocks per accumulator, mostly padding where d or h is 64) decides the
 // launch. [1, 2, 1024, 64], h = 64, chunks of 256: first launch 24 -> 7 us,
-// second 48 -> 9 us (with the gradient split every 64 tokens). In the linear
-// fast weight's forward the gradient tiles run in the same launch and fill it
-// earlier for d > 128 ([1, 1, 8192, 512], chunks of 2048, 64 tiles: 231 us in
-// large tiles, 255 in small ones, chunks of 1536, 48 tiles: 227 and 208; [1, 2,
-// 65536, 256], chunks of 2048, 64 tiles: 1291 and 1371).
-bool small_tiles(int BH, int h, int64_t T, bool linear_fwd = false) {
+// second 48 -> 9 us (with the gradient split every 64 tokens).
+bool small_tiles(int BH, int h, int64_t T) {
   const TileShape t = fwd_tile(FWD_APPLY, false, false);
-  return BH * cdiv(h, t.rows) * cdiv(std::max<int64_t>(T, 1), t.cols) <= (linear_fwd && h > 128 ? 48 : 64);
+  return BH * cdiv(h, t.rows) * cdiv(std::max<int64_t>(T, 1), t.cols) <= 64;
 }
 
 Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
@@ -146,7 +142,7 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   p.C = std::min<int64_t>(dsc->chunk, dsc->n_kv);
   const int64_t tail = dsc->n_q - dsc->n_kv;
   const int64_t tail_rows = std::min<int64_t>(tail, std::max<int64_t>(p.C, 65536));
-  p.narrow = p.bf16 ? p.d <= 128 : small_tiles(p.BH, p.h, std::max(p.C, tail_rows), p.linear);
+  p.narrow = p.bf16 ? p.d <= 128 : small_tiles(p.BH, p.h, std::max(p.C, tail_rows));
   // Small matrices with Muon (one fused Newton-Schulz workgroup each) and the
   // narrow tile shapes: the output tiles of a chunk's apply run in the
   // Newton-Schulz launch, on the CUs its one workgroup per matrix leaves idle,
@@ -172,9 +168,30 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   // partial's write and read against a block of the whole chunk: NVS 1M takes
   // 14 splits, 3 full rounds, 1% faster than 9 splits in 2 uneven rounds).
   // Lengths are a multiple of 32.
-  const TileShape g13 = bwd_tile(BWD_GRAD13, p.bf16, p.narrow), g2 = bwd_tile(BWD_GRAD2, p.bf16, p.narrow);
-  const int64_t tiles = (int64_t)p.BH * ((p.linear ? 0 : cdiv(p.h, g13.rows) * cdiv(p.d, g13.cols)) +
-                                         cdiv(p.d, g2.rows) * cdiv(p.h, g2.cols));
+  const auto grad_tiles = [&](bool narrow) -> int64_t {
+    const TileShape g13 = bwd_tile(BWD_GRAD13, p.bf16, narrow), g2 = bwd_tile(BWD_GRAD2, p.bf16, narrow);
+    return (int64_t)p.BH * ((p.linear ? 0 : cdiv(p.h, g13.rows) * cdiv(p.d, g13.cols)) +
+                            cdiv(p.d, g2.rows) * cdiv(p.h, g2.cols));
+  };
+  // (64 x 64 tiles: matrices so small that a partial costs nothing beside the
+  // idle CUs, so down to 64 tokens)
+  const auto short_split = [&](bool narrow) -> int64_t {
+    return std::min<int64_t>(std::max<int64_t>(1, cdiv(128, grad_tiles(narrow))),
+                             std::max<int64_t>(1, p.C / (!p.bf16 && narrow ? 64 : 256)));
+  };
+  // fp32 linear fast weight, more than 48 of the larger output tiles: the small
+  // form splits its four times as many gradient tiles less, and where that makes
+  // a tile's sum over tokens more than 2.5 times as long, and half as long again
+  // as an output tile's sum over d, it decides the launch. Forward, small and
+  // large: [1, 1, 8192, 512] by 2048 (4 times) 247 and 224 us, [1, 2, 8000, 512]
+  // by 1000 (3 times) 488 and 437; but [1, 1, 12000, 640] by 1500 (2.5) 433 and
+  // 524, [1, 2, 16384, 256] by 2048 (2) 300 and 312, [1, 1, 4456, 768] by 1114 (4,
+  // but 1114 tokens for d = 768) 285 and 297.
+  if (p.linear && !p.bf16 && p.narrow && p.C < 8192 &&
+      p.BH * cdiv(p.d, 128) * cdiv(std::max<int64_t>(p.C, 1), 128) > 48 &&
+      2 * short_split(false) > 5 * short_split(true) && 2 * cdiv(p.C, short_split(true)) > 3 * p.d)
+    p.narrow = false;
+  const int64_t tiles = grad_tiles(p.narrow);
   // The gradient and update kind (below) needs an unsplit gradient; it pays
   // when its row tiles cover at least half the chip and, for long chunks, when
   // apply tiles share the launch (apply-then-update, or more than one chunk)
@@ -198,10 +215,7 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
       }
     }
   } else {
-    // (64 x 64 tiles: matrices so small that a partial costs nothing beside
-    // the idle CUs, so down to 64 tokens)
-    ns = std::max<int64_t>(1, cdiv(128, tiles));
-    ns = std::min<int64_t>(ns, std::max<int64_t>(1, p.C / (!p.bf16 && p.narrow ? 64 : 256)));
+    ns = short_split(p.narrow);
   }
   ns = std::min<int64_t>(ns, kMaxSplit);
   p.split_len = std::max<int64_t>(32, cdiv(cdiv(std::max<int64_t>(p.C, 1), ns), 32) * 32);
@@ -239,6 +253,7 @@ Plan make_plan(const lact_desc* dsc, bool allow_fused = true) {
   p.muon = dsc->use_muon != 0;
   p.m = std::min(p.d, p.h);
   p.ns_bps = (int)cdiv((int64_t)dh, kNsBlockElems);
+  const TileShape g13 = bwd_tile(BWD_GRAD13, p.bf16, p.narrow), g2 = bwd_tile(BWD_GRAD2, p.bf16, p.narrow);
   p.t13 = p.linear ? 0 : (int)(cdiv(p.h, g13.rows) * cdiv(p.d, g13.cols));
   p.t2 = (int)(cdiv(p.d, g2.rows) * cdiv(p.h, g2.cols));
   // Without split the sums of squares that Newton-Schulz normalises by come

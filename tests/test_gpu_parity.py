@@ -1603,6 +1603,16 @@ def test_linear_fp32_tiles_by_launch(tail):
     check_linear_bwd(cfg, x, ct, run_gpu_linear_bwd(cfg, x, ct))
 
 
+@pytest.mark.parametrize("d, chunk", [(512, 1700), (640, 1300)])
+def test_linear_fp32_tiles_by_gradient_sum(d, chunk):
+    # 49 to 64 large output tiles: 128 x 128 tiles where the small ones would split
+    # the gradient's sum over tokens a third as often (d = 512), 64 x 64 otherwise
+    cfg = CONFIGS["tiny_fp32"].with_(name="linear_fp32_sum", B=1, H=1, d=d, h=d, n_kv=chunk + 100, n_q=chunk + 130,
+                                     chunk=chunk, order=0, linear=1)
+    x = make_inputs(cfg, 66)
+    check_linear(cfg, x, run_gpu_linear(cfg, x))
+
+
 def test_linear_backward_narrow_tiles_without_tail():
     # d = 128 (the narrow bf16 tiles), n_q == n_kv, one chunk of a single token at the end
     cfg = CONFIGS["lm32k"].with_(name="linear_bwd_narrow", B=2, H=2, d=128, h=128, n_kv=513, n_q=513, chunk=128,
