@@ -295,13 +295,17 @@ bool lin_narrow(const Plan& p, int64_t n) {
   return p.bf16 ? p.narrow : small_tiles(p.BH, p.d, p.d <= 64 ? p.C : n);
 }
 // The gradients of nch chunks in one launch, two products each: small tiles only
-// while the large ones would not fill the 256 CUs (backward [1, 4, 16384, 512],
-// chunks of 256, 8192 large tiles: 4405 us in small ones, 4311 in large; [1, 1,
-// 24576, 128], chunks of 8192, 6 tiles: 489 and 772).
+// while the large ones would not fill the 256 CUs twice (backward [1, 4, 16384,
+// 512], chunks of 256, 8192 large tiles: 4405 us in small ones, 4311 in large;
+// [1, 2, 65536, 256], chunks of 2048, 512 tiles: 1753 and 1661; [1, 1, 24576,
+// 128], chunks of 8192, 6 tiles: 489 and 772; forward and backward, [1, 2, 960,
+// 600], chunks of 320, 300 tiles: 373 and 383), or have fewer than 256 tokens to
+// sum ([1, 3, 181, 1024], one chunk, 384 tiles: 207 and 216; [1, 12, 114, 600],
+// 600 tiles: 217 and 227).
 bool lin_grads_narrow(const Plan& p, int64_t nch) {
   if (p.bf16) return p.narrow;
   const int64_t t = cdiv(p.d, bwd_tile(BWD_GRAD2, false, false).rows);
-  return small_tiles(p.BH, p.d, p.C) && (p.d <= 64 || 2 * nch * p.BH * t * t < 256);
+  return small_tiles(p.BH, p.d, p.C) && (p.d <= 64 || p.C < 256 || 2 * nch * p.BH * t * t < 512);
 }
 
 bool misaligned(const void* p) { return ((uintptr_t)p & 15) != 0; }

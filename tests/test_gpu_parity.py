@@ -1596,8 +1596,8 @@ def test_linear_backward_fp32_small(order):
 def test_linear_fp32_tiles_by_launch(tail):
     # short chunks (64 x 64 tiles) beside a whole-sequence launch of the reverse
     # (128 x 128) and an apply-only tail (128 x 128 in the forward), d past a tile
-    cfg = CONFIGS["tiny_fp32"].with_(name="linear_fp32_tiles", B=1, H=2, d=136, h=136, n_kv=2200, n_q=2200 + tail,
-                                     chunk=64, order=0, linear=1)
+    cfg = CONFIGS["tiny_fp32"].with_(name="linear_fp32_tiles", B=1, H=2, d=136, h=136, n_kv=8200, n_q=8200 + tail,
+                                     chunk=256, order=0, linear=1)
     x, ct = make_inputs(cfg, 63), make_cotangents(cfg, 63)
     check_linear(cfg, x, run_gpu_linear(cfg, x))
     check_linear_bwd(cfg, x, ct, run_gpu_linear_bwd(cfg, x, ct))
