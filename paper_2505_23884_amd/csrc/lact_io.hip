@@ -557,9 +557,11 @@ hipError_t launch_prologue_bwd(PrologueBwdArgs a, bool io_bf16, hipStream_t s) {
 // workspace it takes. Vectors of at most 4 accesses per lane (hd <= 2048 in 16
 // bits, 1024 in fp32) take one pass that holds its columns' sums in registers,
 // up to 2048 workgroups of (head, token split), if more than two accesses leave
-// at least 2 workgroups per CU. Longer ones would need so many registers (one
-// wave per SIMD) and so long partials that too few workgroups are left: they
-// take a pass of their own, split over the columns too. One pass against two,
+// at least 2 workgroups per CU or one vector per group, where the second pass
+// would only be a launch more ([1, 3, 150, 1024] fp32: 17 and 20 us). Longer ones
+// would need so many registers (one wave per SIMD) and so long partials that too
+// few workgroups are left: they take a pass of their own, split over the columns
+// too. One pass against two,
 // [1, 16, 2048, d]: bf16 d = 2048 124 and 140 us, 2560 218 and 195; fp32
 // d = 1536 252 and 196 us, 4096 809 and 517; one head, [1, 1, 32000, 1024]:
 // bf16 72 and 71, fp32 200 and 117 (287 workgroups).
@@ -575,7 +577,7 @@ RmsDwPlan rms_dw_plan(int B, int64_t L, int H, int hd, bool io_bf16) {
   // one pass: a round of its groups per workgroup at least, as many as the same room holds partials
   const int64_t ng = 256 / group, want = std::min<int64_t>((2048 + H - 1) / H, (ntok + ng - 1) / ng);
   const int64_t one = std::max<int64_t>(1, std::min<int64_t>(want, p.floats / n));
-  p.one_pass = nv <= 2 || (nv <= 4 && one * H >= 512);
+  p.one_pass = nv <= 2 || (nv <= 4 && (one * H >= 512 || one * ng >= ntok));
   p.nsplit = p.one_pass ? one : two;
   p.per = std::max<int64_t>(1, (ntok + p.nsplit - 1) / p.nsplit);
   if (p.one_pass) p.nsplit = (ntok + p.per - 1) / p.per;

@@ -1321,7 +1321,8 @@ def test_output_rmsnorm_weight_cotangent_splits(B, H, L, d, io):
 
 
 @pytest.mark.parametrize("io,d,H,L", [("fp32", 1024, 16, 256), ("fp32", 1024, 3, 150), ("fp32", 1032, 16, 256),
-                                      ("bf16", 2048, 16, 256), ("bf16", 2048, 3, 150), ("bf16", 2080, 16, 256)])
+                                      ("bf16", 2048, 16, 256), ("bf16", 2048, 3, 150), ("bf16", 2080, 16, 256),
+                                      ("fp32", 1024, 1, 3000), ("bf16", 2048, 1, 3000)])
 def test_output_rmsnorm_weight_cotangent_long_vectors(io, d, H, L):
     # either side of the length, and of the number of workgroups, at which the
     # weight's cotangent takes a pass of its own: token splits and columns that
